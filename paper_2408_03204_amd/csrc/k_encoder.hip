@@ -7,13 +7,18 @@
 // one linear head 64 -> 11 and a sigmoid. Weights are one flat float32 buffer:
 // [W1 (64 x 256 x 5), b1 (64), W2 (64 x 64 x 5), b2, ..., W6, b6, Wh (11 x 64), bh (11)].
 //
-// Training runs in float32 through hand-written kernels: forward, the mean-squared-error loss
-// against the normalised labels, the backward of every layer (input gradients and weight
-// gradients, each a fixed-order sum, so runs are bit-reproducible), and Adam. Inference can run
-// the convolutions on the matrix cores: v_mfma_f32_16x16x16_bf16 with float32 accumulation, the
-// layer as an implicit GEMM (M = 64 output channels, N = batch x frames, K = input channels x 5,
-// the input window gathered per lane, no im2col buffer).
+// Every convolution, forward and backward, is an implicit GEMM on the matrix cores without an
+// im2col buffer. Training runs in float32 on v_mfma_f32_16x16x4_f32: the instruction is a chain of
+// float32 fused multiply-adds in ascending k (compared bit for bit with fmaf on gfx950), so an
+// output has the bits of the plain loop over (channel, tap) whatever tile computes it. Inference
+// can run on v_mfma_f32_16x16x16_bf16 with float32 accumulation. The first layer (256 input
+// channels, 0.8 of the multiplications) has a tiled kernel; the others are small (a few frames a
+// sample), so one block per sample runs all of them, the pooling and the head from LDS, and the
+// backward does the same in reverse. The weight gradients of all layers share one launch split
+// over the batch, then one fixed-order sum (runs are bit-reproducible).
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "device_common.h"
 #include "grafx_internal.h"
@@ -31,8 +36,18 @@ struct EncLayout {
   size_t w[kLayers + 2], b[kLayers + 2];  // weight and bias offsets (layer 1..6, head = 7)
   size_t n_w;
   size_t y[kLayers + 1], h, act;          // activations: y_l [B][64][F_l], pooled h [B][64]
-  size_t dy[kLayers + 1], dh, dz, lossp, grad;  // backward scratch
+  size_t dy[kLayers + 1], dz, lossp, part, grad;  // backward scratch
 };
+
+// Weight-gradient work of one layer: the (sample, 64-frame tile) units are dealt to `splits`
+// contiguous ranges; each (split, 64 input channels) is a block, whose partial sums are
+// [split][64 x Cin x 5 weights, 64 biases].
+constexpr int kGradTile = 64, kMaxSplits = 64;
+int grad_tiles(int Fout) { return (Fout + kGradTile - 1) / kGradTile; }
+int grad_splits(int B, int Fout) {
+  const int64_t units = (int64_t)B * grad_tiles(Fout);
+  return (int)(units < kMaxSplits ? units : kMaxSplits);
+}
 
 int cin_of(int l) { return l == 1 ? kCin : kCh; }
 
@@ -63,164 +78,639 @@ EncLayout enc_layout(int B, int F) {
   L.h = a;
   a += (size_t)B * kCh;
   L.act = a;
-  L.dh = d;
-  d += (size_t)B * kCh;
   L.dz = d;
   d += (size_t)B * kOut;
   L.lossp = d;
   d += (size_t)B;
+  L.part = d;
+  for (int l = 1; l <= kLayers; ++l)
+    d += (size_t)grad_splits(B, L.F[l]) * kCh * (cin_of(l) * kKs + 1);
   L.grad = d;
   return L;
 }
 
-// ---- float32 layers ---------------------------------------------------------------------------
+// ---- matrix-core layers -----------------------------------------------------------------------
 
-// y[b][co][t] = ReLU(bias[co] + sum_{ci,k} W[co][ci][k] x[b][ci][2t + k - 2])
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // weights: any float address
+
+__device__ __forceinline__ short to_bf16(float f) {  // round to nearest even
+  unsigned u = __float_as_uint(f);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return (short)(u >> 16);
+}
+
+// Operand layouts, lane l = i + 16 q. v_mfma_f32_16x16x4_f32: A row i, k = q; B column i, k = q.
+// v_mfma_f32_16x16x16_bf16: k = 4 q .. 4 q + 3. Both: D column i, rows 4 q .. 4 q + 3.
+//
+// A row of K operands in LDS, read four steps at a time: in float32 lane q takes k = 4 s + q, so
+// the entries of one q are stored together ([q][s]) and one 16-byte read serves four steps; in
+// bfloat16 the natural order is already what a lane reads. Rows are padded by 4 entries, which
+// spreads the 16-byte reads of eight consecutive rows over distinct banks.
+template <bool BF16, int KC>
+struct Operand {
+  using T = typename std::conditional<BF16, short, float>::type;
+  static constexpr int kRow = KC + 4;
+  static __device__ __forceinline__ int at(int k) { return BF16 ? k : (k & 3) * (KC / 4) + (k >> 2); }
+  static __device__ __forceinline__ T put(float v) {
+    if constexpr (BF16) return to_bf16(v);
+    else return v;
+  }
+};
+
+// acc[j] += A(16 rows at a) x B(16 columns at b + j * 16 rows) over KC entries
+template <bool BF16, int KC, int NT, typename T>
+__device__ __forceinline__ void mma_chunk(const T* a, const T* b, f32x4 (&acc)[NT], int i, int q) {
+  constexpr int R = Operand<BF16, KC>::kRow;
+  if constexpr (BF16) {
+#pragma unroll
+    for (int ks = 0; ks < KC; ks += 16) {
+      const bf16x4 av = *reinterpret_cast<const bf16x4*>(a + i * R + ks + 4 * q);
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+            av, *reinterpret_cast<const bf16x4*>(b + (16 * j + i) * R + ks + 4 * q), acc[j], 0, 0,
+            0);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < KC / 4; s += 4) {
+      const f32x4 av = *reinterpret_cast<const f32x4*>(a + i * R + q * (KC / 4) + s);
+      f32x4 bv[NT];
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        bv[j] = *reinterpret_cast<const f32x4*>(b + (16 * j + i) * R + q * (KC / 4) + s);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[j][e], acc[j], 0, 0, 0);
+    }
+  }
+}
+
+// One layer over columns n = b * Fout + t: y[b][co][t] = ReLU(bias[co] + sum_{ci,k} W[co][ci][k]
+// x[b][ci][2t + k - 2]). A block computes all 64 channels of 16 NT columns, wave w the channels
+// 16 w .. 16 w + 15. K = Cin x 5 advances in chunks of CI input channels, staged in LDS while the
+// next chunk's loads are in flight. Two shapes: NT = 4, CI = 16 fills the CUs from about 200
+// blocks on (256 samples x 125 frames, layer 1, 2.6 GFLOP: 44 us, 61 TFLOP/s of the 154 that a
+// large float32 matrix product reaches; the six layers took 1105 us with one thread per output);
+// below that a chunk's load latency counts, and NT = 1, CI = 64 has four times the blocks and a
+// quarter of the chunks (4 samples in bfloat16: 14 us, 27 us with 64 columns and a block per 64).
+template <bool BF16, int NT, int CI>
 __global__ __launch_bounds__(kBlock) void conv_fwd_kernel(int B, int Cin, int Fin, int Fout,
                                                           const float* x, const float* W,
                                                           const float* bias, float* y) {
-  const int64_t n = (int64_t)B * kCh * Fout;
-  for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < n;
-       idx += (int64_t)gridDim.x * kBlock) {
-    const int t = (int)(idx % Fout), co = (int)((idx / Fout) % kCh), b = (int)(idx / Fout / kCh);
-    float acc = bias[co];
-    const float* xb = x + (int64_t)b * Cin * Fin;
-    const float* wc = W + (int64_t)co * Cin * kKs;
-    for (int ci = 0; ci < Cin; ++ci)
+  constexpr int KC = CI * kKs, COLS = 16 * NT;
+  using Op = Operand<BF16, KC>;
+  constexpr int kA = kCh * KC / 4 / kBlock;       // 4-float groups of W staged per thread
+  constexpr int kStep = kBlock / COLS, kB = CI / kStep;  // input channels staged per thread
+  __shared__ __align__(16) typename Op::T As[kCh * Op::kRow], Bs[COLS * Op::kRow];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, q = lane >> 4;
+  const int64_t N = (int64_t)B * Fout, n0 = (int64_t)blockIdx.x * COLS;
+  const int K = Cin * kKs;
+  // B staging: this thread's column and first input channel; taps outside [0, Fin) read element 0
+  // of the row and store zero
+  const int col = threadIdx.x % COLS, c0 = threadIdx.x / COLS;
+  const int64_t ns = n0 + col < N ? n0 + col : N - 1;
+  const int ts = (int)(ns % Fout);
+  const float* xcol = x + ((ns / Fout) * Cin + c0) * Fin;
+  int src[kKs], dst[kKs];
+  bool ok[kKs];
 #pragma unroll
-      for (int k = 0; k < kKs; ++k) {
-        const int src = 2 * t + k - 2;
-        if (src >= 0 && src < Fin) acc = fmaf(wc[ci * kKs + k], xb[(int64_t)ci * Fin + src], acc);
-      }
-    y[idx] = fmaxf(acc, 0.f);
+  for (int k = 0; k < kKs; ++k) {
+    const int f = 2 * ts + k - 2;
+    ok[k] = f >= 0 && f < Fin;
+    src[k] = ok[k] ? f : 0;
+    dst[k] = col * Op::kRow + Op::at(c0 * kKs + k);
+  }
+  constexpr int kDst = BF16 ? kStep * kKs : kStep * kKs / 4;  // from one staged channel to the next
+  f32x4 va[kA];
+  float vb[kB][kKs];
+  auto load = [&](int ci0) {
+#pragma unroll
+    for (int e = 0; e < kA; ++e) {
+      const int id = threadIdx.x + kBlock * e;
+      va[e] = *reinterpret_cast<const f32x4u*>(W + (id / (KC / 4)) * K + ci0 * kKs +
+                                               4 * (id % (KC / 4)));
+    }
+#pragma unroll
+    for (int j = 0; j < kB; ++j)
+#pragma unroll
+      for (int k = 0; k < kKs; ++k) vb[j][k] = xcol[(int64_t)(ci0 + kStep * j) * Fin + src[k]];
+  };
+  f32x4 acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[j][e] = BF16 ? 0.f : bias[16 * wave + 4 * q + e];
+  load(0);
+  for (int ci0 = 0; ci0 < Cin; ci0 += CI) {
+    __syncthreads();  // the previous chunk's operands have been read
+#pragma unroll
+    for (int e = 0; e < kA; ++e) {
+      const int id = threadIdx.x + kBlock * e;
+      typename Op::T* row = As + (id / (KC / 4)) * Op::kRow;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) row[Op::at(4 * (id % (KC / 4)) + k)] = Op::put(va[e][k]);
+    }
+#pragma unroll
+    for (int j = 0; j < kB; ++j)
+#pragma unroll
+      for (int k = 0; k < kKs; ++k) Bs[dst[k] + j * kDst] = Op::put(ok[k] ? vb[j][k] : 0.f);
+    __syncthreads();
+    if (ci0 + CI < Cin) load(ci0 + CI);
+    mma_chunk<BF16, KC, NT>(As + 16 * wave * Op::kRow, Bs, acc, i, q);
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int64_t n = n0 + 16 * j + i;
+    if (n >= N) continue;
+    float* yc = y + ((n / Fout) * kCh + 16 * wave + 4 * q) * Fout + n % Fout;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      yc[(int64_t)e * Fout] =
+          fmaxf(BF16 ? acc[j][e] + bias[16 * wave + 4 * q + e] : acc[j][e], 0.f);
   }
 }
 
-// Mean over frames, the linear head and the sigmoid: one block of 64 threads per sample.
-__global__ __launch_bounds__(64) void pool_head_kernel(int F6, const float* y6, const float* Wh,
-                                                       const float* bh, float* h, float* s) {
+// ---- per-sample kernels ------------------------------------------------------------------------
+
+constexpr int kTailF = 128;          // largest layer input, in frames, that a per-sample block takes
+constexpr int kK = kCh * kKs;        // 320 entries per row of a 64-channel layer's weights
+constexpr int kWRow = kK + 4;
+constexpr int kWStage = kCh * kK / 4 / kBlock;  // 4-float groups of W per thread
+
+struct TailLayers {
+  int first;                // first layer of the per-sample part (7: none)
+  int F[kLayers + 1];
+  const float* W[kLayers + 2];
+  const float* b[kLayers + 2];
+  float* y[kLayers + 1];
+  float* dy[kLayers + 1];
+};
+
+// Loads of a 64-channel layer's weights, in the order in which the threads store them to LDS.
+__device__ __forceinline__ void load_w(const float* W, f32x4 (&w)[kWStage]) {
+#pragma unroll
+  for (int e = 0; e < kWStage; ++e)
+    w[e] = reinterpret_cast<const f32x4u*>(W)[threadIdx.x + kBlock * e];
+}
+
+// Layers first .. 6, mean over frames, linear head and sigmoid of one sample per block. A layer's
+// input sits in LDS with two zero columns on either side (rows of kTailF + 5 floats), its weights
+// are staged as above while the next layer's are already being loaded; wave w computes channels
+// 16 w .. 16 w + 15, 16 frames at a time. Few frames a layer (32 .. 2 for 125 frames in), so the
+// time is the staging of 82 KB of weights a layer and the chain of 80 dependent matrix
+// instructions: 30 us for five layers, pooling and head of 256 samples, 38 us for 4 samples in
+// bfloat16 (135 us as six launches).
+template <bool BF16>
+__global__ __launch_bounds__(kBlock) void tail_fwd_kernel(TailLayers L, float* h, float* out) {
+  using Op = Operand<BF16, kK>;
+  constexpr int R = kTailF + 5;
+  __shared__ __align__(16) typename Op::T Ws[kCh * Op::kRow];
+  __shared__ float xs[kCh * R], ys[kCh * (kTailF / 2 + 5)];
   __shared__ float hs[kCh];
-  const int b = blockIdx.x, c = threadIdx.x;
-  float acc = 0.f;
-  for (int t = 0; t < F6; ++t) acc += y6[((int64_t)b * kCh + c) * F6 + t];
-  acc /= (float)F6;
-  hs[c] = acc;
-  h[(int64_t)b * kCh + c] = acc;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, q = lane >> 4;
+  const int64_t smp = blockIdx.x;
+  f32x4 w[kWStage];
+  float* in = xs;
+  float* next = ys;
+  int rin = R, rout = kTailF / 2 + 5;  // row lengths of `in` and `next`
+  if (L.first <= kLayers) {
+    load_w(L.W[L.first], w);
+    const int F = L.F[L.first - 1];
+    const float* src = L.y[L.first - 1] + smp * kCh * F;
+    for (int c = wave; c < kCh; c += kBlock / 64)
+      for (int f = lane; f < F + 5; f += 64)
+        in[c * rin + f] = f >= 2 && f < F + 2 ? src[c * F + f - 2] : 0.f;
+  }
+  for (int l = L.first; l <= kLayers; ++l) {
+    const int Fout = L.F[l];
+#pragma unroll
+    for (int e = 0; e < kWStage; ++e) {
+      const int id = threadIdx.x + kBlock * e;
+      typename Op::T* row = Ws + (id / (kK / 4)) * Op::kRow;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) row[Op::at(4 * (id % (kK / 4)) + k)] = Op::put(w[e][k]);
+    }
+    __syncthreads();
+    if (l < kLayers) load_w(L.W[l + 1], w);
+    const typename Op::T* a = Ws + (16 * wave + i) * Op::kRow;
+    const float* bias = L.b[l] + 16 * wave + 4 * q;
+    float* yg = L.y[l] + (smp * kCh + 16 * wave + 4 * q) * Fout;
+    // entry k of a column reads channel k / 5, tap k % 5: the pattern repeats every 4 channels
+    // (float32, five steps) or 16 channels (bfloat16, five steps of 16 entries)
+    for (int t0 = 0; t0 < Fout; t0 += 16) {
+      const int t = t0 + i;
+      const float* xc = in + 2 * (t < Fout ? t : Fout - 1);
+      f32x4 acc;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = BF16 ? 0.f : bias[e];
+      if constexpr (BF16) {
+        for (int c = 0; c < kCh; c += 16)
+#pragma unroll
+          for (int s = 0; s < 5; ++s) {
+            bf16x4 bv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int k = 16 * s + 4 * q + e;
+              bv[e] = to_bf16(xc[(c + k / kKs) * rin + k % kKs]);
+            }
+            const bf16x4 av = *reinterpret_cast<const bf16x4*>(a + c * kKs + 16 * s + 4 * q);
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+          }
+      } else {
+        int off[5];
+#pragma unroll
+        for (int s = 0; s < 5; ++s) off[s] = (4 * s + q) / kKs * rin + (4 * s + q) % kKs;
+#pragma unroll 1
+        for (int c = 0; c < kCh; c += 16) {  // 16 channels: 20 steps
+          const f32x4* ap = reinterpret_cast<const f32x4*>(a + q * (kK / 4) + c * kKs / 4);
+          const float* xq = xc + c * rin;
+          float bv[20];
+#pragma unroll
+          for (int s = 0; s < 20; ++s) bv[s] = xq[s / 5 * 4 * rin + off[s % 5]];
+#pragma unroll
+          for (int s = 0; s < 20; s += 4) {
+            const f32x4 av = ap[s / 4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[s + e], acc, 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = fmaxf(BF16 ? acc[e] + bias[e] : acc[e], 0.f);
+        if (t < Fout) {
+          yg[(int64_t)e * Fout + t] = v;
+          next[(16 * wave + 4 * q + e) * rout + 2 + t] = v;
+        }
+      }
+    }
+    for (int c = threadIdx.x; c < kCh; c += kBlock) {  // the next input's zero columns
+      next[c * rout] = next[c * rout + 1] = 0.f;
+      for (int f = Fout + 2; f < Fout + 5; ++f) next[c * rout + f] = 0.f;
+    }
+    __syncthreads();
+    float* const p = in;
+    in = next;
+    next = p;
+    const int r = rin;
+    rin = rout;
+    rout = r;
+  }
+  const int F6 = L.F[kLayers], c = threadIdx.x;
+  if (c < kCh) {
+    float acc = 0.f;
+    if (L.first <= kLayers)
+      for (int t = 0; t < F6; ++t) acc += in[c * rin + 2 + t];
+    else
+      for (int t = 0; t < F6; ++t) acc += L.y[kLayers][(smp * kCh + c) * F6 + t];
+    acc /= (float)F6;
+    hs[c] = acc;
+    h[smp * kCh + c] = acc;
+  }
   __syncthreads();
   if (c < kOut) {
-    float z = bh[c];
-    for (int i = 0; i < kCh; ++i) z = fmaf(Wh[c * kCh + i], hs[i], z);
-    s[(int64_t)b * kOut + c] = 1.f / (1.f + expf(-z));
+    float z = L.b[kLayers + 1][c];
+    for (int k = 0; k < kCh; ++k) z = fmaf(L.W[kLayers + 1][c * kCh + k], hs[k], z);
+    out[smp * kOut + c] = 1.f / (1.f + expf(-z));
   }
 }
 
-// Loss terms and the head's backward for one sample: dz = 2 (s - y) s (1 - s) / (B 11),
-// dh = Wh^T dz, and the gradient of the pooled frames dy6[b][c][t] = dh[c] / F6.
-__global__ __launch_bounds__(64) void head_bwd_kernel(int B, int F6, const float* s,
-                                                      const float* labels, const float* Wh,
-                                                      float* dz, float* dy6, float* lossp) {
+// Input gradient of a 64-channel layer over frames 2 s, 2 s + 1 (s in [s0, s0 + n)) from the
+// masked output gradient in LDS: gs row co holds g[co][t] at column t - s0 + 1 (columns
+// 0 .. n + 1, zero outside [0, Fout)). dx[ci][f] = sum_{co,k: f = 2t + k - 2} W[co][ci][k] g[co][t]:
+// taps 0, 2, 4 (t = s + 1, s, s - 1) for even f, taps 1, 3 (t = s + 1, s) for odd f; both chains
+// run over (co, tap) in ascending order. Ws: weights in their natural order, rows of kWRow.
+// put(ci, f, value) receives every frame f < Fin.
+template <typename Put>
+__device__ __forceinline__ void bwd_data(const float* Ws, const float* gs, int grow, int s0, int n,
+                                         int Fin, Put&& put) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, q = lane >> 4;
+  const float* wc = Ws + (16 * wave + i) * kKs;
+  int ea[3], eb[3];  // even f: entries 4 s + q = (co, tap / 2) repeat every 4 channels (3 steps)
+  int oa[2], ob[2];  // odd f: every 2 channels (1 step); two steps listed
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int k = 4 * s + q;
+    ea[s] = k / 3 * kWRow + 2 * (k % 3);
+    eb[s] = k / 3 * grow + 2 - k % 3;
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int k = 4 * s + q;
+    oa[s] = k / 2 * kWRow + 2 * (k % 2) + 1;
+    ob[s] = k / 2 * grow + 2 - k % 2;
+  }
+  for (int t0 = 0; t0 < n; t0 += 16) {
+    const int t = t0 + i;
+    const float* gc = gs + (t < n ? t : n - 1);
+    f32x4 ev = {0.f, 0.f, 0.f, 0.f}, od = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int c = 0; c < kCh; c += 4) {
+      float a0[3], b0[3], a1[2], b1[2];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        a0[s] = wc[c * kWRow + ea[s]];
+        b0[s] = gc[c * grow + eb[s]];
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        a1[s] = wc[c * kWRow + oa[s]];
+        b1[s] = gc[c * grow + ob[s]];
+      }
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        ev = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], b0[s], ev, 0, 0, 0);
+        if (s < 2) od = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[s], b1[s], od, 0, 0, 0);
+      }
+    }
+    if (t < n)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int f = 2 * (s0 + t);
+        put(16 * wave + 4 * q + e, f, ev[e]);
+        if (f + 1 < Fin) put(16 * wave + 4 * q + e, f + 1, od[e]);
+      }
+  }
+}
+
+__device__ __forceinline__ void store_w(float* Ws, const f32x4 (&w)[kWStage]) {
+#pragma unroll
+  for (int e = 0; e < kWStage; ++e) {
+    const int id = threadIdx.x + kBlock * e;
+    *reinterpret_cast<f32x4*>(Ws + (id / (kK / 4)) * kWRow + 4 * (id % (kK / 4))) = w[e];
+  }
+}
+
+// Loss terms, the head's backward and the input gradients of layers 6 .. first of one sample:
+// dz = 2 (s - y) s (1 - s) / (B 11), dh = Wh^T dz, dy6[c][t] = dh[c] / F6. What is written to
+// dy[l] is the masked gradient g = dy where y > 0, which is all that the layers below read. 32 us
+// for 256 samples x 125 frames (530 us as one launch a layer with one thread per output).
+__global__ __launch_bounds__(kBlock) void tail_bwd_kernel(int B, TailLayers L, const float* out,
+                                                          const float* labels, float* dz,
+                                                          float* lossp) {
+  constexpr int R = kTailF / 2 + 2;  // no layer output here is longer than kTailF / 2
+  __shared__ __align__(16) float Ws[kCh * kWRow];
+  __shared__ float ga[kCh * R], gb[kCh * R];
   __shared__ float dzs[kOut], sq[kOut];
-  const int b = blockIdx.x, c = threadIdx.x;
+  const int64_t smp = blockIdx.x;
+  const int c = threadIdx.x;
+  f32x4 w[kWStage];
+  if (L.first <= kLayers) load_w(L.W[kLayers], w);
   if (c < kOut) {
-    const float sv = s[(int64_t)b * kOut + c], d = sv - labels[(int64_t)b * kOut + c];
+    const float sv = out[smp * kOut + c], d = sv - labels[smp * kOut + c];
     const float g = 2.f * d / (float)(B * kOut) * sv * (1.f - sv);
     dzs[c] = g;
     sq[c] = d * d;
-    dz[(int64_t)b * kOut + c] = g;
+    dz[smp * kOut + c] = g;
   }
   __syncthreads();
-  float dh = 0.f;
-  for (int o = 0; o < kOut; ++o) dh = fmaf(Wh[o * kCh + c], dzs[o], dh);
-  for (int t = 0; t < F6; ++t) dy6[((int64_t)b * kCh + c) * F6 + t] = dh / (float)F6;
+  const int F6 = L.F[kLayers];
+  float *g = ga, *gn = gb;
+  if (c < kCh) {
+    float dh = 0.f;
+    for (int o = 0; o < kOut; ++o) dh = fmaf(L.W[kLayers + 1][o * kCh + c], dzs[o], dh);
+    const int64_t row = (smp * kCh + c) * F6;
+    for (int t = 0; t < F6; ++t) {
+      const float v = L.y[kLayers][row + t] > 0.f ? dh / (float)F6 : 0.f;
+      L.dy[kLayers][row + t] = v;
+      if (L.first <= kLayers) g[c * R + 1 + t] = v;
+    }
+    if (L.first <= kLayers) g[c * R] = g[c * R + 1 + F6] = 0.f;
+  }
   if (c == 0) {
     float a = 0.f;
     for (int o = 0; o < kOut; ++o) a += sq[o];
-    lossp[b] = a;
+    lossp[smp] = a;
+  }
+  for (int l = kLayers; l >= L.first; --l) {
+    store_w(Ws, w);
+    __syncthreads();
+    if (l > L.first) load_w(L.W[l - 1], w);
+    const int Fin = L.F[l - 1];
+    const float* y = L.y[l - 1] + smp * kCh * Fin;
+    float* dy = L.dy[l - 1] + smp * kCh * Fin;
+    bwd_data(Ws, g, R, 0, L.F[l], Fin, [&](int ci, int f, float v) {
+      v = y[ci * Fin + f] > 0.f ? v : 0.f;
+      dy[ci * Fin + f] = v;
+      if (l > L.first) gn[ci * R + 1 + f] = v;
+    });
+    if (l > L.first)
+      for (int k = threadIdx.x; k < kCh; k += kBlock) gn[k * R] = gn[k * R + 1 + Fin] = 0.f;
+    __syncthreads();
+    float* const p = g;
+    g = gn;
+    gn = p;
   }
 }
 
-// Head weight gradients (fixed order over the batch) and the loss value.
-__global__ __launch_bounds__(kBlock) void head_grad_kernel(int B, const float* dz, const float* h,
-                                                           const float* lossp, float* dWh,
-                                                           float* dbh, float* loss) {
-  for (int i = threadIdx.x; i < kOut * (kCh + 1); i += kBlock) {
-    const int o = i / (kCh + 1), c = i % (kCh + 1);
-    float acc = 0.f;
-    for (int b = 0; b < B; ++b)
-      acc = fmaf(dz[(int64_t)b * kOut + o], c < kCh ? h[(int64_t)b * kCh + c] : 1.f, acc);
-    if (c < kCh)
-      dWh[o * kCh + c] = acc;
-    else
-      dbh[o] = acc;
-  }
-  if (threadIdx.x == 0 && loss) {
-    float a = 0.f;
-    for (int b = 0; b < B; ++b) a += lossp[b];
-    *loss = a / (float)(B * kOut);
-  }
+// The same input gradient of one layer with more frames than a per-sample block holds: a block
+// takes 64 output frames of one sample.
+__global__ __launch_bounds__(kBlock) void conv_bwd_data_kernel(int Fin, int Fout, const float* W,
+                                                               const float* g, const float* y,
+                                                               float* dy) {
+  constexpr int S = 64, R = S + 2;
+  __shared__ __align__(16) float Ws[kCh * kWRow];
+  __shared__ float gs[kCh * R];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int s0 = blockIdx.x * S, n = min(S, Fout - s0);
+  const int64_t smp = blockIdx.y;
+  f32x4 w[kWStage];
+  load_w(W, w);
+  const float* gr = g + smp * kCh * Fout;
+  for (int c = wave; c < kCh; c += kBlock / 64)
+    for (int k = lane; k < n + 2; k += 64) {
+      const int t = s0 + k - 1;
+      gs[c * R + k] = t >= 0 && t < Fout ? gr[(int64_t)c * Fout + t] : 0.f;
+    }
+  store_w(Ws, w);
+  __syncthreads();
+  const float* yr = y + smp * kCh * Fin;
+  float* dr = dy + smp * kCh * Fin;
+  bwd_data(Ws, gs, R, s0, n, Fin, [&](int ci, int f, float v) {
+    const int64_t at = (int64_t)ci * Fin + f;
+    dr[at] = yr[at] > 0.f ? v : 0.f;
+  });
 }
 
-// dx[b][ci][f] = sum_{co,k: f = 2t + k - 2} W[co][ci][k] g[b][co][t], g = dy where y > 0.
-__global__ __launch_bounds__(kBlock) void conv_bwd_data_kernel(int B, int Cin, int Fin, int Fout,
-                                                               const float* W, const float* y,
-                                                               const float* dy, float* dx) {
-  const int64_t n = (int64_t)B * Cin * Fin;
-  for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < n;
-       idx += (int64_t)gridDim.x * kBlock) {
-    const int f = (int)(idx % Fin), ci = (int)((idx / Fin) % Cin), b = (int)(idx / Fin / Cin);
-    float acc = 0.f;
-    for (int co = 0; co < kCh; ++co) {
-      const int64_t row = ((int64_t)b * kCh + co) * Fout;
+// ---- weight gradients --------------------------------------------------------------------------
+
+struct GradLayer {
+  const float* x;   // layer input [B][Cin][Fin]
+  const float* g;   // masked output gradient [B][64][Fout]
+  float* part;      // [splits][64 x Cin x 5 + 64]
+  float* dw;        // weight gradient, followed by the bias gradient
+  int Cin, Fin, Fout, tiles, splits, units, blocks;
+};
+struct GradLayers {
+  GradLayer l[kLayers];
+};
+
+// dW[co][ci][k] = sum_{b,t} g[b][co][t] x[b][ci][2t + k - 2] over the units of one split and 64
+// input channels: M = co, N = ci for each tap, K = frames. Wave w holds 16 input channels x 5 taps
+// x 64 output channels in 20 accumulators, so 9 LDS reads feed 20 matrix instructions; a unit's
+// chain (at most 64 terms) is added to the running sums before the next, which keeps the error of
+// a long float32 chain out. The next unit's loads are in flight while one is computed. 71 us and
+// 9 us for the sums of 64 splits, all layers, 256 samples x 125 frames (5.1 GFLOP; one block per
+// pair of channels, reading both rows for five sums each, took 1144 us, the head's serial sums
+// over the batch 132 us).
+__global__ __launch_bounds__(kBlock, 1) void weight_grad_kernel(GradLayers P) {
+  constexpr int GR = kGradTile + 4, XR = 2 * kGradTile + 9;  // 4 and 9 modulo 64 banks
+  constexpr int kW = 2 * kGradTile + 3;                      // input frames of a unit
+  constexpr int kQ = kCh / (kBlock / 64), kX = (kW + 63) / 64;
+  __shared__ float gs[kCh * GR], xs[kCh * XR];
+  __shared__ double bsum[kBlock];
+  int blk = blockIdx.x, li = 0;
+  while (blk >= P.l[li].blocks) blk -= P.l[li++].blocks;
+  const GradLayer& L = P.l[li];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, q = lane >> 4;
+  const int split = blk % L.splits, cg = blk / L.splits;
+  const int u0 = (int)((int64_t)L.units * split / L.splits);
+  const int u1 = (int)((int64_t)L.units * (split + 1) / L.splits);
+  float xr[kQ][kX], gr[kQ];
+  auto load = [&](int u) {
+    const int64_t b = u / L.tiles;
+    const int t0 = u % L.tiles * kGradTile;
+    const float* x = L.x + (b * L.Cin + cg * kCh) * L.Fin;
+    const float* g = L.g + b * kCh * L.Fout;
 #pragma unroll
-      for (int k = 0; k < kKs; ++k) {
-        const int t2 = f + 2 - k;
-        if (t2 < 0 || (t2 & 1)) continue;
-        const int t = t2 >> 1;
-        if (t >= Fout) continue;
-        const float g = y[row + t] > 0.f ? dy[row + t] : 0.f;
-        acc = fmaf(W[((int64_t)co * Cin + ci) * kKs + k], g, acc);
+    for (int r = 0; r < kQ; ++r) {
+      const int c = wave + 4 * r;
+      gr[r] = t0 + lane < L.Fout ? g[(int64_t)c * L.Fout + t0 + lane] : 0.f;
+#pragma unroll
+      for (int k = 0; k < kX; ++k) {
+        const int col = lane + 64 * k, f = 2 * t0 - 2 + col;
+        xr[r][k] = col < kW && f >= 0 && f < L.Fin ? x[(int64_t)c * L.Fin + f] : 0.f;
       }
     }
-    dx[idx] = acc;
+  };
+  f32x4 tot[4][kKs];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int k = 0; k < kKs; ++k) tot[c][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  double db = 0.0;
+  load(u0);
+  for (int u = u0; u < u1; ++u) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kQ; ++r) {
+      const int c = wave + 4 * r;
+      gs[c * GR + lane] = gr[r];
+#pragma unroll
+      for (int k = 0; k < kX; ++k)
+        if (lane + 64 * k < kW) xs[c * XR + lane + 64 * k] = xr[r][k];
+    }
+    __syncthreads();
+    if (u + 1 < u1) load(u + 1);
+    const int nt = min(kGradTile, L.Fout - u % L.tiles * kGradTile);
+    f32x4 acc[4][kKs];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int k = 0; k < kKs; ++k) acc[c][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float* ga = gs + i * GR + q;
+    const float* xb = xs + (16 * wave + i) * XR + 2 * q;
+    for (int t = 0; t < nt; t += 4) {
+      float a[4], b[kKs];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a[c] = ga[16 * c * GR + t];
+#pragma unroll
+      for (int k = 0; k < kKs; ++k) b[k] = xb[2 * t + k];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int k = 0; k < kKs; ++k)
+          acc[c][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[k], acc[c][k], 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int k = 0; k < kKs; ++k) tot[c][k] += acc[c][k];
+    if (cg == 0) {  // bias gradient: four threads per channel, 16 frames each
+      float s = 0.f;
+#pragma unroll
+      for (int t = 0; t < kGradTile / 4; ++t)
+        s += gs[(threadIdx.x >> 2) * GR + (threadIdx.x & 3) * (kGradTile / 4) + t];
+      db += (double)s;
+    }
+  }
+  float* part = L.part + (int64_t)split * kCh * (L.Cin * kKs + 1);
+  const int ci = cg * kCh + 16 * wave + i;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int k = 0; k < kKs; ++k)
+        part[((int64_t)(16 * c + 4 * q + e) * L.Cin + ci) * kKs + k] = tot[c][k][e];
+  if (cg == 0) {
+    bsum[threadIdx.x] = db;
+    __syncthreads();
+    if (threadIdx.x < kCh) {
+      const double* s = bsum + 4 * threadIdx.x;
+      part[(int64_t)kCh * L.Cin * kKs + threadIdx.x] =
+          (float)(((s[0] + s[1]) + s[2]) + s[3]);
+    }
   }
 }
 
-// dW[co][ci][k] = sum_{b,t} g[b][co][t] x[b][ci][2t + k - 2]: one block per (co, ci) for the
-// five taps (blocks with ci = Cin give the bias gradient sum_{b,t} g); threads stride over
-// (b, t) and a fixed-order block sum combines them.
-__global__ __launch_bounds__(kBlock) void conv_bwd_weight_kernel(int B, int Cin, int Fin,
-                                                                 int Fout, const float* x,
-                                                                 const float* y, const float* dy,
-                                                                 float* dW, float* db) {
-  __shared__ float red[4];
-  const int co = blockIdx.x % kCh, ci = blockIdx.x / kCh;
-  float acc[kKs] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  const int n = B * Fout;
-  for (int i = threadIdx.x; i < n; i += kBlock) {
-    const int b = i / Fout, t = i % Fout;
-    const int64_t row = ((int64_t)b * kCh + co) * Fout;
-    const float g = y[row + t] > 0.f ? dy[row + t] : 0.f;
-    if (ci == Cin) {
-      acc[0] += g;
-      continue;
+// Sums of the splits' partials in order, in double, one thread per weight (the last blocks: the
+// head's weight gradients, one output row each, and the loss).
+__global__ __launch_bounds__(kBlock) void grad_sum_kernel(GradLayers P, int64_t weights, int B,
+                                                          const float* dz, const float* h,
+                                                          const float* lossp, float* dWh,
+                                                          float* dbh, float* loss) {
+  const int nb = (int)((weights + kBlock - 1) / kBlock);
+  if ((int)blockIdx.x < nb) {
+    int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (j >= weights) return;
+    int li = 0;
+    int64_t n = 0;
+    for (; li < kLayers; ++li) {
+      n = (int64_t)kCh * (P.l[li].Cin * kKs + 1);
+      if (j < n) break;
+      j -= n;
     }
-    const float* xr = x + ((int64_t)b * Cin + ci) * Fin;
-#pragma unroll
-    for (int k = 0; k < kKs; ++k) {
-      const int src = 2 * t + k - 2;
-      if (src >= 0 && src < Fin) acc[k] = fmaf(g, xr[src], acc[k]);
-    }
+    const float* p = P.l[li].part + j;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < P.l[li].splits; ++k) s += (double)p[(int64_t)k * n];
+    P.l[li].dw[j] = (float)s;
+    return;
   }
-  const int nk = ci == Cin ? 1 : kKs;
-  for (int k = 0; k < nk; ++k) {
-    const float v = block_sum<float>(acc[k], red);
-    if (threadIdx.x == 0) {
-      if (ci == Cin)
-        db[co] = v;
-      else
-        dW[((int64_t)co * Cin + ci) * kKs + k] = v;
+  // head: thread (c, r) sums samples r, r + 4, ...; c = 64 is the bias
+  __shared__ double red[4][kCh + 1];
+  const int o = (int)blockIdx.x - nb, c = threadIdx.x & 63, r = threadIdx.x >> 6;
+  if (o < kOut) {
+    double a = 0.0, ab = 0.0;
+#pragma unroll 8
+    for (int b = r; b < B; b += 4) {
+      const double d = dz[(int64_t)b * kOut + o];
+      a += d * (double)h[(int64_t)b * kCh + c];
+      ab += d;
     }
+    red[r][c] = a;
+    if (c == 0) red[r][kCh] = ab;
+    __syncthreads();
+    if (r == 0) dWh[o * kCh + c] = (float)(((red[0][c] + red[1][c]) + red[2][c]) + red[3][c]);
+    if (threadIdx.x == 0)
+      dbh[o] = (float)(((red[0][kCh] + red[1][kCh]) + red[2][kCh]) + red[3][kCh]);
+    return;
   }
+  double a = 0.0;
+  for (int b = threadIdx.x; b < B; b += kBlock) a += (double)lossp[b];
+  a = block_sum<double>(a, red[0]);
+  if (threadIdx.x == 0) *loss = (float)(a / (double)(B * kOut));
 }
 
 __global__ __launch_bounds__(kBlock) void adam_kernel(int64_t n, float* p, const float* g,
@@ -300,105 +790,40 @@ __global__ __launch_bounds__(kBlock) void params_kernel(const float* s, float* g
   }
 }
 
-// ---- bfloat16 matrix-core convolution (inference) ----------------------------------------------
-
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ short to_bf16(float f) {  // round to nearest even
-  unsigned u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (short)(u >> 16);
-}
-
-// A block computes all 64 output channels over 64 columns n = b * Fout + t. The K dimension
-// (in channel x tap, K = Cin * 5) advances in chunks of 128: the block stages the weight chunk
-// A[64][128] and the gathered input chunk Bt[64 columns][128] in LDS as bfloat16 (nearest even),
-// then wave w multiplies rows 16 w .. 16 w + 15 against the four 16-column tiles, eight K steps
-// of v_mfma_f32_16x16x16_bf16 each. Large chunks amortise the global-load latency of staging,
-// which bounds the kernel at these sizes. Operands per lane l = i + 16 q: A row i, K entries 4q..4q+3;
-// B column i, K entries 4q..4q+3; D column i, rows 4q..4q+3. Rows of the LDS tiles are padded
-// by 4 bf16 so the 16 lanes of a fragment read distinct banks.
-constexpr int kMN = 64, kKC = 128, kLd = kKC + 4;
-constexpr int kStage = kKC / 4;  // K entries staged per thread and chunk
-
-__global__ __launch_bounds__(kBlock) void conv_fwd_mfma_kernel(int B, int Cin, int Fin, int Fout,
-                                                               const float* x, const float* W,
-                                                               const float* bias, float* y) {
-  __shared__ short As[kMN * kLd], Bs[kMN * kLd];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = lane & 15, q = lane >> 4;
-  const int N = B * Fout, K = Cin * kKs;
-  const int n0 = blockIdx.x * kMN;
-  // staging roles. A: thread r covers channel r / 4 and the kStage consecutive K entries
-  // kStage (r % 4) .. (contiguous weights). B: thread r covers column r % 64 and the K entries
-  // kStage (r / 64) .., so a wave reads 64 neighbouring columns (frames two samples apart) at
-  // every K entry.
-  const int srow = threadIdx.x >> 2, sk = (threadIdx.x & 3) * kStage;
-  const int bn = threadIdx.x & 63, bk = (threadIdx.x >> 6) * kStage;
-  const int n_s = n0 + bn;
-  const bool live_s = n_s < N;
-  const int b_s = live_s ? n_s / Fout : 0, t_s = live_s ? n_s % Fout : 0;
-  // one wave-uniform descriptor per tensor (per-lane descriptors would make the compiler loop
-  // over the lanes for every load); the host keeps both tensors below 2^29 elements
-  const auto rx = row_rsrc(x, (int64_t)B * Cin * Fin);
-  const auto rw = row_rsrc(W, (int64_t)kCh * K);
-  const int xbase = b_s * Cin * Fin, wbase = srow * K;
-  f32x4 acc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += kKC) {
-    __syncthreads();  // the previous chunk's fragments have been read
-    float va[kStage], vb[kStage];  // every load of the chunk in flight before any is used
-#pragma unroll
-    for (int e = 0; e < kStage; ++e) {  // branch-free: out-of-range offsets read 0 in hardware
-      const int ka = k0 + sk + e;
-      va[e] = bload(rw, ka < K ? wbase + ka : -1);
-      const int kb = k0 + bk + e;
-      const int ci = kb / kKs, tap = kb % kKs;
-      const int src = 2 * t_s + tap - 2;
-      const bool ok = live_s && kb < K && src >= 0 && src < Fin;
-      vb[e] = bload(rx, ok ? xbase + ci * Fin + src : -1);
-    }
-#pragma unroll
-    for (int e = 0; e < kStage; ++e) {
-      As[srow * kLd + sk + e] = to_bf16(va[e]);
-      Bs[bn * kLd + bk + e] = to_bf16(vb[e]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < kKC; ks += 16) {
-      bf16x4 a;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = As[(wave * 16 + i) * kLd + ks + 4 * q + e];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bf16x4 bv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bv[e] = Bs[(j * 16 + i) * kLd + ks + 4 * q + e];
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bv, acc[j], 0, 0, 0);
-      }
-    }
-  }
-  float bsum[4];  // this lane's four channels, loaded once before the stores
-#pragma unroll
-  for (int e = 0; e < 4; ++e) bsum[e] = bias[wave * 16 + 4 * q + e];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = n0 + j * 16 + i;
-    if (n >= N) continue;
-    const int b = n / Fout, t = n % Fout;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int co = wave * 16 + 4 * q + e;
-      y[((int64_t)b * kCh + co) * Fout + t] = fmaxf(acc[j][e] + bsum[e], 0.f);
-    }
-  }
-}
-
 unsigned grid_for(int64_t n) {
   const int64_t g = (n + kBlock - 1) / kBlock;
   return (unsigned)(g < 65536 ? (g > 0 ? g : 1) : 65536);
+}
+
+// The per-sample kernels take the layers from the first whose input fits their LDS; the first
+// layer always runs in the tiled kernel.
+TailLayers tail_layers(const EncLayout& L, const float* weights, float* acts, float* grads) {
+  TailLayers t{};
+  t.first = 2;
+  while (t.first <= kLayers && L.F[t.first - 1] > kTailF) ++t.first;
+  for (int l = 0; l <= kLayers; ++l) t.F[l] = L.F[l];
+  for (int l = 1; l <= kLayers + 1; ++l) {
+    t.W[l] = weights + L.w[l];
+    t.b[l] = weights + L.b[l];
+  }
+  for (int l = 1; l <= kLayers; ++l) {
+    t.y[l] = acts + L.y[l];
+    t.dy[l] = grads ? grads + L.dy[l] : nullptr;
+  }
+  return t;
+}
+
+// 64-column tiles from 200 blocks on, 16-column tiles below (same bits).
+template <bool BF16>
+void launch_conv_fwd(int B, int Cin, int Fin, int Fout, const float* x, const float* W,
+                     const float* bias, float* y, hipStream_t s) {
+  const int64_t n = (int64_t)B * Fout;
+  if (n >= 200 * 64)
+    conv_fwd_kernel<BF16, 4, 16><<<(unsigned)((n + 63) / 64), kBlock, 0, s>>>(B, Cin, Fin, Fout, x,
+                                                                             W, bias, y);
+  else
+    conv_fwd_kernel<BF16, 1, 64><<<(unsigned)((n + 15) / 16), kBlock, 0, s>>>(B, Cin, Fin, Fout, x,
+                                                                             W, bias, y);
 }
 
 grafx_status hip_st(hipError_t e, const char* what) {
@@ -465,30 +890,21 @@ grafx_status grafx_encoder_forward(int32_t batch, int32_t frames, const float* x
   if (bf16 && (int64_t)batch * kCin * frames >= ((int64_t)1 << 29))
     return fail(GRAFX_E_SHAPE, "bf16 forward: batch x 256 x frames must be below 2^29");
   const EncLayout L = enc_layout(batch, frames);
+  TailLayers t = tail_layers(L, weights, acts, nullptr);
   const float* in = x;
-  hipError_t e = hipSuccess;
-  for (int l = 1; l <= kLayers && e == hipSuccess; ++l) {
+  for (int l = 1; l < t.first; ++l) {
     float* y = acts + L.y[l];
-    const int Cin = cin_of(l);
-    if (bf16) {
-      const int cols = batch * L.F[l];
-      conv_fwd_mfma_kernel<<<(cols + kMN - 1) / kMN, kBlock, 0, stream>>>(
-          batch, Cin, L.F[l - 1], L.F[l], in, weights + L.w[l], weights + L.b[l], y);
-    } else {
-      const int64_t n = (int64_t)batch * kCh * L.F[l];
-      conv_fwd_kernel<<<grid_for(n), kBlock, 0, stream>>>(batch, Cin, L.F[l - 1], L.F[l], in,
-                                                          weights + L.w[l], weights + L.b[l], y);
-    }
-    e = hipGetLastError();
+    if (bf16)
+      launch_conv_fwd<true>(batch, cin_of(l), L.F[l - 1], L.F[l], in, t.W[l], t.b[l], y, stream);
+    else
+      launch_conv_fwd<false>(batch, cin_of(l), L.F[l - 1], L.F[l], in, t.W[l], t.b[l], y, stream);
     in = y;
   }
-  if (e == hipSuccess) {
-    pool_head_kernel<<<batch, 64, 0, stream>>>(L.F[kLayers], acts + L.y[kLayers],
-                                               weights + L.w[kLayers + 1],
-                                               weights + L.b[kLayers + 1], acts + L.h, out);
-    e = hipGetLastError();
-  }
-  return hip_st(e, "encoder_forward launch");
+  if (bf16)
+    tail_fwd_kernel<true><<<batch, kBlock, 0, stream>>>(t, acts + L.h, out);
+  else
+    tail_fwd_kernel<false><<<batch, kBlock, 0, stream>>>(t, acts + L.h, out);
+  return hip_st(hipGetLastError(), "encoder_forward launch");
 }
 
 grafx_status grafx_encoder_backward(int32_t batch, int32_t frames, const float* x,
@@ -501,28 +917,43 @@ grafx_status grafx_encoder_backward(int32_t batch, int32_t frames, const float* 
   if (!x || !weights || !acts || !out || !labels || !dweights || !grads)
     return fail(GRAFX_E_ARG, "NULL argument");
   const EncLayout L = enc_layout(batch, frames);
-  head_bwd_kernel<<<batch, 64, 0, stream>>>(batch, L.F[kLayers], out, labels,
-                                            weights + L.w[kLayers + 1], grads + L.dz,
-                                            grads + L.dy[kLayers], grads + L.lossp);
-  head_grad_kernel<<<1, kBlock, 0, stream>>>(batch, grads + L.dz, acts + L.h, grads + L.lossp,
-                                             dweights + L.w[kLayers + 1],
-                                             dweights + L.b[kLayers + 1], loss);
-  hipError_t e = hipGetLastError();
-  for (int l = kLayers; l >= 1 && e == hipSuccess; --l) {
-    const int Cin = cin_of(l);
-    const float* xin = l == 1 ? x : acts + L.y[l - 1];
-    const float* y = acts + L.y[l];
-    const float* dy = grads + L.dy[l];
-    conv_bwd_weight_kernel<<<kCh * (Cin + 1), kBlock, 0, stream>>>(
-        batch, Cin, L.F[l - 1], L.F[l], xin, y, dy, dweights + L.w[l], dweights + L.b[l]);
-    if (l > 1) {
-      const int64_t n = (int64_t)batch * Cin * L.F[l - 1];
-      conv_bwd_data_kernel<<<grid_for(n), kBlock, 0, stream>>>(
-          batch, Cin, L.F[l - 1], L.F[l], weights + L.w[l], y, dy, grads + L.dy[l - 1]);
+  const TailLayers t = tail_layers(L, weights, const_cast<float*>(acts), grads);
+  tail_bwd_kernel<<<batch, kBlock, 0, stream>>>(batch, t, out, labels, grads + L.dz,
+                                                grads + L.lossp);
+  for (int l = t.first - 1; l >= 2; --l)
+    for (int b0 = 0; b0 < batch; b0 += 65535) {  // samples on the grid's second dimension
+      const int64_t in = (int64_t)b0 * kCh * L.F[l - 1], o = (int64_t)b0 * kCh * L.F[l];
+      conv_bwd_data_kernel<<<dim3((L.F[l] + 63) / 64, std::min(batch - b0, 65535)), kBlock, 0,
+                             stream>>>(L.F[l - 1], L.F[l], t.W[l], t.dy[l] + o, t.y[l - 1] + in,
+                                       t.dy[l - 1] + in);
     }
-    e = hipGetLastError();
+  GradLayers P;
+  int blocks = 0;
+  int64_t n_w = 0;
+  float* part = grads + L.part;
+  for (int l = 1; l <= kLayers; ++l) {
+    GradLayer& G = P.l[l - 1];
+    G.x = l == 1 ? x : t.y[l - 1];
+    G.g = t.dy[l];
+    G.part = part;
+    G.dw = dweights + L.w[l];
+    G.Cin = cin_of(l);
+    G.Fin = L.F[l - 1];
+    G.Fout = L.F[l];
+    G.tiles = grad_tiles(G.Fout);
+    G.splits = grad_splits(batch, G.Fout);
+    G.units = batch * G.tiles;
+    G.blocks = G.splits * (G.Cin / kCh);
+    blocks += G.blocks;
+    const int64_t n = (int64_t)kCh * (G.Cin * kKs + 1);
+    n_w += n;
+    part += G.splits * n;
   }
-  return hip_st(e, "encoder_backward launch");
+  weight_grad_kernel<<<blocks, kBlock, 0, stream>>>(P);
+  grad_sum_kernel<<<(unsigned)((n_w + kBlock - 1) / kBlock + kOut + 1), kBlock, 0,
+                    stream>>>(P, n_w, batch, grads + L.dz, acts + L.h, grads + L.lossp,
+                              dweights + L.w[kLayers + 1], dweights + L.b[kLayers + 1], loss);
+  return hip_st(hipGetLastError(), "encoder_backward launch");
 }
 
 grafx_status grafx_adam(int64_t n, float* p, const float* g, float* m, float* v,

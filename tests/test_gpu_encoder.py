@@ -172,3 +172,44 @@ def test_gather_is_a_copy():
     torch.cuda.synchronize()
     assert torch.equal(x, torch.cat([feats[dry.long()], mixf[mix.long()]], dim=1))
     assert torch.equal(lab, table[dry.long()])
+
+
+@pytest.mark.parametrize("B,F", [(1, 1), (3, 2), (2, 257), (1, 1100), (65, 9)])
+def test_layer_tilings_match_oracle(B, F):
+    """Forward and backward where the work is cut differently: one and two frames; layer 2 or
+    layers 2-4 too long for the per-sample kernels (more than 128 input frames); fewer, as many
+    and more (sample, tile) units than weight-gradient splits. Random features; same tolerances as
+    above."""
+    say(f"[encoder tilings] B={B} F={F}")
+    rng = np.random.default_rng(100 * B + F)
+    x = (0.4 * rng.standard_normal((B, 256, F))).astype(np.float32)
+    lab = rng.uniform(size=(B, 11)).astype(np.float32)
+    w, ws = _weights(2)
+    net = enc.Encoder(torch.as_tensor(w).cuda(), B, F)
+    xd, ld = torch.as_tensor(x).cuda(), torch.as_tensor(lab).cuda()
+    out = net.forward(xd).cpu().numpy()
+    net.backward(xd, ld)
+    torch.cuda.synchronize()
+    ws64 = [t.clone().requires_grad_(True) for t in ws]
+    ref_out = E.forward(torch.as_tensor(x, dtype=F64), ws64)
+    ref_loss = ((ref_out - torch.as_tensor(lab, dtype=F64)) ** 2).mean()
+    grads = torch.autograd.grad(ref_loss, ws64)
+    assert float(np.max(np.abs(out - ref_out.detach().numpy()))) <= 1e-5
+    assert abs(float(net.loss) - float(ref_loss.detach())) <= 1e-5 * float(ref_loss.detach())
+    dw, o = net.dw.cpu().numpy(), 0
+    for i, g in enumerate(grads):
+        e = grad_err(dw[o:o + g.numel()], g.reshape(-1).numpy())
+        assert e <= 1e-3, (i, e)
+        o += g.numel()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_forward_bits_do_not_depend_on_the_batch(bf16):
+    """205 samples take the 64-column tiles of layer 1, 3 samples the 16-column ones: the same
+    samples give the same bits."""
+    x = torch.randn((205, 256, 125), generator=torch.Generator().manual_seed(3)).cuda() * 0.4
+    w = torch.as_tensor(_weights(0)[0]).cuda()
+    many = enc.Encoder(w, 205, 125).forward(x, bf16=bf16)
+    few = enc.Encoder(w, 3, 125).forward(x[:3].contiguous(), bf16=bf16)
+    torch.cuda.synchronize()
+    assert torch.equal(many[:3], few)
