@@ -25,7 +25,6 @@ struct GraphView {
   int64_t T;                 // row stride (and the length of every node when len is null)
   int32_t K;                 // number of input nodes (= sigma positions [0, K))
   int32_t out_begin;         // sigma position of the first output node
-  int32_t vec4;              // T and every node length are multiples of 4 (16-byte vectors)
   int32_t pw_unroll;         // pointwise kernels: 1024-sample parts per block (1, 2 or 4)
   int32_t wait_polls;        // dynamics kernels: reads of a published chunk state before giving up
   int32_t eq_order;          // EQ kernels: 0 tiles of a node on one XCD, 1 hardware block order

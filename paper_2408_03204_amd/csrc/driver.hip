@@ -152,7 +152,6 @@ GraphView make_view(const grafx_schedule_t* h, const void* dev_plan, int64_t T, 
   g.T = T;
   g.K = h->K;
   g.out_begin = h->step_ptr[h->N];
-  g.vec4 = (T % 4 == 0) && h->len4;
   g.pw_unroll = h->pw_unroll;
   g.wait_polls = h->wait_polls;
   g.eq_order = h->eq_order;

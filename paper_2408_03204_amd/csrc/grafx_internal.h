@@ -46,7 +46,6 @@ struct grafx_schedule_t {
   std::vector<int32_t> param_row;  // [V]
   std::vector<int32_t> node_len;   // [V] per-node signal length (sigma order); empty = all T
   int32_t max_len = 0;             // largest node length (0 when uniform)
-  bool len4 = true;                // every node length is a multiple of 4
   int32_t pw_unroll = 1;           // tuning: pointwise 1024-sample parts per block
   int32_t ar_max_pass = 16;        // attack/release forward: branch-pattern passes (1..16)
   int32_t wait_polls = 1 << 24;    // dynamics kernels: polls of a chunk wait before giving up

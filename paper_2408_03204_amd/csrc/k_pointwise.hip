@@ -4,12 +4,15 @@
 // Types: mix / out (identity, Eq. 1b only), gain_pan (Eq. 2), imager (Eq. 3), tanh distortion.
 // One block of 256 threads covers 1024 x UN samples of one node (both channels), UN = 1, 2 or 4
 // being a tuning setting of the schedule; blockIdx.y picks the node inside the step. Thread j
-// covers samples 4j..4j+3 of each 1024-sample part of the tile: with T and every node
-// length multiples of 4, rows are 16-byte aligned and it moves one float4 per channel and input;
-// otherwise it moves the 4 samples one by one. Inputs are read through raw buffer resources sized to their node's
-// length, so samples past an input's length read as zero without a branch, and are summed in
-// original edge order, so a node's arithmetic does not depend on the step it was batched into.
-// A node's own samples past its length are neither computed nor stored.
+// covers samples 4j..4j+3 of each 1024-sample part of the tile and moves them as one 16-byte
+// access per channel and input. The hardware takes such an access at any 4-byte boundary, so rows
+// of odd lengths (whose starts are not 16-byte aligned) use it too; only the last tile of a node
+// whose length is not a multiple of 4 moves the samples one by one, because a group of four there
+// may cross the row's end. (64 tracks of gain_pan -> imager -> tanh at T = 250,007, render and
+// adjoint: 424 us, 5.7 TB/s, where one-by-one moves took 908 us.) Inputs are read through raw buffer resources
+// sized to their node's length, so samples past an input's length read as zero without a branch,
+// and are summed in original edge order, so a node's arithmetic does not depend on the step it was
+// batched into. A node's own samples past its length are neither computed nor stored.
 #include "device_common.h"
 #include "grafx_internal.h"
 #include "kernels.h"
@@ -50,9 +53,9 @@ __device__ __forceinline__ void fwd_op(float& l, float& r, Gains k) {
   }
 }
 
-// Streaming store of 4 floats (16-byte aligned): marked non-temporal, since a step's output rows
+// Streaming store of 4 floats (any 4-byte boundary): marked non-temporal, since a step's output rows
 // are read back only by later steps, long after the caches have turned over.
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void nt_store4(float* p, float a, float b, float c, float d) {
   __builtin_nontemporal_store(v4f{a, b, c, d}, reinterpret_cast<v4f*>(p));
 }
@@ -73,13 +76,16 @@ __device__ __forceinline__ void bload_n(__amdgpu_buffer_rsrc_t r, int idx, float
   }
 }
 
+// Whether the groups of four samples of the tile at `base` are each wholly inside or wholly outside
+// a row of Tn samples (uniform over the block).
+__device__ __forceinline__ bool whole_groups(int64_t base, int tile, int64_t Tn) {
+  return (Tn & 3) == 0 || base + tile <= Tn;
+}
+
 template <int TYPE, bool V4, int UN>
-__global__ __launch_bounds__(kBlock) void pointwise_fwd_kernel(GraphView g, float* U,
-                                                               const float* P, int node_begin) {
-  const int node = node_begin + blockIdx.y;
-  const int64_t T = g.T, Tn = node_len(g, node);
-  const int64_t base = (int64_t)blockIdx.x * (kTile * UN);
-  if (base >= Tn) return;  // tile past the node's length (uniform over the block)
+__device__ __forceinline__ void fwd_tile(const GraphView& g, float* U, const float* P, int node,
+                                         int64_t Tn, int64_t base) {
+  const int64_t T = g.T;
   const Gains k = load_gains<TYPE>(P, g.param_row[node]);
   const int e0 = g.in_ptr[node], e1 = g.in_ptr[node + 1];
   float* y = U + (int64_t)node * 2 * T;
@@ -140,6 +146,19 @@ __global__ __launch_bounds__(kBlock) void pointwise_fwd_kernel(GraphView g, floa
   }
 }
 
+template <int TYPE, int UN>
+__global__ __launch_bounds__(kBlock) void pointwise_fwd_kernel(GraphView g, float* U,
+                                                               const float* P, int node_begin) {
+  const int node = node_begin + blockIdx.y;
+  const int64_t Tn = node_len(g, node);
+  const int64_t base = (int64_t)blockIdx.x * (kTile * UN);
+  if (base >= Tn) return;  // tile past the node's length (uniform over the block)
+  if (whole_groups(base, kTile * UN, Tn))
+    fwd_tile<TYPE, true, UN>(g, U, P, node, Tn, base);
+  else
+    fwd_tile<TYPE, false, UN>(g, U, P, node, Tn, base);
+}
+
 // Adjoint of one pointwise step. `dst` receives the input adjoint (dU, or dS for the input step,
 // whose rows are indexed the same way). Parameter-gradient partials (one per block and
 // parameter, double) go to part[(slot * tiles + tile) * NP + j].
@@ -188,20 +207,13 @@ __device__ __forceinline__ void adj_op(float yl, float yr, float ul_in, float ur
 }
 
 template <int TYPE, bool V4, int UN>
-__global__ __launch_bounds__(kBlock) void pointwise_bwd_kernel(GraphView g, float* dst,
-                                                               const float* P, int node_begin,
-                                                               double* part, int tiles) {
-  constexpr int NP = AdjOp<TYPE>::NP;
-  const int node = node_begin + blockIdx.y;
-  const int64_t T = g.T, Tn = node_len(g, node);
-  const int slot = g.param_row[node];
-  const Gains k = load_gains<TYPE>(P, slot);
+__device__ __forceinline__ void bwd_tile(const GraphView& g, float* dst, int node, int64_t Tn,
+                                         int64_t base, Gains k, float* acc) {
+  const int64_t T = g.T;
   const int o0 = g.out_ptr[node], o1 = g.out_ptr[node + 1];
   const int i0 = g.in_ptr[node], i1 = g.in_ptr[node + 1];
   const float* yrow = g.U + (int64_t)node * 2 * T;  // used by gain_pan / imager only
   float* d = dst + (int64_t)node * 2 * T;
-  float acc[NP > 0 ? NP : 1] = {0.f};
-  const int64_t base = (int64_t)blockIdx.x * (kTile * UN);
   constexpr int NV = V4 ? 4 : 1;
   // Thread j covers samples base + kTile u + 4j .. + 3 (u < UN) in both paths, in the same order,
   // so the gradient partials are accumulated identically whichever path a launch takes. Blocks
@@ -256,6 +268,23 @@ __global__ __launch_bounds__(kBlock) void pointwise_bwd_kernel(GraphView g, floa
   }
   (void)i0;
   (void)i1;
+}
+
+template <int TYPE, int UN>
+__global__ __launch_bounds__(kBlock) void pointwise_bwd_kernel(GraphView g, float* dst,
+                                                               const float* P, int node_begin,
+                                                               double* part, int tiles) {
+  constexpr int NP = AdjOp<TYPE>::NP;
+  const int node = node_begin + blockIdx.y;
+  const int64_t Tn = node_len(g, node);
+  const int slot = g.param_row[node];
+  const Gains k = load_gains<TYPE>(P, slot);
+  float acc[NP > 0 ? NP : 1] = {0.f};
+  const int64_t base = (int64_t)blockIdx.x * (kTile * UN);
+  if (whole_groups(base, kTile * UN, Tn))
+    bwd_tile<TYPE, true, UN>(g, dst, node, Tn, base, k, acc);
+  else
+    bwd_tile<TYPE, false, UN>(g, dst, node, Tn, base, k, acc);
   if constexpr (NP > 0) {
     __shared__ double red[4];
 #pragma unroll
@@ -286,10 +315,7 @@ template <int TYPE, int UN>
 void fwd_un(const GraphView& g, float* U, const float* P, int node_begin, int n_nodes,
             hipStream_t s) {
   dim3 grid((unsigned)((g.T + kTile * UN - 1) / (kTile * UN)), (unsigned)n_nodes);
-  if (g.vec4)
-    pointwise_fwd_kernel<TYPE, true, UN><<<grid, kBlock, 0, s>>>(g, U, P, node_begin);
-  else
-    pointwise_fwd_kernel<TYPE, false, UN><<<grid, kBlock, 0, s>>>(g, U, P, node_begin);
+  pointwise_fwd_kernel<TYPE, UN><<<grid, kBlock, 0, s>>>(g, U, P, node_begin);
 }
 
 template <int TYPE>
@@ -308,12 +334,7 @@ void bwd_un(const GraphView& g, float* dst, const float* P, int node_begin, int 
             double* part, hipStream_t s) {
   const int tiles = (int)((g.T + kTile * UN - 1) / (kTile * UN));
   dim3 grid((unsigned)tiles, (unsigned)n_nodes);
-  if (g.vec4)
-    pointwise_bwd_kernel<TYPE, true, UN><<<grid, kBlock, 0, s>>>(g, dst, P, node_begin, part,
-                                                                 tiles);
-  else
-    pointwise_bwd_kernel<TYPE, false, UN><<<grid, kBlock, 0, s>>>(g, dst, P, node_begin, part,
-                                                                  tiles);
+  pointwise_bwd_kernel<TYPE, UN><<<grid, kBlock, 0, s>>>(g, dst, P, node_begin, part, tiles);
 }
 
 template <int TYPE>

@@ -504,12 +504,10 @@ grafx_status grafx_schedule_with_lengths(int32_t num_nodes, const int32_t* node_
   if (st != GRAFX_OK) return st;
   h->node_len.resize(h->V);
   h->max_len = 0;
-  h->len4 = true;
   for (int i = 0; i < h->V; ++i) {
     const int32_t n = node_len[h->perm[i]];
     h->node_len[i] = n;
     h->max_len = std::max(h->max_len, n);
-    h->len4 = h->len4 && (n % 4 == 0);
   }
   build_plan(h);
   *out = h;

@@ -98,6 +98,29 @@ def test_empty_and_trivial_graphs():
         check_render(w, sched, Y, U)
 
 
+@pytest.mark.parametrize("T", [3, 1023, 1025, 4096 + 1022])
+def test_pointwise_odd_lengths(T):
+    """Rows that do not start on 16-byte boundaries, with one, two and three samples past the last
+    whole group and a last tile of one sample: forward and adjoint of a gain, imager and tanh
+    chain against the oracle (the usual tolerances)."""
+    say(f"[pointwise odd] T={T}")
+    b = synth.GraphBuilder()
+    i0, i1 = b.add(synth.IN), b.add(synth.IN)
+    a, z = b.chain([synth.GAIN_PAN, synth.IMAGER, synth.TANH, synth.MIX, synth.OUT])
+    b.connect(i0, a)
+    b.connect(i1, a)
+    g = b.build()
+    w = synth.Workload("odd", g, synth.make_sources(synth.rng_for(7, 1), 2, T),
+                       synth.draw_params(synth.rng_for(7, 2), g), None, T, 7)
+    sched = Schedule(g.node_type, g.edges)
+    S, P = device_inputs(w)
+    Y, U = render(sched, S, P, return_U=True)
+    torch.cuda.synchronize()
+    check_render(w, sched, Y, U)
+    for k, e in run_backward(w, 8).items():
+        assert e <= GRAD_TOL, (k, e)
+
+
 # ---- adjoint -------------------------------------------------------------------------------
 
 
