@@ -267,11 +267,13 @@ grafx_status grafx_render(const grafx_schedule_t* sched, const void* dev_plan, i
  * library instead of a caller buffer.
  *
  *   dev_plan, T, S, P, U, stream   exactly as for grafx_render
- * Scratch: one array of GRAFX_NOALLOC_SCRATCH_BYTES (32 MiB) per GPU, in the library's code
- * object; each GPU the library runs on holds it until the process ends. The first call on a
+ * Scratch: one array per GPU, in the library's code object: GRAFX_NOALLOC_SCRATCH_BYTES (32 MiB)
+ * and seven times as much for the slot spectra of multitap delays (2,112 bytes per slot and node,
+ * which count apart); each GPU the library runs on holds it until the process ends. The first call on a
  * device (the device current on the calling thread, which must own `stream`) looks up the
  * array's address there; no call allocates or frees memory. A render whose forward workspace
- * (grafx_workspace_bytes with with_backward = 0) exceeds the scratch fails with
+ * (grafx_workspace_bytes with with_backward = 0), less its delay spectra, exceeds
+ * GRAFX_NOALLOC_SCRATCH_BYTES fails with
  * GRAFX_E_WORKSPACE before any device work: use grafx_render then. The call clears what must
  * start at zero (the dynamics chunk states and the error word) itself; everything else it
  * writes before reading.
@@ -352,7 +354,7 @@ grafx_status grafx_render_backward_step(const grafx_schedule_t* sched, const voi
  *     2 (default) interleaves a launch of at least 4096 blocks (several rounds of resident
  *     blocks) and keeps a smaller one contiguous. Chunks are still taken in ticket order per
  *     node: same bits.
- *   GRAFX_TUNE_TAP_TILES: time tiles (2048 samples) per block of the delay's tap-gradient pass:
+ *   GRAFX_TUNE_TAP_TILES: half tiles (237 samples) per group of the delay's tap gradients:
  *     4, 8 or 16 (default); sets the grouping of the tap-gradient partial sums.
  * Two settings bound the iterative parts of the dynamics kernels instead:
  *   GRAFX_TUNE_AR_MAX_PASSES: branch-pattern passes of the attack/release compressor's forward

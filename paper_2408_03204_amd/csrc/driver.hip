@@ -12,8 +12,14 @@
 // Workspace of grafx_render_noalloc: a file-scope device array, one copy per GPU, held until the
 // process ends. In host code its name is not a device address: the address comes from
 // hipGetSymbolAddress, looked up once per device (with that device current) by noalloc_scratch.
+// The public limit holds for the workspace without the delays' slot spectra, which come on top: at
+// most 6.6 bytes for each of the limit's, since a slot's taps and delay (320 bytes) are inside it.
 static constexpr size_t kNoallocScratchBytes = GRAFX_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
+static constexpr size_t kNoallocSpecBytes = 7 * kNoallocScratchBytes;
+static_assert(grafx::delay_spec(1) * sizeof(float2) <=
+                  7 * (grafx::delay_coef(1) * sizeof(float) + 2 * sizeof(int32_t)),
+              "the spectra of every delay that fits the limit fit the scratch");
+static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes + kNoallocSpecBytes];
 
 namespace grafx {
 namespace {
@@ -23,7 +29,7 @@ namespace {
 // compressor nodes (by parameter slot) followed by the noisegate nodes: both run the same
 // envelope scan and share one set of chunk totals, carries, tickets and gradient partials.
 struct WsLayout {
-  size_t eq_h, eq_H, comp_agg, comp_carry, comp_tickets, delay_taps[2], delay_offs[2];
+  size_t eq_h, eq_H, comp_agg, comp_carry, comp_tickets, delay_taps[2], delay_spec[2], delay_offs[2];
   size_t ar_slots, ar_carry, ar_pat, ar_tickets;
   size_t rv_Un, rv_h, rv_H, rv_Z, rv_C;
   size_t fwd_end;
@@ -91,6 +97,9 @@ WsLayout ws_layout(const grafx_schedule_t* h, int64_t T, bool with_bwd) {
   L.rv_Z = take(n_rv * rv_nb * kRvStride * sizeof(float4));
   L.rv_C = take(n_rv * (n_rv ? (size_t)rv_conv_tiles(h->rv_len) : 0) * rv_nb * kRvStride *
                 sizeof(float4));
+  for (int f = 0; f < 2; ++f)  // last: the allocation-free render counts these apart
+    L.delay_spec[f] = take((size_t)h->type_count[kDelayType[f]] * delay_spec(kDelaySlots[f]) *
+                           sizeof(float2));
   L.fwd_end = off;
   if (with_bwd) {
     const size_t tiles = pointwise_tiles(T);
@@ -106,7 +115,7 @@ WsLayout ws_layout(const grafx_schedule_t* h, int64_t T, bool with_bwd) {
     // sized for the smallest tap-gradient group, so that the size does not depend on tuning
     for (int f = 0; f < 2; ++f)
       L.delay_part[f] = take((size_t)h->type_count[kDelayType[f]] * delay_groups(T, kTapTilesMin) *
-                             delay_coef(kDelaySlots[f]) * sizeof(float));
+                             delay_lags(kDelaySlots[f]) * sizeof(float));
     L.ar_ragg = take(n_ar * chunks * 2 * sizeof(uint64_t));
     L.ar_part = take(n_ar * chunks * kArParams * sizeof(double));
     L.rv_Y0 = take(n_rv * rv_nb * kRvStride * sizeof(float4));
@@ -264,7 +273,7 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
     case GRAFX_DELAY:
     case GRAFX_DELAY_LONG: {
       const int f = delay_family(t);
-      return launch_delay_fwd(kDelaySlots[f], g, U, at<float>(ws, L.delay_taps[f]),
+      return launch_delay_fwd(kDelaySlots[f], g, U, at<float2>(ws, L.delay_spec[f]),
                               at<int32_t>(ws, L.delay_offs[f]), b, cnt, stream);
     }
     case GRAFX_COMPRESSOR_AR: {
@@ -309,7 +318,7 @@ hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const
     case GRAFX_DELAY:
     case GRAFX_DELAY_LONG: {
       const int f = delay_family(t);
-      hipError_t e = launch_delay_bwd(kDelaySlots[f], g, dU, at<float>(ws, L.delay_taps[f]),
+      hipError_t e = launch_delay_bwd(kDelaySlots[f], g, dU, at<float2>(ws, L.delay_spec[f]),
                                       at<int32_t>(ws, L.delay_offs[f]), b, cnt,
                                       at<float>(ws, L.delay_part[f]), stream);
       // R[n] = sum_t ybar[t - 19] u[t - n]: lag n - 19 of the plain correlation
@@ -359,8 +368,8 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
   for (int f = 0; f < 2 && e == hipSuccess; ++f)
     if (h->type_count[kDelayType[f]] > 0)
       e = launch_delay_design(kDelaySlots[f], par(kDelayType[f]), h->type_count[kDelayType[f]],
-                              at<float>(ws, L.delay_taps[f]), at<int32_t>(ws, L.delay_offs[f]),
-                              stream);
+                              at<float>(ws, L.delay_taps[f]), at<float2>(ws, L.delay_spec[f]),
+                              at<int32_t>(ws, L.delay_offs[f]), stream);
   if (e == hipSuccess && h->type_count[GRAFX_REVERB] > 0)
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,
                          at<double2>(ws, L.rv_Un), at<float>(ws, L.rv_h), at<float4>(ws, L.rv_H),
@@ -439,10 +448,17 @@ grafx_status grafx_render_noalloc(const grafx_schedule_t* h, const void* dev_pla
   // the same checks as grafx_render with a stand-in workspace of the scratch's size (aligned, not
   // dereferenced), so that a request beyond the scratch fails before any HIP call
   void* const stand_in = reinterpret_cast<void*>(uintptr_t{256});
-  grafx_status st = check_common(h, dev_plan, T, S, P, U, stand_in, kNoallocScratchBytes, false);
+  size_t need = 0, spectra = 0;
+  if (h && T >= 1) {
+    const WsLayout L = ws_layout(h, T, false);
+    need = L.delay_spec[0];
+    spectra = L.fwd_end - need;
+  }
+  grafx_status st =
+      check_common(h, dev_plan, T, S, P, U, stand_in, kNoallocScratchBytes + spectra, false);
   if (st == GRAFX_E_WORKSPACE)
     return fail(GRAFX_E_WORKSPACE,
-                "grafx_render_noalloc needs " + std::to_string(ws_layout(h, T, false).total) +
+                "grafx_render_noalloc needs " + std::to_string(need) +
                     " bytes of scratch; its static scratch holds " +
                     std::to_string(kNoallocScratchBytes) + " bytes (use grafx_render)");
   if (st != GRAFX_OK) return st;

@@ -52,7 +52,7 @@ struct grafx_schedule_t {
   int32_t eq_order = 0;            // tuning: EQ block order (0 XCD-contiguous, 1 hardware order)
   int32_t dyn_order = 2;           // tuning: dynamics block order (0 node-major, 1 interleaved,
                                    // 2 interleaved only for launches of many blocks)
-  int32_t tap_tiles = 16;          // tuning: delay tiles per tap-gradient block (4, 8 or 16)
+  int32_t tap_tiles = 16;          // tuning: delay gradient group, in half tiles (4, 8 or 16)
   const float* rv_noise = nullptr; // reverb noise realisation (device, [2][rv_len]; borrowed)
   int64_t rv_len = 0;              // its length: the reverb FIR length
   int32_t delay_surrogate = 0;     // delay phasors: 0 no gradient, 1 straight-through surrogate

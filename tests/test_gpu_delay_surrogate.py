@@ -140,3 +140,19 @@ def test_phasor_regularise_matches_the_oracle_helpers(delay_type, M):
     got = dPd.cpu().numpy().reshape(n, 2, M, 22).astype(np.float64)
     assert np.array_equal(got[..., 2:], dP[..., 2:])
     assert np.max(np.abs(got - want)) < 1e-5 * max(1.0, np.max(np.abs(want)))
+
+
+@pytest.mark.parametrize("T", [1, 20, 474, 475, 8 * 474 + 1])
+def test_delay_tile_edges(T):
+    """Lengths at the edges of the 474-sample tiles and of a group of eight tiles, with first-slot
+    delays of 0, 1, 18 and 19 samples (windows that start before the row) and, past the first slot,
+    delays beyond the signal's end; forward and adjoint against the oracle."""
+    say(f"[delay tiles] T={T}")
+    w = delay_graph(T, 83)
+    q = w.params[synth.DELAY].reshape(-1, 2, 5, 22)
+    for i, d in enumerate((0, 1, 18, 19)):
+        for c in range(2):
+            ph = -2.0 * np.pi * ((d + c) % 4410) / 4410
+            q[i, c, 0, 0], q[i, c, 0, 1] = np.cos(ph), np.sin(ph)
+    errs, _, _ = run(w, 7, surrogate=False)
+    check(errs)

@@ -9,6 +9,7 @@ T out of range / misaligned buffer / missing parameter tensor -> GRAFX_E_SHAPE, 
 small -> GRAFX_E_WORKSPACE, step out of range -> GRAFX_E_ARG."""
 import ctypes
 
+import numpy as np
 import pytest
 
 import synth
@@ -178,6 +179,21 @@ def test_noalloc_render_refuses_a_workspace_beyond_its_scratch():
     assert sched.workspace_bytes(small, False) <= (32 << 20)
     if not _has_device():
         assert noalloc(sched, T=small) == 8  # GRAFX_E_HIP
+        assert b"scratch address" in load().grafx_last_error()
+
+
+@pytest.mark.parametrize("kind,n", [(synth.DELAY, 20000), (synth.DELAY_LONG, 5000)])
+def test_noalloc_render_counts_delay_spectra_apart(kind, n):
+    """Graphs whose delays' taps and delay times (1,600 or 6,400 bytes a node) fit the 32 MiB pass
+    validation, though with the slot spectra their workspace is several times as large."""
+    types = np.full(n + 2, kind, dtype=np.int32)
+    types[0], types[-1] = synth.IN, synth.OUT
+    ids = np.arange(1, n + 1)
+    edges = np.concatenate([[np.zeros(n, int), ids], [ids, np.full(n, n + 1)]], axis=1)
+    sched = Schedule(types, edges, "greedy")
+    assert sched.workspace_bytes(4096, False) > (128 << 20)
+    if not _has_device():
+        assert noalloc(sched, T=4096) == 8  # GRAFX_E_HIP: validation passed, no device
         assert b"scratch address" in load().grafx_last_error()
 
 
