@@ -95,8 +95,7 @@ WsLayout ws_layout(const grafx_schedule_t* h, int64_t T, bool with_bwd) {
   L.rv_h = take(n_rv * 2 * rv_L * sizeof(float));
   L.rv_H = take(n_rv * rv_P * kRvStride * sizeof(float4));
   L.rv_Z = take(n_rv * rv_nb * kRvStride * sizeof(float4));
-  L.rv_C = take(n_rv * (n_rv ? (size_t)rv_conv_tiles(h->rv_len) : 0) * rv_nb * kRvStride *
-                sizeof(float4));
+  L.rv_C = take(n_rv * rv_nb * kRvStride * sizeof(float4));
   for (int f = 0; f < 2; ++f)  // last: the allocation-free render counts these apart
     L.delay_spec[f] = take((size_t)h->type_count[kDelayType[f]] * delay_spec(kDelaySlots[f]) *
                            sizeof(float2));

@@ -149,9 +149,8 @@ int rv_grad_blocks(int64_t L);  // blocks of the mask-gradient pass (frames in g
 hipError_t launch_rv_design(const float* P, int n, const float* noise, int64_t L, double2* Un,
                             float* h, float4* Hs, hipStream_t s);
 // Z: float4 [n][blocks][kRvStride] per-channel one-sided spectra of the input windows (kept for
-// the adjoint); C: float4 [n][rv_conv_tiles(L)][blocks][kRvStride] partial product spectra
-// (scratch, shared by the forward and the adjoint)
-int rv_conv_tiles(int64_t L);
+// the adjoint); C: float4 [n][blocks][kRvStride] product spectra (scratch, shared by the forward
+// and the adjoint)
 hipError_t launch_rv_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int64_t L,
                          const float4* Hs, float4* Z, float4* C, hipStream_t s);
 // Y0: float4 [n][blocks][kRvStride] spectra of the output-adjoint blocks (kept for the FIR

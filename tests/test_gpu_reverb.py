@@ -113,6 +113,17 @@ def test_single_reverb(T, L):
     check(run(w, noise, 3))
 
 
+@pytest.mark.parametrize("T,L", [(15 * 2048, 3 * 2048), (17 * 2048 + 1, 17 * 2048 + 1),
+                                 (3 * 2048 + 7, 66 * 2048 + 11)])
+def test_product_edges(T, L):
+    """Block counts of 15, 18 and 4 against the 16 output blocks of a wave; partition counts of 3, 18
+    and 67 against its unrolling by 16, the 11 partitions of a cross-spectrum wave and the 64 lanes
+    that sum bin 2048."""
+    say(f"[reverb product edges] T={T} L={L}")
+    w, noise = single_reverb(T, L, 66)
+    check(run(w, noise, 7))
+
+
 @pytest.mark.parametrize("T,L", [(5 * 2048 + 300, 7000), (2 ** 14, synth.REVERB_LEN)])
 def test_reverb_graph(T, L):
     say(f"[reverb graph] T={T} L={L}")
