@@ -209,33 +209,30 @@ bool has_dynamics(const grafx_schedule_t* h) {
   return n_dynamics(h) + h->type_count[GRAFX_COMPRESSOR_AR] > 0;
 }
 
-// Reset the dynamics chaining state of one pass (all compressor and noisegate nodes, all steps).
-// The forward reset also clears the error word, which sits just before the forward tickets; it
-// runs whenever the graph has any dynamics node (attack/release compressors included).
-hipError_t reset_comp(const grafx_schedule_t* h, void* ws, const WsLayout& L, bool bwd,
-                      int64_t T, hipStream_t stream) {
+// Prepare the dynamics state of one pass (all compressor and noisegate nodes, all steps): chaining
+// state reset, coefficients formed from P. The forward call also clears the error word; it runs
+// whenever the graph has any dynamics node (attack/release compressors included).
+hipError_t prepare_comp(const grafx_schedule_t* h, const float* const* P, void* ws,
+                        const WsLayout& L, bool bwd, int64_t T, hipStream_t stream) {
   const int n_comp = n_dynamics(h);
   if (!has_dynamics(h) || (bwd && n_comp == 0)) return hipSuccess;
-  uint64_t* tot = at<uint64_t>(ws, bwd ? L.comp_ragg : L.comp_agg);
-  if (bwd)
-    return launch_comp_reset(tot, (int64_t)n_comp * comp_chunks(T), tickets(ws, L, h, true),
-                             n_comp * kCompTicketStride, stream);
-  return launch_comp_reset(tot, (int64_t)n_comp * comp_chunks(T), error_word(ws, L),
-                           (1 + n_comp) * kCompTicketStride, stream);
+  return launch_dyn_prepare(false, at<uint64_t>(ws, bwd ? L.comp_ragg : L.comp_agg),
+                            (int64_t)n_comp * comp_chunks(T), tickets(ws, L, h, bwd),
+                            bwd ? nullptr : error_word(ws, L), P ? P[GRAFX_COMPRESSOR] : nullptr,
+                            h->type_count[GRAFX_COMPRESSOR], P ? P[GRAFX_NOISEGATE] : nullptr,
+                            h->type_count[GRAFX_NOISEGATE], stream);
 }
 
-// Reset the attack/release chaining state of one pass.
-hipError_t reset_ar(const grafx_schedule_t* h, void* ws, const WsLayout& L, bool bwd, int64_t T,
-                    hipStream_t stream) {
+// The same for the attack/release compressors.
+hipError_t prepare_ar(const grafx_schedule_t* h, const float* const* P, void* ws, const WsLayout& L,
+                      bool bwd, int64_t T, hipStream_t stream) {
   const int n_ar = h->type_count[GRAFX_COMPRESSOR_AR];
   if (n_ar == 0) return hipSuccess;
   const size_t chunks = comp_chunks(T);
   unsigned* t = at<unsigned>(ws, L.ar_tickets) + (bwd ? (size_t)n_ar * kCompTicketStride : 0);
-  if (bwd)
-    return launch_comp_reset(at<uint64_t>(ws, L.ar_ragg), (int64_t)(n_ar * chunks * 2), t,
-                             n_ar * kCompTicketStride, stream);
-  return launch_comp_reset(at<uint64_t>(ws, L.ar_slots), (int64_t)(n_ar * ar_slot_words(chunks)),
-                           t, n_ar * kCompTicketStride, stream);
+  return launch_dyn_prepare(true, at<uint64_t>(ws, bwd ? L.ar_ragg : L.ar_slots),
+                            (int64_t)n_ar * (bwd ? chunks * 2 : ar_slot_words(chunks)), t, nullptr,
+                            P[GRAFX_COMPRESSOR_AR], n_ar, nullptr, 0, stream);
 }
 
 // The dynamics block order of one launch: the setting, or for "auto" (2) interleaved nodes once a
@@ -265,7 +262,7 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
       return launch_eq_fwd(g, U, at<float>(ws, L.eq_H), b, cnt, stream);
     case GRAFX_COMPRESSOR:
     case GRAFX_NOISEGATE:
-      return launch_comp_fwd(dyn_view(g, cnt), U, p, b, cnt, dyn_row(h, t), t == GRAFX_NOISEGATE,
+      return launch_comp_fwd(dyn_view(g, cnt), U, b, cnt, dyn_row(h, t), t == GRAFX_NOISEGATE,
                              at<uint64_t>(ws, L.comp_agg),
                              at<double>(ws, L.comp_carry), tickets(ws, L, h, false),
                              error_word(ws, L), stream);
@@ -278,7 +275,7 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
     case GRAFX_COMPRESSOR_AR: {
       const size_t n_ar = h->type_count[GRAFX_COMPRESSOR_AR], chunks = comp_chunks(g.T);
       uint64_t* slots = at<uint64_t>(ws, L.ar_slots);
-      return launch_comp_ar_fwd(dyn_view(g, cnt), U, p, b, cnt, h->ar_max_pass, slots,
+      return launch_comp_ar_fwd(dyn_view(g, cnt), U, b, cnt, h->ar_max_pass, slots,
                                 slots + n_ar * (size_t)kArPasses * chunks * 3,
                                 at<double>(ws, L.ar_carry), at<uint16_t>(ws, L.ar_pat),
                                 at<unsigned>(ws, L.ar_tickets), error_word(ws, L), stream);
@@ -310,7 +307,7 @@ hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const
       return launch_eq_bwd(g, dU, at<float>(ws, L.eq_H), b, cnt, at<float>(ws, L.eq_C), stream);
     case GRAFX_COMPRESSOR:
     case GRAFX_NOISEGATE:
-      return launch_comp_bwd(dyn_view(g, cnt), dU, p, b, cnt, dyn_row(h, t), t == GRAFX_NOISEGATE,
+      return launch_comp_bwd(dyn_view(g, cnt), dU, b, cnt, dyn_row(h, t), t == GRAFX_NOISEGATE,
                              at<double>(ws, L.comp_carry),
                              at<uint64_t>(ws, L.comp_ragg), at<double>(ws, L.comp_part),
                              tickets(ws, L, h, true), error_word(ws, L), stream);
@@ -331,7 +328,7 @@ hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const
       return e;
     }
     case GRAFX_COMPRESSOR_AR:
-      return launch_comp_ar_bwd(dyn_view(g, cnt), dU, p, b, cnt, at<double>(ws, L.ar_carry),
+      return launch_comp_ar_bwd(dyn_view(g, cnt), dU, b, cnt, at<double>(ws, L.ar_carry),
                                 at<uint16_t>(ws, L.ar_pat), at<uint64_t>(ws, L.ar_ragg),
                                 at<double>(ws, L.ar_part),
                                 at<unsigned>(ws, L.ar_tickets) +
@@ -373,8 +370,8 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,
                          at<double2>(ws, L.rv_Un), at<float>(ws, L.rv_h), at<float4>(ws, L.rv_H),
                          stream);
-  if (e == hipSuccess) e = reset_comp(h, ws, L, false, T, stream);
-  if (e == hipSuccess) e = reset_ar(h, ws, L, false, T, stream);
+  if (e == hipSuccess) e = prepare_comp(h, P, ws, L, false, T, stream);
+  if (e == hipSuccess) e = prepare_ar(h, P, ws, L, false, T, stream);
   for (int n = 1; n <= h->N && e == hipSuccess; ++n)
     e = enqueue_fwd_step(h, g, P, U, ws, L, n, stream);
   return hip_status(e, "render launch");
@@ -483,8 +480,8 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   g.dU = dU;
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
   auto dpar = [&](int t) -> float* { return dP ? dP[t] : nullptr; };
-  hipError_t e = reset_comp(h, ws, L, true, T, stream);
-  if (e == hipSuccess) e = reset_ar(h, ws, L, true, T, stream);
+  hipError_t e = prepare_comp(h, P, ws, L, true, T, stream);
+  if (e == hipSuccess) e = prepare_ar(h, P, ws, L, true, T, stream);
   for (int n = h->N - 1; n >= 1 && e == hipSuccess; --n)
     e = enqueue_bwd_step(h, g, P, dU, ws, L, n, stream);
   if (e == hipSuccess && dS && h->K > 0)  // adjoint of the input step: sum over output edges
@@ -544,8 +541,8 @@ grafx_status grafx_render_step(const grafx_schedule_t* h, const void* dev_plan, 
   const GraphView g = make_view(h, dev_plan, T, S, U);
   hipError_t e = hipSuccess;
   const bool ar = h->step_type[step] == GRAFX_COMPRESSOR_AR;
-  if (is_dynamics(h->step_type[step]) || ar) e = reset_comp(h, ws, L, false, T, stream);
-  if (e == hipSuccess && ar) e = reset_ar(h, ws, L, false, T, stream);
+  if (is_dynamics(h->step_type[step]) || ar) e = prepare_comp(h, P, ws, L, false, T, stream);
+  if (e == hipSuccess && ar) e = prepare_ar(h, P, ws, L, false, T, stream);
   if (e == hipSuccess) e = enqueue_fwd_step(h, g, P, U, ws, L, step, stream);
   return hip_status(e, "render_step launch");
 }
@@ -564,9 +561,9 @@ grafx_status grafx_render_backward_step(const grafx_schedule_t* h, const void* d
   g.dY = dY;
   g.dU = dU;
   hipError_t e = hipSuccess;
-  if (is_dynamics(h->step_type[step])) e = reset_comp(h, ws, L, true, T, stream);
+  if (is_dynamics(h->step_type[step])) e = prepare_comp(h, P, ws, L, true, T, stream);
   if (e == hipSuccess && h->step_type[step] == GRAFX_COMPRESSOR_AR)
-    e = reset_ar(h, ws, L, true, T, stream);
+    e = prepare_ar(h, P, ws, L, true, T, stream);
   if (e == hipSuccess) e = enqueue_bwd_step(h, g, P, dU, ws, L, step, stream);
   return hip_status(e, "render_backward_step launch");
 }

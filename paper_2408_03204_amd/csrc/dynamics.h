@@ -25,72 +25,144 @@ static_assert(kPer * 8 == 96, "one padding word per 8 segments");
 constexpr double kEps = 1e-8;
 constexpr uint64_t kNotReady = ~0ull;
 
-// Coefficient structs passed to the curves provide thr (T), knee (W), c = 1/R - 1 and
-// g1 = 1 - R, inv2w = 1/(2W), inv4w = 1/(4W) (0 for a hard knee) and invR2 = 1/R^2.
-struct Curve {
-  float e, dG, dT, dW, dR;
+// ---- gain curves ------------------------------------------------------------------------------
+// Both curves (Eqs. 10-11 and the noisegate's) are a coefficient times one ramp function of the
+// distance d between the log-envelope and the threshold (compressor: d = G_u - T, c = 1/R - 1;
+// noisegate: d = T - G_u, c = 1 - R), G_y - G_u = c f(d):
+//   f(d) = m^2 / (4 W) + max(d - W, 0),  m = clamp(d + W, 0, 2 W),
+// which is 0 below the knee, (d + W)^2 / (4 W) inside it and d above it, with f'(d) = m / (2 W) and
+// df/dW = f' (1 - f') in all three regions, so no region is selected per sample. A hard knee
+// (W <= 0) is W = 0 with f' a step. Logarithms are base 2 throughout: what is stored is in those
+// units, the threshold as a sum of two floats.
+struct CurveCoef {
+  float thr_hi, thr_lo;  // T
+  float w, w_2;          // W (0 for a hard knee), 2 W
+  float inv2w, inv4w;    // 1/(2W), 1/(4W) (0 for a hard knee)
+  float c;               // 1/R - 1 (compressor) or 1 - R (noisegate)
+  float kR;              // -dc/dR in natural-log units: ln 2 / R^2 or ln 2
 };
 
-// e = G_y - G_u of the quadratic-knee curve (Eqs. 10-11) and its partial derivatives, without
-// branches: the three regions (below the knee, inside it, above it) are selected per lane.
-template <bool GRAD, class K>
-__device__ __forceinline__ Curve comp_curve(float Gu, const K& k) {
-  const float d = Gu - k.thr;
-  const float q = d + k.knee;
-  const bool soft = k.knee > 0.f;
-  const bool below = soft ? (q < 0.f) : (d < 0.f);  // Gu < T - W (soft) or Gu < T (hard)
-  const bool knee = soft && !below && d < k.knee;   // T - W <= Gu < T + W
-  Curve o;
-  const float e_knee = k.c * q * q * k.inv4w, e_lin = k.c * d;
-  o.e = below ? 0.f : (knee ? e_knee : e_lin);
-  if (GRAD) {
-    const float g_knee = k.c * q * k.inv2w;
-    o.dG = below ? 0.f : (knee ? g_knee : k.c);
-    o.dT = -o.dG;
-    const float w_knee = k.c * (q * k.inv2w - q * q * k.inv4w * (2.f * k.inv2w));
-    o.dW = knee ? w_knee : 0.f;
-    const float r_knee = -q * q * k.inv4w * k.invR2, r_lin = -d * k.invR2;
-    o.dR = below ? 0.f : (knee ? r_knee : r_lin);
-  } else {
-    o.dG = o.dT = o.dW = o.dR = 0.f;
-  }
-  return o;
+__device__ __forceinline__ CurveCoef make_curve(double thr, double knee, double ratio, bool gate) {
+  constexpr double log2e = 1.4426950408889634074, ln2 = 0.69314718055994530942;
+  CurveCoef k;
+  const double t = thr * log2e, w = knee > 1e-30 ? knee * log2e : 0.0;  // 1/(4W) in float's range
+  k.thr_hi = (float)t;
+  k.thr_lo = fabsf(k.thr_hi) < INFINITY ? (float)(t - (double)k.thr_hi) : 0.f;
+  k.w = (float)w;
+  k.w_2 = (float)(2.0 * w);
+  k.inv2w = w > 0.0 ? (float)(0.5 / w) : 0.f;
+  k.inv4w = w > 0.0 ? (float)(0.25 / w) : 0.f;
+  k.c = (float)(gate ? 1.0 - ratio : 1.0 / ratio - 1.0);
+  k.kR = (float)(gate ? ln2 : ln2 / (ratio * ratio));
+  return k;
 }
 
-// Noisegate curve (Sec. 3 "Noisegate"): e = 0 at or above T + W, (1 - R)(G_u - T - W)^2 / (4W) on
-// the knee, (R - 1)(G_u - T) below T - W (hard knee at T when W <= 0), and its derivatives.
-template <bool GRAD, class K>
-__device__ __forceinline__ Curve gate_curve(float Gu, const K& k) {
-  const float d = Gu - k.thr;
-  const float q = d - k.knee;  // G_u - T - W
-  const bool soft = k.knee > 0.f;
-  const bool below = soft ? (d + k.knee < 0.f) : (d < 0.f);  // Gu < T - W (soft) or Gu < T
-  const bool knee = soft && !below && q < 0.f;               // T - W <= Gu < T + W
-  Curve o;
-  const float e_knee = k.g1 * q * q * k.inv4w, e_lin = -k.g1 * d;
-  o.e = below ? e_lin : (knee ? e_knee : 0.f);
-  if (GRAD) {
-    const float g_knee = k.g1 * q * k.inv2w;
-    o.dG = below ? -k.g1 : (knee ? g_knee : 0.f);
-    o.dT = -o.dG;
-    const float w_knee = -k.g1 * (q * k.inv2w + q * q * k.inv4w * (2.f * k.inv2w));
-    o.dW = knee ? w_knee : 0.f;
-    const float r_knee = -q * q * k.inv4w;
-    o.dR = below ? d : (knee ? r_knee : 0.f);
-  } else {
-    o.dG = o.dT = o.dW = o.dR = 0.f;
-  }
-  return o;
+struct Ramp {
+  float f, fp, fq;  // f(d), f'(d) and 1 - f'(d) inside the knee (0 where f' = 1)
+};
+
+// The ramp at an envelope value gs > 0. The envelope goes through the hardware base-2 logarithm
+// (gs is normal: the envelope plus 1e-8). NaN stays NaN (v_med3 and v_max alone would drop it).
+template <bool GATE, bool GRAD>
+__device__ __forceinline__ Ramp ramp(float gs, const CurveCoef& k) {
+  const float L = __builtin_amdgcn_logf(gs);
+  const float d = GATE ? (k.thr_hi - L) + k.thr_lo : (L - k.thr_hi) - k.thr_lo;
+  const float m = __builtin_amdgcn_fmed3f(d + k.w, 0.f, k.w_2);
+  Ramp r;
+  r.f = fmaf(m * k.inv4w, m, fmaxf(d - k.w, 0.f));
+  r.f = d == d ? r.f : d;
+  r.fp = GRAD ? m * k.inv2w : 0.f;
+  r.fq = GRAD ? (k.w_2 - m) * k.inv2w : 0.f;
+  if (GRAD && k.w_2 == 0.f) r.fp = (GATE ? d > 0.f : d >= 0.f) ? 1.f : 0.f;  // uniform condition
+  return r;
 }
 
-// ln x and exp x through the hardware base-2 instructions (v_log_f32, v_exp_f32). x > 0 is
-// normal here (the envelope plus 1e-8); the exp argument is a gain in natural-log units, whose
-// relative error grows with its magnitude (about 2e-6 at |x| = 30).
-__device__ __forceinline__ float ln_f(float x) {
-  return __builtin_amdgcn_logf(x) * 0.69314718055994531f;
+// exp(c f): the gain, through the hardware base-2 exponential (relative error about 2e-6 where the
+// exponent is 30)
+__device__ __forceinline__ float gain(float f, const CurveCoef& k) {
+  return __builtin_amdgcn_exp2f(k.c * f);
 }
-__device__ __forceinline__ float exp_f(float x) {
-  return __builtin_amdgcn_exp2f(x * 1.4426950408889634f);
+
+// a / gs for gs >= 1e-8 with one correction step (within one unit in the last place)
+__device__ __forceinline__ float over_envelope(float a, float gs) {
+  const float b = fminf(gs, 1e37f), r = __builtin_amdgcn_rcpf(b), q = a * r;
+  return fmaf(fmaf(-b, q, a), r, q);
+}
+
+// ---- wave exchanges without LDS ----------------------------------------------------------------
+
+// The value of another lane of the same row of 16 (a DPP control); lanes without a source get `old`.
+template <int CTRL>
+__device__ __forceinline__ double row_move(double x, double old = 0.0) {
+  const int2 v = __builtin_bit_cast(int2, x), o = __builtin_bit_cast(int2, old);
+  return __builtin_bit_cast(
+      double, make_int2(__builtin_amdgcn_update_dpp(o.x, v.x, CTRL, 0xF, 0xF, false),
+                        __builtin_amdgcn_update_dpp(o.y, v.y, CTRL, 0xF, 0xF, false)));
+}
+// From the lane N below (forward) or above (REV) in the row.
+template <bool REV, int N>
+__device__ __forceinline__ double row_before(double x, double old = 0.0) {
+  return row_move<(REV ? 0x100 : 0x110) + N>(x, old);
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const int2 v = __builtin_bit_cast(int2, x);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(v.x, lane),
+                                              __builtin_amdgcn_readlane(v.y, lane)));
+}
+
+// Sum over the wave, in every lane: a butterfly inside the rows, then the four rows in order.
+__device__ __forceinline__ double wave_total(double v) {
+  v += row_move<0xB1>(v);   // lane ^ 1
+  v += row_move<0x4E>(v);   // lane ^ 2
+  v += row_move<0x141>(v);  // mirrored within 8
+  v += row_move<0x140>(v);  // mirrored within 16
+  return ((lane_value(v, 0) + lane_value(v, 16)) + lane_value(v, 32)) + lane_value(v, 48);
+}
+
+// Sums of N values over the block (kBlock threads) with one exchange through LDS; the results are
+// valid on every thread. `scratch` holds 4 N doubles.
+template <int N>
+__device__ __forceinline__ void block_totals(double (&v)[N], double* scratch) {
+  const int w = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_total(v[i]);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < N; ++i) scratch[4 * i + w] = v[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    v[i] = ((scratch[4 * i] + scratch[4 * i + 1]) + scratch[4 * i + 2]) + scratch[4 * i + 3];
+}
+
+// ---- per-node coefficients ---------------------------------------------------------------------
+// Computed once per pass by the kernel that resets the chaining state and kept next to the node's
+// ticket (second half of its 256-byte line), so a block reads them as scalars instead of forming
+// them in every thread.
+
+struct DynCoef {
+  double a, b;   // alpha, 1 - alpha
+  double logA;   // ln(a^kChunk), -inf for a = 0
+  double pw[8];  // pw[d] = (a^kPer)^(2^d)
+  CurveCoef cv;
+};
+struct DynCoefAR {
+  double aa, ar, ba, br;  // alpha_a, alpha_r, 1 - alpha_a, 1 - alpha_r
+  CurveCoef cv;
+};
+constexpr int kCoefOffset = 128;  // bytes into a ticket line
+static_assert(sizeof(DynCoef) <= 128 && sizeof(DynCoefAR) <= 128 &&
+                  kCompTicketStride * sizeof(unsigned) == 256,
+              "coefficients fit the second half of a ticket line");
+
+inline const char* dyn_coefs(const unsigned* tickets) {  // of row 0
+  return reinterpret_cast<const char*>(tickets) + kCoefOffset;
+}
+
+template <class C>
+__device__ __forceinline__ C load_coef(const char* __restrict__ coefs, int row) {
+  return *reinterpret_cast<const C*>(coefs + (int64_t)row * kCompTicketStride * sizeof(unsigned));
 }
 
 __device__ __forceinline__ int comp_chunks_of(int64_t n) { return (int)((n + kChunk - 1) / kChunk); }

@@ -5,8 +5,8 @@
 // With equal attack and release the energy envelope g[t] = a g[t-1] + (1-a) x[t],
 // x = (u_l + u_r)^2, is a linear one-pole recursion (the untruncated FIR of Eq. 9). It is computed
 // in double as a chunked scan: a block owns a chunk of 3072 samples (256 threads x 12 consecutive
-// samples); a thread folds its samples, a Kogge-Stone scan across the wave and a fold across the
-// 4 waves give every thread its state relative to the chunk start. The chunk then publishes its
+// samples); a thread folds its samples, a scan inside the rows of 16 lanes and folds over the rows
+// and the 4 waves give every thread its state relative to the chunk start. The chunk then publishes its
 // total (the state it would leave from a zero start) and folds the totals of all earlier chunks
 // of its node, c_k = sum_{j<k} total_j A^(k-1-j), A = a^3072, as one block-wide sum in a fixed
 // order. Folding totals (never partially folded prefixes) keeps the arithmetic independent of
@@ -15,6 +15,15 @@
 // is chosen so that a 17-node step of 2^18 samples is resident in one round of blocks (24 KB of
 // LDS and at most 80 VGPRs per thread give 6 blocks per CU), since a second round costs a whole
 // block lifetime.
+//
+// Instructions bound the adjoint as much as memory does (1.4k float and 0.5k double instructions
+// per wave left the vector units busy 64 of 98 us on 48 compressors of 2^18 samples), so: what
+// depends only on the node (powers of a, curve constants) is formed once per pass by
+// dyn_prepare_kernel and read as scalars; lanes exchange by DPP moves and readlane, not through
+// LDS; both gain curves are one branch-free ramp in base-2 units (dynamics.h); the curve's
+// derivatives are scaled once per chunk instead of per sample; and a thread's first read of an
+// earlier total is under way during the parameter sums. The same strips: adjoint 102 -> 81 us,
+// forward 52 -> 51 us (there memory, 3.9 of 4.8 TB/s, is the bound).
 //
 // A block's node comes from its block id; its chunk within the node comes from an atomic ticket
 // on that node's counter (one cache line per counter), taken when the block starts, so every
@@ -26,7 +35,7 @@
 // write-back and invalidation. Every wait is bounded; a wait that runs out records an error word
 // and poisons its result instead of spinning forever.
 //
-// The gain curve G_u = ln(g + 1e-8), quadratic knee, gain exp(G_y - G_u) is evaluated in float.
+// The gain curve (log of g + 1e-8, quadratic knee, gain) is evaluated in float.
 //
 // Adjoint (rho = sum_c ybar_c y_c, e = G_y - G_u):
 //   gbar = rho de/dG_u / (g + 1e-8);  lambda[t] = gbar[t] + a lambda[t+1]  (reverse scan);
@@ -34,6 +43,8 @@
 //   dL/da = sum lambda[t] (g[t-1] - x[t]);  dL/d(T, W, R) = sum rho de/d(T, W, R).
 // The adjoint takes chunks from the end of each node backwards and runs the same scan on
 // reversed thread order; the envelope entering each chunk is kept from the forward call.
+#include <algorithm>
+
 #include "device_common.h"
 #include "dynamics.h"
 #include "grafx_internal.h"
@@ -44,77 +55,62 @@ namespace {
 
 using namespace dyn;
 
+using Coef = DynCoef;
 
-struct Coef {
-  double a, b;        // alpha, 1 - alpha
-  float thr, knee;    // T, W
-  float c;            // 1/R - 1 (compressor)
-  float g1;           // 1 - R (noisegate)
-  float inv2w, inv4w; // 1/(2W), 1/(4W)
-  float invR2;        // 1/R^2
-  double pw[9];       // pw[d] = (a^kPer)^(2^d); pw[8] = a^kChunk
-  double logA;        // ln(a^kChunk), -inf for a = 0
+// Powers (a^kPer)^n of this thread's place: n its lane's position in the row of 16 and in the wave,
+// counted from the end of the chunk when REV.
+struct Powers {
+  double row, wave;
 };
-
-__device__ __forceinline__ Coef load_coef(const float* P, int slot) {
-  Coef k;
-  const float* p = P + (int64_t)slot * 4;
-  k.a = (double)p[0];
-  k.b = 1.0 - k.a;
-  k.thr = p[1];
-  k.knee = p[2];
-  const float R = p[3];
-  k.c = 1.0f / R - 1.0f;
-  k.g1 = 1.0f - R;
-  k.inv2w = k.knee > 0.f ? 1.0f / (2.f * k.knee) : 0.f;
-  k.inv4w = k.knee > 0.f ? 1.0f / (4.f * k.knee) : 0.f;
-  k.invR2 = 1.0f / (R * R);
-  k.logA = (double)kChunk * log(fabs(k.a));  // a^kChunk = |a|^kChunk: kChunk is even
-  double q = 1.0, b = k.a;  // a^kPer by binary powering
-  for (int e = kPer; e > 0; e >>= 1) {
-    if (e & 1) q *= b;
-    b *= b;
-  }
-  k.pw[0] = q;
-#pragma unroll
-  for (int d = 1; d < 9; ++d) k.pw[d] = k.pw[d - 1] * k.pw[d - 1];
-  return k;
+template <bool REV>
+__device__ __forceinline__ Powers lane_powers(const Coef& k) {
+  const int lane0 = threadIdx.x & 63, n = REV ? 63 - lane0 : lane0;
+  Powers p;
+  double r = (n & 1) ? k.pw[0] : 1.0;
+  if (n & 2) r *= k.pw[1];
+  if (n & 4) r *= k.pw[2];
+  if (n & 8) r *= k.pw[3];
+  p.row = r;
+  if (n & 16) r *= k.pw[4];
+  if (n & 32) r *= k.pw[5];
+  p.wave = r;
+  return p;
 }
 
-// (a^kPer)^n for 0 <= n < 512
-__device__ __forceinline__ double pow_a8(const Coef& k, int n) {
-  double r = 1.0;
-#pragma unroll
-  for (int d = 0; d < 9; ++d)
-    if ((n >> d) & 1) r *= k.pw[d];
-  return r;
-}
-
-template <bool GRAD, bool GATE>
-__device__ __forceinline__ Curve curve(float Gu, const Coef& k) {
-  if constexpr (GATE) return gate_curve<GRAD>(Gu, k);
-  else return comp_curve<GRAD>(Gu, k);
+// (a^kPer)^J' of this thread's place J' in the chunk, from its place in the wave
+template <bool REV>
+__device__ __forceinline__ double chunk_power(const Coef& k, double wave) {
+  const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), w = REV ? 3 - w0 : w0;
+  if (w & 1) wave *= k.pw[6];
+  if (w & 2) wave *= k.pw[7];
+  return wave;
 }
 
 // Chunk scan of s_out = a^kPer s_in + B over the block's 256 threads (reversed thread order when
-// REV), from a zero state entering the chunk. Returns the state entering this thread's samples;
-// `total` receives the state leaving the chunk (every thread). Thread J's state for a non-zero
-// entering state c is the returned value plus (a^kPer)^J' c, J' = J (forward) or 255 - J (REV).
+// REV), from a zero state entering the chunk: inside the rows of 16 lanes by DPP moves, then over
+// the four rows and the four waves. Returns the state entering this thread's samples; `total`
+// receives the state leaving the chunk (every thread). The thread's state for a non-zero entering
+// state c is the returned value plus chunk_power c.
 template <bool REV>
-__device__ __forceinline__ double chunk_scan(double B, const Coef& k, double* wtot, double& total) {
+__device__ __forceinline__ double chunk_scan(double B, const Coef& k, const Powers& p, double* wtot,
+                                             double& total) {
   const int lane0 = threadIdx.x & 63, w0 = threadIdx.x >> 6;
-  const int lane = REV ? 63 - lane0 : lane0;
+  const int row = REV ? 3 - (lane0 >> 4) : lane0 >> 4;
   const int w = REV ? 3 - w0 : w0;
   double S = B;
+  S = fma(k.pw[0], row_before<REV, 1>(S), S);
+  S = fma(k.pw[1], row_before<REV, 2>(S), S);
+  S = fma(k.pw[2], row_before<REV, 4>(S), S);
+  S = fma(k.pw[3], row_before<REV, 8>(S), S);
+  double C = 0.0, Ci = 0.0;  // states leaving the rows before this lane's, and row i
 #pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    const double o = REV ? __shfl_down(S, 1 << d, 64) : __shfl_up(S, 1 << d, 64);
-    if (lane >= (1 << d)) S = fma(k.pw[d], o, S);
+  for (int i = 0; i < 4; ++i) {
+    if (row == i) C = Ci;
+    Ci = fma(k.pw[4], Ci, lane_value(S, REV ? 48 - 16 * i : 16 * i + 15));
   }
-  double ex = REV ? __shfl_down(S, 1, 64) : __shfl_up(S, 1, 64);
-  if (lane == 0) ex = 0.0;
+  const double ex = fma(p.row, C, row_before<REV, 1>(S));
   __syncthreads();
-  if (lane == 63) wtot[w] = S;
+  if (lane0 == 0) wtot[w] = Ci;
   __syncthreads();
   double P = 0.0, end = 0.0;
 #pragma unroll
@@ -123,12 +119,7 @@ __device__ __forceinline__ double chunk_scan(double B, const Coef& k, double* wt
     end = fma(k.pw[6], end, wtot[v]);
   }
   total = end;
-  return fma(pow_a8(k, lane), P, ex);
-}
-
-
-__device__ __forceinline__ int scan_index(bool rev) {
-  return rev ? kBlock - 1 - (int)threadIdx.x : (int)threadIdx.x;
+  return fma(p.wave, P, ex);
 }
 
 // Entering state of chunk k: fixed-order block-wide sum over the published totals of the
@@ -138,33 +129,48 @@ __device__ __forceinline__ double carry_weight(int dist, const Coef& c) {
   return dist == 0 ? 1.0 : exp((double)dist * c.logA);
 }
 
+// A thread's first total is read as soon as the chunk's own is published, and its weight (and, in
+// the adjoint, the parameter sums) formed while that read is under way.
 template <bool REV>
-__device__ __forceinline__ double chunk_carry(uint64_t* tot, int k, int chunks, const Coef& c,
-                                              unsigned* err, int polls, double* red) {
-  double s = 0.0;
-  if (!REV) {
-    for (int j = threadIdx.x; j < k; j += kBlock)
-      s += await_total(tot + j, err, polls) * carry_weight(k - 1 - j, c);
-  } else {
-    for (int j = k + 1 + threadIdx.x; j < chunks; j += kBlock)
-      s += await_total(tot + j, err, polls) * carry_weight(j - k - 1, c);
+struct Carry {
+  uint64_t* tot;
+  int n;  // totals to fold: distances 0 .. n - 1 at tot[-dist] (forward) or tot[dist]
+  uint64_t first;
+
+  __device__ __forceinline__ uint64_t* at(int dist) const { return REV ? tot + dist : tot - dist; }
+  __device__ __forceinline__ Carry(uint64_t* tots, int k, int chunks)
+      : tot(REV ? tots + k + 1 : tots + k - 1), n(REV ? chunks - 1 - k : k), first(kNotReady) {
+    const int d = threadIdx.x;
+    if (d < n) first = __hip_atomic_load(at(d), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  return block_sum<double>(s, red);
-}
+  // This thread's part of the sum.
+  __device__ __forceinline__ double part(const Coef& c, unsigned* err, int polls) const {
+    double s = 0.0;
+    int d = threadIdx.x;
+    if (d < n) {
+      const double w = carry_weight(d, c);
+      s = (first != kNotReady && polls > 0 ? __longlong_as_double((long long)first)
+                                           : await_total(at(d), err, polls)) * w;
+    }
+    for (d += kBlock; d < n; d += kBlock) s += await_total(at(d), err, polls) * carry_weight(d, c);
+    return s;
+  }
+};
 
 // ---- forward ----------------------------------------------------------------------------------
 
 template <bool RAGGED, bool GATE>
-__global__ __launch_bounds__(kBlock) void comp_fwd_kernel(GraphView g, float* U, const float* P,
-                                                          int node_begin, int n_nodes, int chunks,
-                                                          int ws_off, uint64_t* agg, double* carry,
+__global__ __launch_bounds__(kBlock) void comp_fwd_kernel(GraphView g, float* U, int node_begin,
+                                                          int n_nodes, int chunks, int ws_off,
+                                                          const char* __restrict__ coefs,
+                                                          uint64_t* agg, double* carry,
                                                           unsigned* ticket, unsigned* err) {
   __shared__ float sl[kLdsChunk], sr[kLdsChunk];
   __shared__ double wtot[4], red[4];
   __shared__ int sh_ticket;
   const int node = node_begin + block_node(g, n_nodes, chunks);
-  const int slot = g.param_row[node];  // row in P
-  const int ws = slot + ws_off;         // row of the dynamics workspace (compressors, then gates)
+  const int ws = g.param_row[node] + ws_off;  // row of the dynamics workspace (compressors, then gates)
+  const Coef k = load_coef<Coef>(coefs, ws);
   const int chunk = take_ticket(ticket + (int64_t)ws * kCompTicketStride, &sh_ticket);
   if (chunk >= chunks) {  // tickets not reset before the launch: do nothing
     if (threadIdx.x == 0) atomicOr(err, 2u);
@@ -172,7 +178,6 @@ __global__ __launch_bounds__(kBlock) void comp_fwd_kernel(GraphView g, float* U,
   }
   const int64_t Tn = RAGGED ? (int64_t)g.len[node] : g.T;
   if (RAGGED && chunk >= comp_chunks_of(Tn)) return;  // past the node's length
-  const Coef k = load_coef(P, slot);
   const int t0 = chunk * kChunk;
   stage<false, RAGGED>(g, node, t0, sl, sr);
   __syncthreads();
@@ -180,18 +185,21 @@ __global__ __launch_bounds__(kBlock) void comp_fwd_kernel(GraphView g, float* U,
   double B = 0.0;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) B = fma(k.a, B, k.b * energy(sl, sr, i0 + i));
+  const Powers p = lane_powers<false>(k);
   double total;
-  const double E0 = chunk_scan<false>(B, k, wtot, total);
+  const double E0 = chunk_scan<false>(B, k, p, wtot, total);
   uint64_t* tots = agg + (int64_t)ws * chunks;
   if (threadIdx.x == 0) publish(tots + chunk, total);
-  const double cin = chunk_carry<false>(tots, chunk, chunks, k, err, g.wait_polls, red);
-  if (threadIdx.x == 0) carry[(int64_t)ws * chunks + chunk] = cin;
-  double s = fma(pow_a8(k, scan_index(false)), cin, E0);
+  const Carry<false> from(tots, chunk, chunks);
+  const double pj = chunk_power<false>(k, p.wave);
+  double cin[1] = {from.part(k, err, g.wait_polls)};
+  block_totals(cin, red);
+  if (threadIdx.x == 0) carry[(int64_t)ws * chunks + chunk] = cin[0];
+  double s = fma(pj, cin[0], E0);
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     s = fma(k.a, s, k.b * energy(sl, sr, i0 + i));
-    const Curve cv = curve<false, GATE>(ln_f((float)(s + kEps)), k);
-    const float gam = exp_f(cv.e);
+    const float gam = gain(ramp<GATE, false>((float)(s + kEps), k.cv).f, k.cv);
     sl[i0 + i] = gam * sl[i0 + i];
     sr[i0 + i] = gam * sr[i0 + i];
   }
@@ -202,17 +210,18 @@ __global__ __launch_bounds__(kBlock) void comp_fwd_kernel(GraphView g, float* U,
 // ---- adjoint ----------------------------------------------------------------------------------
 
 template <bool RAGGED, bool GATE>
-__global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU, const float* P,
-                                                          int node_begin, int n_nodes, int chunks, int ws_off,
+__global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU, int node_begin,
+                                                          int n_nodes, int chunks, int ws_off,
+                                                          const char* __restrict__ coefs,
                                                           const double* carry, uint64_t* ragg,
                                                           double* part, unsigned* ticket,
                                                           unsigned* err) {
   __shared__ float ul[kLdsChunk], ur[kLdsChunk], yl[kLdsChunk], yr[kLdsChunk];
-  __shared__ double wtot[4], red[4];
+  __shared__ double wtot[4], red[16];
   __shared__ int sh_ticket;
   const int node = node_begin + block_node(g, n_nodes, chunks);
-  const int slot = g.param_row[node];  // row in P
-  const int ws = slot + ws_off;         // row of the dynamics workspace (compressors, then gates)
+  const int ws = g.param_row[node] + ws_off;  // row of the dynamics workspace (compressors, then gates)
+  const Coef k = load_coef<Coef>(coefs, ws);
   const int tk = take_ticket(ticket + (int64_t)ws * kCompTicketStride, &sh_ticket);
   if (tk >= chunks) {  // tickets not reset before the launch: do nothing
     if (threadIdx.x == 0) atomicOr(err, 2u);
@@ -225,7 +234,6 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
     return;
   }
   const int chunk = chunks_n - 1 - tk;
-  const Coef k = load_coef(P, slot);
   const int t0 = chunk * kChunk;
   stage<false, RAGGED>(g, node, t0, ul, ur);
   stage<true, RAGGED>(g, node, t0, yl, yr);
@@ -235,14 +243,18 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
   double B = 0.0;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) B = fma(k.a, B, k.b * energy(ul, ur, i0 + i));
-  double total;
-  const double E0 = chunk_scan<false>(B, k, wtot, total);
-  const double E = fma(pow_a8(k, scan_index(false)), carry[(int64_t)ws * chunks + chunk], E0);
+  double total, E;
+  {
+    const Powers p = lane_powers<false>(k);
+    const double E0 = chunk_scan<false>(B, k, p, wtot, total);
+    E = fma(chunk_power<false>(k, p.wave), carry[(int64_t)ws * chunks + chunk], E0);
+  }
   // First pass (forward over the thread's samples): envelope, gain and the local adjoint terms.
   // What the reverse pass needs is written back over the thread's own LDS slots: ul <- g[t-1] -
-  // x[t], ur <- u_l + u_r, yl/yr <- gain * ybar.
+  // x[t], ur <- u_l + u_r, yl/yr <- gain * ybar. With de/dG_u = dg f': gbar = rho dg f' / (g + eps).
+  const float dg = GATE ? -k.cv.c : k.cv.c;
   float gbar[kPer];
-  double accT = 0.0, accW = 0.0, accR = 0.0;
+  double sum_fp = 0.0, sum_w = 0.0, sum_f = 0.0;  // of rho f', rho f' (1 - f') and rho f
   {
     double s = E;
 #pragma unroll
@@ -254,30 +266,38 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
       const double sprev = s;
       s = fma(k.a, s, k.b * x);
       const float gs = (float)(s + kEps);
-      const Curve cv = curve<true, GATE>(ln_f(gs), k);
-      const float gam = exp_f(cv.e);
-      const float y_l = yl[idx], y_r = yr[idx];
-      const float rho = gam * (y_l * u_l + y_r * u_r);
-      gbar[i] = rho * cv.dG / gs;
-      accT += (double)(rho * cv.dT);
-      accW += (double)(rho * cv.dW);
-      accR += (double)(rho * cv.dR);
+      const Ramp r = ramp<GATE, true>(gs, k.cv);
+      const float gam = gain(r.f, k.cv);
+      const float y_l = gam * yl[idx], y_r = gam * yr[idx];
+      const float rho = fmaf(y_l, u_l, y_r * u_r);
+      const float rfp = rho * r.fp;
+      gbar[i] = over_envelope(dg * rfp, gs);
+      sum_fp += (double)rfp;
+      sum_w += (double)(rfp * r.fq);
+      sum_f += (double)(rho * r.f);
       ul[idx] = (float)(sprev - x);
       ur[idx] = m;
-      yl[idx] = gam * y_l;
-      yr[idx] = gam * y_r;
+      yl[idx] = y_l;
+      yr[idx] = y_r;
     }
   }
   // reverse recursion lambda[t] = gbar[t] + a lambda[t+1]
   double R = 0.0;
 #pragma unroll
   for (int i = kPer - 1; i >= 0; --i) R = fma(k.a, R, (double)gbar[i]);
+  const Powers p = lane_powers<true>(k);
   double rtotal;
-  const double L0 = chunk_scan<true>(R, k, wtot, rtotal);
+  const double L0 = chunk_scan<true>(R, k, p, wtot, rtotal);
   uint64_t* rtots = ragg + (int64_t)ws * chunks;
   if (threadIdx.x == 0) publish(rtots + chunk, rtotal);
-  const double rin = chunk_carry<true>(rtots, chunk, chunks_n, k, err, g.wait_polls, red);  // own chunks
-  double lam = fma(pow_a8(k, scan_index(true)), rin, L0);
+  const Carry<true> from(rtots, chunk, chunks_n);  // own chunks
+  const double pj = chunk_power<true>(k, p.wave);
+  double sums[4] = {sum_fp, sum_w, sum_f, 0.0};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) sums[i] = wave_total(sums[i]);
+  double rin[1] = {from.part(k, err, g.wait_polls)};
+  block_totals(rin, red);
+  double lam = fma(pj, rin[0], L0);
   double accA = 0.0;
 #pragma unroll
   for (int i = kPer - 1; i >= 0; --i) {
@@ -288,83 +308,127 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
     yl[idx] += mid;
     yr[idx] += mid;
   }
-  const double sA = block_sum<double>(accA, red);
-  const double sT = block_sum<double>(accT, red);
-  const double sW = block_sum<double>(accW, red);
-  const double sR = block_sum<double>(accR, red);
-  if (threadIdx.x == 0) {
-    double* p = part + ((int64_t)ws * chunks + chunk) * 4;
-    p[0] = sA;
-    p[1] = sT;
-    p[2] = sW;
-    p[3] = sR;
-  }
+  sums[3] = wave_total(accA);
+  __syncthreads();
   store_chunk(dU + (int64_t)node * 2 * g.T, g.T, Tn, t0, yl, yr);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[4 * i + (threadIdx.x >> 6)] = sums[i];
+  __syncthreads();
+  if (threadIdx.x < 4) {  // dL/da, dL/dT, dL/dW, dL/dR
+    const double* q = red + 4 * ((threadIdx.x + 3) & 3);
+    const double v = ((q[0] + q[1]) + q[2]) + q[3];
+    const double f = threadIdx.x == 0   ? 1.0
+                     : threadIdx.x == 1 ? -(double)dg
+                     : threadIdx.x == 2 ? (double)k.cv.c
+                                        : -(double)k.cv.kR;
+    part[((int64_t)ws * chunks + chunk) * 4 + threadIdx.x] = f * v;
+  }
 }
 
-// Reset the published totals to "not ready" and the per-node tickets to 0 before a pass.
-__global__ __launch_bounds__(kBlock) void comp_reset_kernel(uint64_t* tot, int64_t n,
-                                                            unsigned* tickets, int n_tickets) {
+// Before a pass: the published totals set to "not ready", the tickets (and, given one, the error
+// word) to 0, and the nodes' coefficients formed. AR: rows of attack/release compressors.
+template <bool AR>
+__global__ __launch_bounds__(kBlock) void dyn_prepare_kernel(uint64_t* tot, int64_t n,
+                                                             unsigned* tickets, unsigned* err,
+                                                             const float* P, int n_comp,
+                                                             const float* Pg, int n_gate) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) tot[i] = kNotReady;
-  if (i < n_tickets) tickets[i] = 0u;
+  if (i == 0 && err) *err = 0u;
+  if (i >= n_comp + n_gate) return;
+  unsigned* line = tickets + i * kCompTicketStride;
+  *line = 0u;
+  void* coefs = reinterpret_cast<char*>(line) + kCoefOffset;
+  if constexpr (AR) {
+    const float* p = P + i * kArParams;
+    DynCoefAR k;
+    k.aa = (double)p[0];
+    k.ar = (double)p[1];
+    k.ba = 1.0 - k.aa;
+    k.br = 1.0 - k.ar;
+    k.cv = make_curve(p[2], p[3], p[4], false);
+    *reinterpret_cast<DynCoefAR*>(coefs) = k;
+  } else {
+    const bool gate = i >= n_comp;
+    const float* p = gate ? Pg + (i - n_comp) * 4 : P + i * 4;
+    DynCoef k;
+    k.a = (double)p[0];
+    k.b = 1.0 - k.a;
+    k.logA = (double)kChunk * log(fabs(k.a));  // a^kChunk = |a|^kChunk: kChunk is even
+    double q = 1.0, b = k.a;  // a^kPer by binary powering
+    for (int e = kPer; e > 0; e >>= 1) {
+      if (e & 1) q *= b;
+      b *= b;
+    }
+    k.pw[0] = q;
+#pragma unroll
+    for (int d = 1; d < 8; ++d) k.pw[d] = k.pw[d - 1] * k.pw[d - 1];
+    k.cv = make_curve(p[1], p[2], p[3], gate);
+    *reinterpret_cast<DynCoef*>(coefs) = k;
+  }
 }
 
 }  // namespace
 
 int comp_chunks(int64_t T) { return (int)((T + kChunk - 1) / kChunk); }
 
-hipError_t launch_comp_reset(uint64_t* tot, int64_t n, unsigned* tickets, int n_tickets,
-                             hipStream_t s) {
-  const int64_t m = n > n_tickets ? n : n_tickets;
+hipError_t launch_dyn_prepare(bool ar, uint64_t* tot, int64_t n, unsigned* tickets, unsigned* err,
+                              const float* P, int n_comp, const float* Pg, int n_gate,
+                              hipStream_t s) {
+  const int64_t m = std::max(std::max(n, (int64_t)n_comp + n_gate), (int64_t)(err ? 1 : 0));
   if (m <= 0) return hipSuccess;
-  comp_reset_kernel<<<(unsigned)((m + kBlock - 1) / kBlock), kBlock, 0, s>>>(tot, n, tickets,
-                                                                              n_tickets);
+  const unsigned blocks = (unsigned)((m + kBlock - 1) / kBlock);
+  if (ar)
+    dyn_prepare_kernel<true><<<blocks, kBlock, 0, s>>>(tot, n, tickets, err, P, n_comp, Pg, n_gate);
+  else
+    dyn_prepare_kernel<false><<<blocks, kBlock, 0, s>>>(tot, n, tickets, err, P, n_comp, Pg,
+                                                        n_gate);
   return hipGetLastError();
 }
 
 template <bool RAGGED, bool GATE>
-static void launch_fwd_t(const GraphView& g, float* U, const float* P, int node_begin,
-                         int n_nodes, int chunks, int ws_off, uint64_t* agg, double* carry,
-                         unsigned* ticket, unsigned* err, hipStream_t s) {
+static void launch_fwd_t(const GraphView& g, float* U, int node_begin, int n_nodes, int chunks,
+                         int ws_off, uint64_t* agg, double* carry, unsigned* ticket, unsigned* err,
+                         hipStream_t s) {
   comp_fwd_kernel<RAGGED, GATE><<<(unsigned)(chunks * n_nodes), kBlock, 0, s>>>(
-      g, U, P, node_begin, n_nodes, chunks, ws_off, agg, carry, ticket, err);
+      g, U, node_begin, n_nodes, chunks, ws_off, dyn_coefs(ticket), agg, carry, ticket, err);
 }
 
 template <bool RAGGED, bool GATE>
-static void launch_bwd_t(const GraphView& g, float* dU, const float* P, int node_begin,
-                         int n_nodes, int chunks, int ws_off, const double* carry, uint64_t* ragg,
-                         double* part, unsigned* ticket, unsigned* err, hipStream_t s) {
+static void launch_bwd_t(const GraphView& g, float* dU, int node_begin, int n_nodes, int chunks,
+                         int ws_off, const double* carry, uint64_t* ragg, double* part,
+                         unsigned* ticket, unsigned* err, hipStream_t s) {
   comp_bwd_kernel<RAGGED, GATE><<<(unsigned)(chunks * n_nodes), kBlock, 0, s>>>(
-      g, dU, P, node_begin, n_nodes, chunks, ws_off, carry, ragg, part, ticket, err);
+      g, dU, node_begin, n_nodes, chunks, ws_off, dyn_coefs(ticket), carry, ragg, part, ticket,
+      err);
 }
 
 // Per-node lengths and the noisegate curve get their own instantiations, so the uniform
 // compressor carries no code for either.
-hipError_t launch_comp_fwd(const GraphView& g, float* U, const float* P, int node_begin,
-                           int n_nodes, int ws_off, bool gate, uint64_t* agg, double* carry,
-                           unsigned* ticket, unsigned* err, hipStream_t s) {
+hipError_t launch_comp_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int ws_off,
+                           bool gate, uint64_t* agg, double* carry, unsigned* ticket,
+                           unsigned* err, hipStream_t s) {
   const int chunks = comp_chunks(g.T);
   if (g.len)
     (gate ? launch_fwd_t<true, true> : launch_fwd_t<true, false>)(
-        g, U, P, node_begin, n_nodes, chunks, ws_off, agg, carry, ticket, err, s);
+        g, U, node_begin, n_nodes, chunks, ws_off, agg, carry, ticket, err, s);
   else
     (gate ? launch_fwd_t<false, true> : launch_fwd_t<false, false>)(
-        g, U, P, node_begin, n_nodes, chunks, ws_off, agg, carry, ticket, err, s);
+        g, U, node_begin, n_nodes, chunks, ws_off, agg, carry, ticket, err, s);
   return hipGetLastError();
 }
 
-hipError_t launch_comp_bwd(const GraphView& g, float* dU, const float* P, int node_begin,
-                           int n_nodes, int ws_off, bool gate, const double* carry,
-                           uint64_t* ragg, double* part, unsigned* ticket, unsigned* err,
-                           hipStream_t s) {
+hipError_t launch_comp_bwd(const GraphView& g, float* dU, int node_begin, int n_nodes, int ws_off,
+                           bool gate, const double* carry, uint64_t* ragg, double* part,
+                           unsigned* ticket, unsigned* err, hipStream_t s) {
   const int chunks = comp_chunks(g.T);
   if (g.len)
     (gate ? launch_bwd_t<true, true> : launch_bwd_t<true, false>)(
-        g, dU, P, node_begin, n_nodes, chunks, ws_off, carry, ragg, part, ticket, err, s);
+        g, dU, node_begin, n_nodes, chunks, ws_off, carry, ragg, part, ticket, err, s);
   else
     (gate ? launch_bwd_t<false, true> : launch_bwd_t<false, false>)(
-        g, dU, P, node_begin, n_nodes, chunks, ws_off, carry, ragg, part, ticket, err, s);
+        g, dU, node_begin, n_nodes, chunks, ws_off, carry, ragg, part, ticket, err, s);
   return hipGetLastError();
 }
 

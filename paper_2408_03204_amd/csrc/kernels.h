@@ -64,20 +64,23 @@ int comp_chunks(int64_t T);
 // pass); carry: double [n_comp][chunks] envelope entering each chunk (forward, kept for the
 // adjoint); part: double [n_comp][chunks][4]; ticket: one counter per compressor node (reset to 0),
 // kCompTicketStride words apart so that no two counters share a cache line (atomics on one line
-// serialise); err: error word (bit 0: a wait ran out, bit 1: tickets were not reset)
+// serialise), with the node's coefficients in the second half of its line; err: error word (bit 0:
+// a wait ran out, bit 1: tickets were not reset)
 constexpr int kCompTicketStride = 64;
-hipError_t launch_comp_reset(uint64_t* tot, int64_t n, unsigned* tickets, int n_tickets,
-                             hipStream_t s);
+// Before a pass: n totals reset, the rows' tickets and coefficients written (rows: n_comp nodes of
+// P, then n_gate noisegates of Pg; ar: attack/release rows), the error word cleared if given.
+hipError_t launch_dyn_prepare(bool ar, uint64_t* tot, int64_t n, unsigned* tickets, unsigned* err,
+                              const float* P, int n_comp, const float* Pg, int n_gate,
+                              hipStream_t s);
 // Compressors and noisegates share one workspace family ("dynamics"): rows [0, n_comp) belong to
 // the compressors, [n_comp, n_comp + n_gate) to the noisegates; ws_off is the family row of the
 // launch's type (0 or n_comp) and `gate` selects the noisegate curve.
-hipError_t launch_comp_fwd(const GraphView& g, float* U, const float* P, int node_begin,
-                           int n_nodes, int ws_off, bool gate, uint64_t* agg, double* carry,
+hipError_t launch_comp_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int ws_off,
+                           bool gate, uint64_t* agg, double* carry, unsigned* ticket,
+                           unsigned* err, hipStream_t s);
+hipError_t launch_comp_bwd(const GraphView& g, float* dU, int node_begin, int n_nodes, int ws_off,
+                           bool gate, const double* carry, uint64_t* ragg, double* part,
                            unsigned* ticket, unsigned* err, hipStream_t s);
-hipError_t launch_comp_bwd(const GraphView& g, float* dU, const float* P, int node_begin,
-                           int n_nodes, int ws_off, bool gate, const double* carry,
-                           uint64_t* ragg, double* part, unsigned* ticket, unsigned* err,
-                           hipStream_t s);
 
 // ---- compressor with attack/release ballistics (k_comp_ar.hip) -----------------------------
 constexpr int kArParams = 5;   // alpha_a, alpha_r, T, W, R
@@ -86,12 +89,12 @@ constexpr int kArPasses = 16;  // branch-pattern passes before a chunk falls bac
 // "not ready"; carry: double [n_ar][chunks] and pats: uint16 [n_ar][chunks][kBlock] are written
 // for the adjoint; ragg: uint64 [n_ar][chunks][2] (reset); part: double [n_ar][chunks][5];
 // ticket: kCompTicketStride words per node (reset to 0); err as for the compressor.
-hipError_t launch_comp_ar_fwd(const GraphView& g, float* U, const float* P, int node_begin,
-                              int n_nodes, int max_pass, uint64_t* pslot, uint64_t* fin,
-                              double* carry, uint16_t* pats, unsigned* ticket, unsigned* err,
+hipError_t launch_comp_ar_fwd(const GraphView& g, float* U, int node_begin, int n_nodes,
+                              int max_pass, uint64_t* pslot, uint64_t* fin, double* carry,
+                              uint16_t* pats, unsigned* ticket, unsigned* err,
                               hipStream_t s);
-hipError_t launch_comp_ar_bwd(const GraphView& g, float* dU, const float* P, int node_begin,
-                              int n_nodes, const double* carry, const uint16_t* pats,
+hipError_t launch_comp_ar_bwd(const GraphView& g, float* dU, int node_begin, int n_nodes,
+                              const double* carry, const uint16_t* pats,
                               uint64_t* ragg, double* part, unsigned* ticket, unsigned* err,
                               hipStream_t s);
 

@@ -92,3 +92,31 @@ def test_compressor_curve_regions(T, t, knee_db):
     say("   regions", (below, inside, above), "grad errs", {k: f"{e:.2e}" for k, e in errs.items()})
     for k, e in errs.items():
         assert e <= GRAD_TOL, (k, e)
+
+
+@pytest.mark.parametrize("t", [synth.COMP, synth.COMP_AR])
+@pytest.mark.parametrize("knee,thr", [(1e-33, -4.0), (1.0, 1e30), (0.0, float("inf"))])
+def test_compressor_curve_extremes(t, knee, thr):
+    """A knee so narrow that 1/(4 W) has no float value renders, and differentiates, like the hard
+    knee; a threshold above every level, infinite included, leaves the signal as it is. Both to the
+    bit: the first by the same arithmetic, the second because the gain's exponent is exactly 0."""
+    say(f"[{synth.TYPE_NAMES[t]} curve extremes] W={knee} T={thr}")
+    col = 1 if t == synth.COMP else 2
+    out = []
+    for w_knee in (knee, 0.0):
+        w = comp_workload(t, 3072 + 555, 52, 0.0)
+        w.params[t][:, col], w.params[t][:, col + 1] = thr, w_knee
+        sched = Schedule(w.graph.node_type, w.graph.edges)
+        S, P = device_inputs(w)
+        S.requires_grad_(True)
+        P[t].requires_grad_(True)
+        Y = render(sched, S, P)
+        Y.square().sum().backward()
+        torch.cuda.synchronize()
+        out.append((Y.detach(), S.grad, P[t].grad))
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+    if thr > 0:
+        y, gs, gp = out[0]
+        assert torch.equal(y[0], S.detach()[0] + S.detach()[1])
+        assert torch.equal(gs[0], 2 * y[0]) and not gp.any()
