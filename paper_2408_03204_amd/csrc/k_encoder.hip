@@ -14,8 +14,8 @@
 // can run on v_mfma_f32_16x16x16_bf16 with float32 accumulation. The first layer (256 input
 // channels, 0.8 of the multiplications) has a tiled kernel; the others are small (a few frames a
 // sample), so one block per sample runs all of them, the pooling and the head from LDS, and the
-// backward does the same in reverse. The weight gradients of all layers share one launch split
-// over the batch, then one fixed-order sum (runs are bit-reproducible).
+// backward does the same in reverse. The weight gradients of all layers and of the head are one
+// launch (sums in a fixed order: runs are bit-reproducible).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -36,18 +36,8 @@ struct EncLayout {
   size_t w[kLayers + 2], b[kLayers + 2];  // weight and bias offsets (layer 1..6, head = 7)
   size_t n_w;
   size_t y[kLayers + 1], h, act;          // activations: y_l [B][64][F_l], pooled h [B][64]
-  size_t dy[kLayers + 1], dz, lossp, part, grad;  // backward scratch
+  size_t dy[kLayers + 1], dz, lossp, grad;  // backward scratch
 };
-
-// Weight-gradient work of one layer: the (sample, 64-frame tile) units are dealt to `splits`
-// contiguous ranges; each (split, 64 input channels) is a block, whose partial sums are
-// [split][64 x Cin x 5 weights, 64 biases].
-constexpr int kGradTile = 64, kMaxSplits = 64;
-int grad_tiles(int Fout) { return (Fout + kGradTile - 1) / kGradTile; }
-int grad_splits(int B, int Fout) {
-  const int64_t units = (int64_t)B * grad_tiles(Fout);
-  return (int)(units < kMaxSplits ? units : kMaxSplits);
-}
 
 int cin_of(int l) { return l == 1 ? kCin : kCh; }
 
@@ -82,9 +72,7 @@ EncLayout enc_layout(int B, int F) {
   d += (size_t)B * kOut;
   L.lossp = d;
   d += (size_t)B;
-  L.part = d;
-  for (int l = 1; l <= kLayers; ++l)
-    d += (size_t)grad_splits(B, L.F[l]) * kCh * (cin_of(l) * kKs + 1);
+  d += (size_t)B * kCh;  // not used; part of the size callers allocate
   L.grad = d;
   return L;
 }
@@ -93,6 +81,8 @@ EncLayout enc_layout(int B, int F) {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // weights: any float address
 
 __device__ __forceinline__ short to_bf16(float f) {  // round to nearest even
@@ -452,7 +442,8 @@ __device__ __forceinline__ void store_w(float* Ws, const f32x4 (&w)[kWStage]) {
 
 // Loss terms, the head's backward and the input gradients of layers 6 .. first of one sample:
 // dz = 2 (s - y) s (1 - s) / (B 11), dh = Wh^T dz, dy6[c][t] = dh[c] / F6. What is written to
-// dy[l] is the masked gradient g = dy where y > 0, which is all that the layers below read. 32 us
+// dy[l] is the masked gradient g = dy where y > 0, which is all that the layers below read, with the
+// channel as the fastest index ([B][F_l][64]), as the weight gradients read it. 32 us
 // for 256 samples x 125 frames (530 us as one launch a layer with one thread per output).
 __global__ __launch_bounds__(kBlock) void tail_bwd_kernel(int B, TailLayers L, const float* out,
                                                           const float* labels, float* dz,
@@ -481,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void tail_bwd_kernel(int B, TailLayers L, c
     const int64_t row = (smp * kCh + c) * F6;
     for (int t = 0; t < F6; ++t) {
       const float v = L.y[kLayers][row + t] > 0.f ? dh / (float)F6 : 0.f;
-      L.dy[kLayers][row + t] = v;
+      L.dy[kLayers][(smp * F6 + t) * kCh + c] = v;
       if (L.first <= kLayers) g[c * R + 1 + t] = v;
     }
     if (L.first <= kLayers) g[c * R] = g[c * R + 1 + F6] = 0.f;
@@ -500,7 +491,7 @@ __global__ __launch_bounds__(kBlock) void tail_bwd_kernel(int B, TailLayers L, c
     float* dy = L.dy[l - 1] + smp * kCh * Fin;
     bwd_data(Ws, g, R, 0, L.F[l], Fin, [&](int ci, int f, float v) {
       v = y[ci * Fin + f] > 0.f ? v : 0.f;
-      dy[ci * Fin + f] = v;
+      dy[f * kCh + ci] = v;
       if (l > L.first) gn[ci * R + 1 + f] = v;
     });
     if (l > L.first)
@@ -526,191 +517,198 @@ __global__ __launch_bounds__(kBlock) void conv_bwd_data_kernel(int Fin, int Fout
   f32x4 w[kWStage];
   load_w(W, w);
   const float* gr = g + smp * kCh * Fout;
-  for (int c = wave; c < kCh; c += kBlock / 64)
-    for (int k = lane; k < n + 2; k += 64) {
-      const int t = s0 + k - 1;
-      gs[c * R + k] = t >= 0 && t < Fout ? gr[(int64_t)c * Fout + t] : 0.f;
-    }
+  for (int k = wave; k < n + 2; k += kBlock / 64) {
+    const int t = s0 + k - 1;
+    gs[lane * R + k] = t >= 0 && t < Fout ? gr[(int64_t)t * kCh + lane] : 0.f;
+  }
   store_w(Ws, w);
   __syncthreads();
   const float* yr = y + smp * kCh * Fin;
   float* dr = dy + smp * kCh * Fin;
   bwd_data(Ws, gs, R, s0, n, Fin, [&](int ci, int f, float v) {
-    const int64_t at = (int64_t)ci * Fin + f;
-    dr[at] = yr[at] > 0.f ? v : 0.f;
+    dr[(int64_t)f * kCh + ci] = yr[(int64_t)ci * Fin + f] > 0.f ? v : 0.f;
   });
 }
 
 // ---- weight gradients --------------------------------------------------------------------------
 
 struct GradLayer {
-  const float* x;   // layer input [B][Cin][Fin]
-  const float* g;   // masked output gradient [B][64][Fout]
-  float* part;      // [splits][64 x Cin x 5 + 64]
-  float* dw;        // weight gradient, followed by the bias gradient
-  int Cin, Fin, Fout, tiles, splits, units, blocks;
+  const float* x;  // layer input [B][Cin][Fin]
+  const float* g;  // masked output gradient [B][Fout][64]
+  float* dw;       // weight gradient, followed by the bias gradient
+  int Cin, Fin, Fout, blocks;
 };
 struct GradLayers {
   GradLayer l[kLayers];
 };
 
-// dW[co][ci][k] = sum_{b,t} g[b][co][t] x[b][ci][2t + k - 2] over the units of one split and 64
-// input channels: M = co, N = ci for each tap, K = frames. Wave w holds 16 input channels x 5 taps
-// x 64 output channels in 20 accumulators, so 9 LDS reads feed 20 matrix instructions; a unit's
-// chain (at most 64 terms) is added to the running sums before the next, which keeps the error of
-// a long float32 chain out. The next unit's loads are in flight while one is computed. 71 us and
-// 9 us for the sums of 64 splits, all layers, 256 samples x 125 frames (5.1 GFLOP; one block per
-// pair of channels, reading both rows for five sums each, took 1144 us, the head's serial sums
-// over the batch 132 us).
-__global__ __launch_bounds__(kBlock, 1) void weight_grad_kernel(GradLayers P) {
-  constexpr int GR = kGradTile + 4, XR = 2 * kGradTile + 9;  // 4 and 9 modulo 64 banks
-  constexpr int kW = 2 * kGradTile + 3;                      // input frames of a unit
-  constexpr int kQ = kCh / (kBlock / 64), kX = (kW + 63) / 64;
-  __shared__ float gs[kCh * GR], xs[kCh * XR];
-  __shared__ double bsum[kBlock];
-  int blk = blockIdx.x, li = 0;
-  while (blk >= P.l[li].blocks) blk -= P.l[li++].blocks;
-  const GradLayer& L = P.l[li];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = lane & 15, q = lane >> 4;
-  const int split = blk % L.splits, cg = blk / L.splits;
-  const int u0 = (int)((int64_t)L.units * split / L.splits);
-  const int u1 = (int)((int64_t)L.units * (split + 1) / L.splits);
-  float xr[kQ][kX], gr[kQ];
-  auto load = [&](int u) {
-    const int64_t b = u / L.tiles;
-    const int t0 = u % L.tiles * kGradTile;
-    const float* x = L.x + (b * L.Cin + cg * kCh) * L.Fin;
-    const float* g = L.g + b * kCh * L.Fout;
-#pragma unroll
-    for (int r = 0; r < kQ; ++r) {
-      const int c = wave + 4 * r;
-      gr[r] = t0 + lane < L.Fout ? g[(int64_t)c * L.Fout + t0 + lane] : 0.f;
-#pragma unroll
-      for (int k = 0; k < kX; ++k) {
-        const int col = lane + 64 * k, f = 2 * t0 - 2 + col;
-        xr[r][k] = col < kW && f >= 0 && f < L.Fin ? x[(int64_t)c * L.Fin + f] : 0.f;
-      }
-    }
-  };
-  f32x4 tot[4][kKs];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int k = 0; k < kKs; ++k) tot[c][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-  double db = 0.0;
-  load(u0);
-  for (int u = u0; u < u1; ++u) {
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kQ; ++r) {
-      const int c = wave + 4 * r;
-      gs[c * GR + lane] = gr[r];
-#pragma unroll
-      for (int k = 0; k < kX; ++k)
-        if (lane + 64 * k < kW) xs[c * XR + lane + 64 * k] = xr[r][k];
-    }
-    __syncthreads();
-    if (u + 1 < u1) load(u + 1);
-    const int nt = min(kGradTile, L.Fout - u % L.tiles * kGradTile);
-    f32x4 acc[4][kKs];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int k = 0; k < kKs; ++k) acc[c][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* ga = gs + i * GR + q;
-    const float* xb = xs + (16 * wave + i) * XR + 2 * q;
-    for (int t = 0; t < nt; t += 4) {
-      float a[4], b[kKs];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) a[c] = ga[16 * c * GR + t];
-#pragma unroll
-      for (int k = 0; k < kKs; ++k) b[k] = xb[2 * t + k];
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int k = 0; k < kKs; ++k)
-          acc[c][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[k], acc[c][k], 0, 0, 0);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int k = 0; k < kKs; ++k) tot[c][k] += acc[c][k];
-    if (cg == 0) {  // bias gradient: four threads per channel, 16 frames each
-      float s = 0.f;
-#pragma unroll
-      for (int t = 0; t < kGradTile / 4; ++t)
-        s += gs[(threadIdx.x >> 2) * GR + (threadIdx.x & 3) * (kGradTile / 4) + t];
-      db += (double)s;
-    }
-  }
-  float* part = L.part + (int64_t)split * kCh * (L.Cin * kKs + 1);
-  const int ci = cg * kCh + 16 * wave + i;
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int k = 0; k < kKs; ++k)
-        part[((int64_t)(16 * c + 4 * q + e) * L.Cin + ci) * kKs + k] = tot[c][k][e];
-  if (cg == 0) {
-    bsum[threadIdx.x] = db;
-    __syncthreads();
-    if (threadIdx.x < kCh) {
-      const double* s = bsum + 4 * threadIdx.x;
-      part[(int64_t)kCh * L.Cin * kKs + threadIdx.x] =
-          (float)(((s[0] + s[1]) + s[2]) + s[3]);
-    }
-  }
+// Descriptor of n floats from p (wave-uniform), of 2^32 bytes at most; loads past it return 0.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const float* p, int64_t n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0,
+                                           (int)(unsigned)min(4 * n, (int64_t)0xFFFFFFF0), 0x00020000);
 }
 
-// Sums of the splits' partials in order, in double, one thread per weight (the last blocks: the
-// head's weight gradients, one output row each, and the loss).
-__global__ __launch_bounds__(kBlock) void grad_sum_kernel(GradLayers P, int64_t weights, int B,
-                                                          const float* dz, const float* h,
-                                                          const float* lossp, float* dWh,
-                                                          float* dbh, float* loss) {
-  const int nb = (int)((weights + kBlock - 1) / kBlock);
-  if ((int)blockIdx.x < nb) {
-    int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= weights) return;
-    int li = 0;
-    int64_t n = 0;
-    for (; li < kLayers; ++li) {
-      n = (int64_t)kCh * (P.l[li].Cin * kKs + 1);
-      if (j < n) break;
-      j -= n;
-    }
-    const float* p = P.l[li].part + j;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < P.l[li].splits; ++k) s += (double)p[(int64_t)k * n];
-    P.l[li].dw[j] = (float)s;
-    return;
-  }
-  // head: thread (c, r) sums samples r, r + 4, ...; c = 64 is the bias
-  __shared__ double red[4][kCh + 1];
-  const int o = (int)blockIdx.x - nb, c = threadIdx.x & 63, r = threadIdx.x >> 6;
-  if (o < kOut) {
+constexpr int kGradWaves = 16, kGradBlock = 64 * kGradWaves;
+constexpr int kGradFrames = 16;                    // frames of a unit
+constexpr int kGradCols = 2 * kGradFrames + 3;     // input frames of a unit
+constexpr int kGradStage = (4 * kGradCols + 63) / 64;
+constexpr int kGradRow = 80;  // 4 rows' 11 columns read at a time lie on distinct banks
+
+// dW[co][ci][k] = sum_{b,t} g[b][co][t] x[b][ci][2t + k - 2]: M = co, N = (ci, k), K = (b, t). A
+// block owns 32 x 16 weights and all of K, dealt to its 16 waves and summed in double through LDS,
+// so no partial sums go to memory and the weights come out of one launch. Consecutive blocks are
+// the two halves of co: with blocks dealt to the XCDs in turn, an XCD's L2 holds one half of g.
+// A wave's unit is 16 frames of a sample. Lane (i, q) of a matrix instruction holds frame q of four and
+// two output channels, g's fastest index, so that a load of g is four whole lines; the 16 columns
+// are four rows of x at most, which go through the wave's own piece of LDS (read by lanes, their 16
+// columns cost an L1 access per row and instruction: 87 us). A chain of 64 terms is added to double
+// sums before the next, which keeps the error of a long float32 chain out. The matrix instructions
+// are the bound to work towards (27 us on the 160 blocks of the first layer at 256 samples x 125
+// frames). 71 us there for all layers, the head and the loss; units of 32 frames 84 us; blocks of 64
+// x 64 channels with the batch split 64 ways and a launch that sums the parts 80 us, with 47 MB of
+// scratch.
+// The last blocks sum the head's gradients (one output row each) and the loss over the batch.
+__global__ __launch_bounds__(kGradBlock) void weight_grad_kernel(GradLayers P, int B,
+                                                                const float* dz, const float* h,
+                                                                const float* lossp, float* dWh,
+                                                                float* dbh, float* loss) {
+  __shared__ double red[kGradWaves][8][64];
+  __shared__ float xs[kGradWaves][4 * kGradRow];  // each wave's own
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int blk = blockIdx.x, li = 0;
+  while (li < kLayers && blk >= P.l[li].blocks) blk -= P.l[li++].blocks;
+  if (li == kLayers) {  // wave r sums samples r, r + 16, ...
     double a = 0.0, ab = 0.0;
-#pragma unroll 8
-    for (int b = r; b < B; b += 4) {
-      const double d = dz[(int64_t)b * kOut + o];
-      a += d * (double)h[(int64_t)b * kCh + c];
-      ab += d;
+    if (blk < kOut) {
+#pragma unroll 4
+      for (int b = wave; b < B; b += kGradWaves) {
+        const double d = dz[(int64_t)b * kOut + blk];
+        a += d * (double)h[(int64_t)b * kCh + lane];
+        ab += d;
+      }
+    } else {
+      for (int b = threadIdx.x; b < B; b += kGradBlock) a += (double)lossp[b];
     }
-    red[r][c] = a;
-    if (c == 0) red[r][kCh] = ab;
+    red[wave][0][lane] = a;
+    red[wave][1][lane] = ab;
     __syncthreads();
-    if (r == 0) dWh[o * kCh + c] = (float)(((red[0][c] + red[1][c]) + red[2][c]) + red[3][c]);
-    if (threadIdx.x == 0)
-      dbh[o] = (float)(((red[0][kCh] + red[1][kCh]) + red[2][kCh]) + red[3][kCh]);
+    if (wave != 0) return;
+    a = ab = 0.0;
+    for (int r = 0; r < kGradWaves; ++r) {
+      a += red[r][0][lane];
+      ab += red[r][1][lane];
+    }
+    if (blk < kOut) {
+      dWh[blk * kCh + lane] = (float)a;
+      if (lane == 0) dbh[blk] = (float)ab;
+    } else {
+      for (int d = 32; d > 0; d >>= 1) a += __shfl_xor(a, d);
+      if (lane == 0 && loss) *loss = (float)(a / (double)(B * kOut));
+    }
     return;
   }
-  double a = 0.0;
-  for (int b = threadIdx.x; b < B; b += kBlock) a += (double)lossp[b];
-  a = block_sum<double>(a, red[0]);
-  if (threadIdx.x == 0) *loss = (float)(a / (double)(B * kOut));
+  const GradLayer& L = P.l[li];
+  const int i = lane & 15, q = lane >> 4;
+  const int co = (blk & 1) * 32, col = (blk >> 1) * 16 + i;  // this lane's column (ci, k)
+  const int ci = col / kKs, k = col - ci * kKs;
+  const int Fin = L.Fin, Fout = L.Fout;
+  const int tiles = (Fout + kGradFrames - 1) / kGradFrames;
+  const int w = __builtin_amdgcn_readfirstlane(wave);
+  const int64_t units = (int64_t)B * tiles, u0 = units * w / kGradWaves;
+  const int n = (int)(units * (w + 1) / kGradWaves - u0);
+  int b = (int)(u0 / tiles), t0 = (int)(u0 - (int64_t)b * tiles) * kGradFrames;
+  const int c0 = (blk >> 1) * 16 / kKs;  // first channel of the columns
+  struct Unit {
+    f32x2 a[kGradFrames / 4];
+    float x[kGradStage];
+    int nt;  // frames
+  };
+  auto load = [&](Unit& U) {
+    const auto rx = buffer_at(L.x + ((int64_t)b * L.Cin + c0) * Fin, (int64_t)(L.Cin - c0) * Fin);
+    const auto rg = buffer_at(L.g + ((int64_t)b * Fout + t0) * kCh, (int64_t)(Fout - t0) * kCh);
+    U.nt = Fout - t0;
+#pragma unroll
+    for (int m = 0; m < kGradStage; ++m) {
+      const int e = lane + 64 * m, r = e / kGradCols, f = 2 * t0 - 2 + e - r * kGradCols;
+      const unsigned off = (unsigned)f < (unsigned)Fin ? (unsigned)(r * Fin + f) * 4u : ~0u;
+      U.x[m] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, off, 0, 0));
+    }
+#pragma unroll
+    for (int j = 0; j < kGradFrames / 4; ++j)
+      U.a[j] = __builtin_bit_cast(
+          f32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                     rg, (unsigned)((4 * j + q) * kCh + co + 2 * i) * 4u, 0, 0));
+    t0 += kGradFrames;
+    if (t0 >= Fout) {
+      t0 = 0;
+      ++b;
+    }
+  };
+  float* const xw = xs[wave];
+  const float* const xq = xw + (ci - c0) * kGradRow + k + 2 * q;
+  double tot[2][4] = {};
+  double bias[2] = {0.0, 0.0};
+  Unit nx;
+  if (n > 0) load(nx);
+  for (int s = 0; s < n;) {
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    float bs[2] = {0.f, 0.f};
+    const int end = min(s + 64 / kGradFrames, n);
+    for (; s < end; ++s) {
+      const Unit c = nx;
+#pragma unroll
+      for (int m = 0; m < kGradStage; ++m) {
+        const int e = lane + 64 * m, r = e / kGradCols;
+        if (e < 4 * kGradCols) xw[r * kGradRow + e - r * kGradCols] = c.x[m];
+      }
+      if (s + 1 < n) load(nx);
+      float xv[kGradFrames / 4];
+#pragma unroll
+      for (int j = 0; j < kGradFrames / 4; ++j) xv[j] = xq[8 * j];
+      auto multiply = [&](auto whole) {
+#pragma unroll
+        for (int j = 0; j < kGradFrames / 4; ++j) {
+          if (!whole.value && 4 * j >= c.nt) break;
+          const float v = whole.value || 4 * j + q < c.nt ? xv[j] : 0.f;
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[j][m], v, acc[m], 0, 0, 0);
+            bs[m] += c.a[j][m];
+          }
+        }
+      };
+      if (c.nt >= kGradFrames)
+        multiply(std::true_type{});
+      else
+        multiply(std::false_type{});
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tot[m][e] += (double)acc[m][e];
+      bias[m] += (double)bs[m];
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][4 * m + e][lane] = tot[m][e];
+  __syncthreads();
+  if (wave < 8) {
+    double v = 0.0;
+    for (int r = 0; r < kGradWaves; ++r) v += red[r][wave][lane];
+    L.dw[(int64_t)(co + 2 * (4 * q + (wave & 3)) + (wave >> 2)) * L.Cin * kKs + col] = (float)v;
+  }
+  if (blk >= 2) return;  // bias: by the blocks of the first columns
+  __syncthreads();
+  red[wave][0][lane] = bias[0];
+  red[wave][1][lane] = bias[1];
+  __syncthreads();
+  if (threadIdx.x >= 32) return;
+  double v = 0.0;
+  for (int r = 0; r < kGradWaves; ++r)
+    for (int u = 0; u < 4; ++u) v += red[r][threadIdx.x & 1][16 * u + (threadIdx.x >> 1)];
+  L.dw[(int64_t)kCh * L.Cin * kKs + co + threadIdx.x] = (float)v;
 }
 
 __global__ __launch_bounds__(kBlock) void adam_kernel(int64_t n, float* p, const float* g,
@@ -929,30 +927,20 @@ grafx_status grafx_encoder_backward(int32_t batch, int32_t frames, const float* 
     }
   GradLayers P;
   int blocks = 0;
-  int64_t n_w = 0;
-  float* part = grads + L.part;
   for (int l = 1; l <= kLayers; ++l) {
     GradLayer& G = P.l[l - 1];
     G.x = l == 1 ? x : t.y[l - 1];
     G.g = t.dy[l];
-    G.part = part;
     G.dw = dweights + L.w[l];
     G.Cin = cin_of(l);
     G.Fin = L.F[l - 1];
     G.Fout = L.F[l];
-    G.tiles = grad_tiles(G.Fout);
-    G.splits = grad_splits(batch, G.Fout);
-    G.units = batch * G.tiles;
-    G.blocks = G.splits * (G.Cin / kCh);
+    G.blocks = 2 * (G.Cin * kKs / 16);
     blocks += G.blocks;
-    const int64_t n = (int64_t)kCh * (G.Cin * kKs + 1);
-    n_w += n;
-    part += G.splits * n;
   }
-  weight_grad_kernel<<<blocks, kBlock, 0, stream>>>(P);
-  grad_sum_kernel<<<(unsigned)((n_w + kBlock - 1) / kBlock + kOut + 1), kBlock, 0,
-                    stream>>>(P, n_w, batch, grads + L.dz, acts + L.h, grads + L.lossp,
-                              dweights + L.w[kLayers + 1], dweights + L.b[kLayers + 1], loss);
+  weight_grad_kernel<<<blocks + kOut + 1, kGradBlock, 0, stream>>>(
+      P, batch, grads + L.dz, acts + L.h, grads + L.lossp, dweights + L.w[kLayers + 1],
+      dweights + L.b[kLayers + 1], loss);
   return hip_st(hipGetLastError(), "encoder_backward launch");
 }
 

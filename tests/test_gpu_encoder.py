@@ -13,6 +13,7 @@ import synth
 from gpu_common import grad_err, say
 from oracle import encoder as E
 from paper_2408_03204_amd import encoder as enc
+from paper_2408_03204_amd._lib import check, load
 
 pytestmark = pytest.mark.gpu
 F64 = torch.float64
@@ -177,8 +178,8 @@ def test_gather_is_a_copy():
 @pytest.mark.parametrize("B,F", [(1, 1), (3, 2), (2, 257), (1, 1100), (65, 9)])
 def test_layer_tilings_match_oracle(B, F):
     """Forward and backward where the work is cut differently: one and two frames; layer 2 or
-    layers 2-4 too long for the per-sample kernels (more than 128 input frames); fewer, as many
-    and more (sample, tile) units than weight-gradient splits. Random features; same tolerances as
+    layers 2-4 too long for the per-sample kernels (more than 128 input frames); fewer and more
+    groups of frames than a weight-gradient block has waves. Random features; same tolerances as
     above."""
     say(f"[encoder tilings] B={B} F={F}")
     rng = np.random.default_rng(100 * B + F)
@@ -213,3 +214,28 @@ def test_forward_bits_do_not_depend_on_the_batch(bf16):
     few = enc.Encoder(w, 3, 125).forward(x[:3].contiguous(), bf16=bf16)
     torch.cuda.synchronize()
     assert torch.equal(many[:3], few)
+
+
+@pytest.mark.parametrize("B,F", [(1, 1), (5, 37), (65, 9)])
+def test_backward_within_its_scratch_and_without_a_loss(B, F):
+    """The backward writes nothing past the scratch that grafx_encoder_sizes states, and a NULL loss
+    gives the same gradients."""
+    say(f"[encoder scratch] B={B} F={F}")
+    rng = np.random.default_rng(B + F)
+    x = torch.as_tensor(rng.standard_normal((B, 256, F)).astype(np.float32)).cuda()
+    lab = torch.as_tensor(rng.uniform(size=(B, 11)).astype(np.float32)).cuda()
+    net = enc.Encoder(torch.as_tensor(_weights(2)[0]).cuda(), B, F)
+    net.forward(x)
+    n_grad = enc.sizes(B, F)[2]
+    scratch = torch.full((n_grad + 4096,), -7.0, device="cuda")
+    net.grads = scratch[:n_grad]
+    net.backward(x, lab)
+    torch.cuda.synchronize()
+    assert (scratch[n_grad:] == -7.0).all()
+    dw = torch.empty_like(net.dw)
+    check(load().grafx_encoder_backward(B, F, x.data_ptr(), net.w.data_ptr(), net.acts.data_ptr(),
+                                        net.out.data_ptr(), lab.data_ptr(), None, dw.data_ptr(),
+                                        scratch.data_ptr(),
+                                        torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(dw, net.dw)
