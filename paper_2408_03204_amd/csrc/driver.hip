@@ -204,35 +204,31 @@ unsigned* tickets(void* ws, const WsLayout& L, const grafx_schedule_t* h, bool b
          (size_t)(1 + (bwd ? n_dynamics(h) : 0)) * kCompTicketStride;
 }
 
-bool is_dynamics(int t) { return t == GRAFX_COMPRESSOR || t == GRAFX_NOISEGATE; }
+bool is_dynamics(int t) {
+  return t == GRAFX_COMPRESSOR || t == GRAFX_NOISEGATE || t == GRAFX_COMPRESSOR_AR;
+}
 bool has_dynamics(const grafx_schedule_t* h) {
   return n_dynamics(h) + h->type_count[GRAFX_COMPRESSOR_AR] > 0;
 }
 
-// Prepare the dynamics state of one pass (all compressor and noisegate nodes, all steps): chaining
-// state reset, coefficients formed from P. The forward call also clears the error word; it runs
-// whenever the graph has any dynamics node (attack/release compressors included).
-hipError_t prepare_comp(const grafx_schedule_t* h, const float* const* P, void* ws,
-                        const WsLayout& L, bool bwd, int64_t T, hipStream_t stream) {
-  const int n_comp = n_dynamics(h);
-  if (!has_dynamics(h) || (bwd && n_comp == 0)) return hipSuccess;
-  return launch_dyn_prepare(false, at<uint64_t>(ws, bwd ? L.comp_ragg : L.comp_agg),
-                            (int64_t)n_comp * comp_chunks(T), tickets(ws, L, h, bwd),
-                            bwd ? nullptr : error_word(ws, L), P ? P[GRAFX_COMPRESSOR] : nullptr,
-                            h->type_count[GRAFX_COMPRESSOR], P ? P[GRAFX_NOISEGATE] : nullptr,
-                            h->type_count[GRAFX_NOISEGATE], stream);
-}
-
-// The same for the attack/release compressors.
-hipError_t prepare_ar(const grafx_schedule_t* h, const float* const* P, void* ws, const WsLayout& L,
-                      bool bwd, int64_t T, hipStream_t stream) {
-  const int n_ar = h->type_count[GRAFX_COMPRESSOR_AR];
-  if (n_ar == 0) return hipSuccess;
-  const size_t chunks = comp_chunks(T);
-  unsigned* t = at<unsigned>(ws, L.ar_tickets) + (bwd ? (size_t)n_ar * kCompTicketStride : 0);
-  return launch_dyn_prepare(true, at<uint64_t>(ws, bwd ? L.ar_ragg : L.ar_slots),
-                            (int64_t)n_ar * (bwd ? chunks * 2 : ar_slot_words(chunks)), t, nullptr,
-                            P[GRAFX_COMPRESSOR_AR], n_ar, nullptr, 0, stream);
+// Prepare one pass over the dynamics nodes (all steps of all types): chaining state reset,
+// coefficients formed from P. The forward call also clears the error word.
+PrepareJobs dyn_jobs(const grafx_schedule_t* h, const float* const* P, void* ws, const WsLayout& L,
+                     bool bwd, int64_t T) {
+  PrepareJobs j;
+  if (!has_dynamics(h)) return j;
+  const int64_t n_comp = n_dynamics(h), n_ar = h->type_count[GRAFX_COMPRESSOR_AR];
+  const int64_t chunks = comp_chunks(T);
+  auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
+  if (!bwd) j.err = error_word(ws, L);
+  j.comp = {at<uint64_t>(ws, bwd ? L.comp_ragg : L.comp_agg), n_comp * chunks,
+            tickets(ws, L, h, bwd), par(GRAFX_COMPRESSOR), h->type_count[GRAFX_COMPRESSOR],
+            par(GRAFX_NOISEGATE), h->type_count[GRAFX_NOISEGATE]};
+  j.ar = {at<uint64_t>(ws, bwd ? L.ar_ragg : L.ar_slots),
+          n_ar * (bwd ? chunks * 2 : (int64_t)ar_slot_words(chunks)),
+          at<unsigned>(ws, L.ar_tickets) + (bwd ? n_ar * kCompTicketStride : 0),
+          par(GRAFX_COMPRESSOR_AR), (int)n_ar, nullptr, 0};
+  return j;
 }
 
 // The dynamics block order of one launch: the setting, or for "auto" (2) interleaved nodes once a
@@ -356,11 +352,14 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
   const WsLayout L = ws_layout(h, T, false);
   const GraphView g = make_view(h, dev_plan, T, S, U);
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
-  hipError_t e = hipSuccess;
-  // per-render parameter preprocessing
-  if (h->type_count[GRAFX_EQ] > 0)
-    e = launch_eq_design(par(GRAFX_EQ), h->type_count[GRAFX_EQ], at<double>(ws, L.eq_h),
-                         at<float>(ws, L.eq_H), stream);
+  // per-render parameter preprocessing and the dynamics chaining state
+  PrepareJobs jobs = dyn_jobs(h, P, ws, L, false, T);
+  jobs.eq_P = par(GRAFX_EQ);
+  jobs.n_eq = h->type_count[GRAFX_EQ];
+  jobs.eq_H = at<float>(ws, L.eq_H);
+  hipError_t e = launch_prepare(jobs, stream);
+  if (e == hipSuccess)
+    e = launch_eq_design(jobs.n_eq, at<double>(ws, L.eq_h), jobs.eq_H, stream);
   for (int f = 0; f < 2 && e == hipSuccess; ++f)
     if (h->type_count[kDelayType[f]] > 0)
       e = launch_delay_design(kDelaySlots[f], par(kDelayType[f]), h->type_count[kDelayType[f]],
@@ -370,8 +369,6 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,
                          at<double2>(ws, L.rv_Un), at<float>(ws, L.rv_h), at<float4>(ws, L.rv_H),
                          stream);
-  if (e == hipSuccess) e = prepare_comp(h, P, ws, L, false, T, stream);
-  if (e == hipSuccess) e = prepare_ar(h, P, ws, L, false, T, stream);
   for (int n = 1; n <= h->N && e == hipSuccess; ++n)
     e = enqueue_fwd_step(h, g, P, U, ws, L, n, stream);
   return hip_status(e, "render launch");
@@ -480,8 +477,7 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   g.dU = dU;
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
   auto dpar = [&](int t) -> float* { return dP ? dP[t] : nullptr; };
-  hipError_t e = prepare_comp(h, P, ws, L, true, T, stream);
-  if (e == hipSuccess) e = prepare_ar(h, P, ws, L, true, T, stream);
+  hipError_t e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
   for (int n = h->N - 1; n >= 1 && e == hipSuccess; --n)
     e = enqueue_bwd_step(h, g, P, dU, ws, L, n, stream);
   if (e == hipSuccess && dS && h->K > 0)  // adjoint of the input step: sum over output edges
@@ -540,9 +536,7 @@ grafx_status grafx_render_step(const grafx_schedule_t* h, const void* dev_plan, 
   const WsLayout L = ws_layout(h, T, false);
   const GraphView g = make_view(h, dev_plan, T, S, U);
   hipError_t e = hipSuccess;
-  const bool ar = h->step_type[step] == GRAFX_COMPRESSOR_AR;
-  if (is_dynamics(h->step_type[step]) || ar) e = prepare_comp(h, P, ws, L, false, T, stream);
-  if (e == hipSuccess && ar) e = prepare_ar(h, P, ws, L, false, T, stream);
+  if (is_dynamics(h->step_type[step])) e = launch_prepare(dyn_jobs(h, P, ws, L, false, T), stream);
   if (e == hipSuccess) e = enqueue_fwd_step(h, g, P, U, ws, L, step, stream);
   return hip_status(e, "render_step launch");
 }
@@ -561,9 +555,7 @@ grafx_status grafx_render_backward_step(const grafx_schedule_t* h, const void* d
   g.dY = dY;
   g.dU = dU;
   hipError_t e = hipSuccess;
-  if (is_dynamics(h->step_type[step])) e = prepare_comp(h, P, ws, L, true, T, stream);
-  if (e == hipSuccess && h->step_type[step] == GRAFX_COMPRESSOR_AR)
-    e = prepare_ar(h, P, ws, L, true, T, stream);
+  if (is_dynamics(h->step_type[step])) e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
   if (e == hipSuccess) e = enqueue_bwd_step(h, g, P, dU, ws, L, step, stream);
   return hip_status(e, "render_backward_step launch");
 }

@@ -19,7 +19,7 @@
 // Instructions bound the adjoint as much as memory does (1.4k float and 0.5k double instructions
 // per wave left the vector units busy 64 of 98 us on 48 compressors of 2^18 samples), so: what
 // depends only on the node (powers of a, curve constants) is formed once per pass by
-// dyn_prepare_kernel and read as scalars; lanes exchange by DPP moves and readlane, not through
+// prepare_kernel and read as scalars; lanes exchange by DPP moves and readlane, not through
 // LDS; both gain curves are one branch-free ramp in base-2 units (dynamics.h); the curve's
 // derivatives are scaled once per chunk instead of per sample; and a thread's first read of an
 // earlier total is under way during the parameter sums. The same strips: adjoint 102 -> 81 us,
@@ -326,32 +326,34 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
   }
 }
 
-// Before a pass: the published totals set to "not ready", the tickets (and, given one, the error
-// word) to 0, and the nodes' coefficients formed. AR: rows of attack/release compressors.
-template <bool AR>
-__global__ __launch_bounds__(kBlock) void dyn_prepare_kernel(uint64_t* tot, int64_t n,
-                                                             unsigned* tickets, unsigned* err,
-                                                             const float* P, int n_comp,
-                                                             const float* Pg, int n_gate) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) tot[i] = kNotReady;
-  if (i == 0 && err) *err = 0u;
-  if (i >= n_comp + n_gate) return;
-  unsigned* line = tickets + i * kCompTicketStride;
+__device__ __forceinline__ void* reset_line(unsigned* tickets, int64_t row) {
+  unsigned* line = tickets + row * kCompTicketStride;
   *line = 0u;
-  void* coefs = reinterpret_cast<char*>(line) + kCoefOffset;
-  if constexpr (AR) {
-    const float* p = P + i * kArParams;
+  return reinterpret_cast<char*>(line) + kCoefOffset;
+}
+
+// Before a pass: published totals set to "not ready", tickets and the error word to 0, the nodes'
+// coefficients and the EQ nodes' exp(p) formed. One thread an item of every kind.
+__global__ __launch_bounds__(kBlock) void prepare_kernel(PrepareJobs j) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i == 0 && j.err) *j.err = 0u;
+  if (i < j.comp.n_tot) j.comp.tot[i] = kNotReady;
+  if (i < j.ar.n_tot) j.ar.tot[i] = kNotReady;
+  if (i < (int64_t)j.n_eq * 1024)
+    reinterpret_cast<double*>(j.eq_H + (i >> 10) * kEqFFT)[i & 1023] = exp((double)j.eq_P[i]);
+  if (i < j.ar.n) {
+    const float* p = j.ar.P + i * kArParams;
     DynCoefAR k;
     k.aa = (double)p[0];
     k.ar = (double)p[1];
     k.ba = 1.0 - k.aa;
     k.br = 1.0 - k.ar;
     k.cv = make_curve(p[2], p[3], p[4], false);
-    *reinterpret_cast<DynCoefAR*>(coefs) = k;
-  } else {
-    const bool gate = i >= n_comp;
-    const float* p = gate ? Pg + (i - n_comp) * 4 : P + i * 4;
+    *reinterpret_cast<DynCoefAR*>(reset_line(j.ar.tickets, i)) = k;
+  }
+  if (i < j.comp.n + j.comp.n_gate) {
+    const bool gate = i >= j.comp.n;
+    const float* p = gate ? j.comp.Pg + (i - j.comp.n) * 4 : j.comp.P + i * 4;
     DynCoef k;
     k.a = (double)p[0];
     k.b = 1.0 - k.a;
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kBlock) void dyn_prepare_kernel(uint64_t* tot, int6
 #pragma unroll
     for (int d = 1; d < 8; ++d) k.pw[d] = k.pw[d - 1] * k.pw[d - 1];
     k.cv = make_curve(p[1], p[2], p[3], gate);
-    *reinterpret_cast<DynCoef*>(coefs) = k;
+    *reinterpret_cast<DynCoef*>(reset_line(j.comp.tickets, i)) = k;
   }
 }
 
@@ -373,17 +375,11 @@ __global__ __launch_bounds__(kBlock) void dyn_prepare_kernel(uint64_t* tot, int6
 
 int comp_chunks(int64_t T) { return (int)((T + kChunk - 1) / kChunk); }
 
-hipError_t launch_dyn_prepare(bool ar, uint64_t* tot, int64_t n, unsigned* tickets, unsigned* err,
-                              const float* P, int n_comp, const float* Pg, int n_gate,
-                              hipStream_t s) {
-  const int64_t m = std::max(std::max(n, (int64_t)n_comp + n_gate), (int64_t)(err ? 1 : 0));
+hipError_t launch_prepare(const PrepareJobs& j, hipStream_t s) {
+  const int64_t m = std::max({j.comp.n_tot, j.ar.n_tot, (int64_t)j.n_eq * 1024, (int64_t)j.ar.n,
+                              (int64_t)j.comp.n + j.comp.n_gate, (int64_t)(j.err ? 1 : 0)});
   if (m <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((m + kBlock - 1) / kBlock);
-  if (ar)
-    dyn_prepare_kernel<true><<<blocks, kBlock, 0, s>>>(tot, n, tickets, err, P, n_comp, Pg, n_gate);
-  else
-    dyn_prepare_kernel<false><<<blocks, kBlock, 0, s>>>(tot, n, tickets, err, P, n_comp, Pg,
-                                                        n_gate);
+  prepare_kernel<<<(unsigned)((m + kBlock - 1) / kBlock), kBlock, 0, s>>>(j);
   return hipGetLastError();
 }
 

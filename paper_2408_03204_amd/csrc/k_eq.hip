@@ -41,65 +41,77 @@ namespace {
 using namespace fft4;
 
 // ---- design ----------------------------------------------------------------------------------
-// Cosine sums in double, eight lanes per output: lane q sums the terms m = q, q + 8, ... with the
-// stride-8 Chebyshev recurrence c_{m+8} = 2 cos(8 theta) c_m - c_{m-8}, so each lane's dependent
-// chain is 128 FMAs long; the eight partial sums are combined by a fixed xor butterfly (addition
-// is commutative, so all eight lanes end with the same value). Every angle is theta = 2 pi s / M
-// for an integer s, so the starting cosines of each lane are read from the table
-// tab[i] = cos(2 pi i / M) (correctly rounded) instead of being evaluated.
+// The three cosine sums (A -> h, h -> H and, in the adjoint, hbar -> dL/dp) are products of a
+// [nodes x 1024] matrix with a cosine matrix, in double on the matrix cores: a block computes 16
+// outputs of 16 nodes, its 4 waves taking 256 terms each. Lane (i, q) supplies node i and output i at
+// the wave's terms 64 q, 64 q + 1, ..., so a row is read 16 bytes at a time; the cosines follow the
+// Chebyshev recurrence c_{m+1} = 2 cos(theta) c_m - c_{m-1} over 64 terms from correctly rounded table
+// values (every angle is 2 pi s / M for an integer s). The sums over even and odd terms are kept
+// apart: their difference is the sum at M / 2 - s, so H needs half the products. 48 nodes: h 11.2 ->
+// 7.6 us, H 18.5 -> 8.5 us, dL/dp 11.4 -> 7.8 us, bound by the matrix rate in double (twice the waves
+// with half the terms each take as long); 4 nodes: 5.9, 5.4, 5.7 -> 5.3, 4.9, 4.9 us (launch and load
+// latency). Before, eight lanes an output read every term from LDS, and each of 32 blocks a node
+// formed all 1024 exponentials, which are now part of the launch that prepares the pass.
 
-constexpr int kCosLanes = 8;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int M>
-__device__ __forceinline__ double cos_sum(const double* w, int s, const double* tab) {
-  // sum_{m=1}^{1023} w[m] cos(2 pi m s / M), 0 <= s < 2 M
-  const int q = (int)threadIdx.x & (kCosLanes - 1);
-  const double two_c8 = 2.0 * tab[(kCosLanes * s) % M];
-  double cm = tab[((q - kCosLanes) * s % M + M) % M], c = tab[(q * s) % M];
-  double acc = q > 0 ? w[q] * c : 0.0;  // the m = 0 term is not part of the sum
-  {
-    const double cn = fma(two_c8, c, -cm);
-    cm = c;
-    c = cn;
-  }
-#pragma unroll 8
-  for (int i = 1; i < 1024 / kCosLanes; ++i) {  // the same trip count on every lane
-    acc = fma(w[q + kCosLanes * i], c, acc);
-    const double cn = fma(two_c8, c, -cm);
-    cm = c;
-    c = cn;
+// w [rows][stride] -> the 16 x 16 sums of this block: thread (r, n) of 16 x 16 receives
+// sum_m w[16 blockIdx.y + r][m] cos(2 pi m s / M), s = 16 blockIdx.x + n, 0 <= s <= M, as the sums over
+// even and over odd m (added: the sum at s; subtracted, for even M: at M / 2 - s); the term m = 0
+// counts half if HALF. Rows past the last repeat it.
+template <int M, bool HALF>
+__device__ __forceinline__ double2 cos_sums(const double* w, int rows, int stride,
+                                            const double* tab) {
+  __shared__ double2 red[4][256];
+  const int wave = threadIdx.x >> 6, i = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+  const int row = min((int)blockIdx.y * 16 + i, rows - 1), s = (int)blockIdx.x * 16 + i;
+  const int m0 = 256 * wave + 64 * q;
+  const double2* wr = reinterpret_cast<const double2*>(w + (int64_t)row * stride + m0);
+  double2 a[32];
+#pragma unroll
+  for (int m = 0; m < 32; ++m) a[m] = wr[m];
+  double c = tab[m0 * s % M], cm = tab[(m0 + M - 1) * s % M];
+  const double two_c = 2.0 * tab[s % M];
+  if (HALF && m0 == 0) a[0].x *= 0.5;
+  f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+  for (int m = 0; m < 32; ++m) {
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m].x, c, acc[0], 0, 0, 0);
+    cm = fma(two_c, c, -cm);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m].y, cm, acc[1], 0, 0, 0);
+    c = fma(two_c, cm, -c);
   }
 #pragma unroll
-  for (int d = 1; d < kCosLanes; d <<= 1) acc += __shfl_xor(acc, d, 64);
-  return acc;
+  for (int e = 0; e < 4; ++e) red[wave][(q + 4 * e) * 16 + i] = make_double2(acc[0][e], acc[1][e]);
+  __syncthreads();
+  const int t = threadIdx.x;
+  return make_double2(((red[0][t].x + red[1][t].x) + red[2][t].x) + red[3][t].x,
+                      ((red[0][t].y + red[1][t].y) + red[2][t].y) + red[3][t].y);
 }
 
-// Outputs handled by one block of the design kernels (kCosLanes threads per output).
-constexpr int kCosOut = kBlock / kCosLanes;
+constexpr int kAStride = kN / 2;  // A = exp(p) waits in the first half of the node's row of H
 
-__global__ __launch_bounds__(kBlock) void eq_design_h_kernel(const float* P, double* h) {
-  __shared__ double A[1024];
-  const int slot = blockIdx.x;
-  for (int i = threadIdx.x; i < 1024; i += kBlock) A[i] = exp((double)P[(int64_t)slot * 1024 + i]);
-  __syncthreads();
-  const int n = blockIdx.y * kCosOut + (int)threadIdx.x / kCosLanes;  // 0..1023
-  const double h0 = (A[0] + 2.0 * cos_sum<2047>(A, n, kCos2047)) / 2047.0;
+__global__ __launch_bounds__(kBlock) void eq_design_h_kernel(const double* A, int n_eq,
+                                                             double* h) {
+  const double2 sum = cos_sums<2047, true>(A, n_eq, kAStride, kCos2047);
+  const int slot = blockIdx.y * 16 + (threadIdx.x >> 4), n = blockIdx.x * 16 + (threadIdx.x & 15);
+  if (slot >= n_eq) return;
   const double win = 0.5 + 0.5 * cospi((double)n / 1023.0);
-  if ((threadIdx.x & (kCosLanes - 1)) == 0) h[(int64_t)slot * 1024 + n] = win * h0;
+  h[(int64_t)slot * 1024 + n] = win * (2.0 * (sum.x + sum.y) / 2047.0);
 }
 
-__global__ __launch_bounds__(kBlock) void eq_design_H_kernel(const double* h, float* H) {
-  __shared__ double hs[1024];
-  const int slot = blockIdx.x;
-  for (int i = threadIdx.x; i < 1024; i += kBlock) hs[i] = h[(int64_t)slot * 1024 + i];
-  __syncthreads();
-  const int k = blockIdx.y * kCosOut + (int)threadIdx.x / kCosLanes;
-  if (k > kN / 2) return;  // whole groups of kCosLanes lanes leave together
-  const float Hk = (float)((hs[0] + 2.0 * cos_sum<kN>(hs, k, kCos4096)) / (double)kN);
-  if ((threadIdx.x & (kCosLanes - 1)) != 0) return;
+__global__ __launch_bounds__(kBlock) void eq_design_H_kernel(const double* h, int n_eq, float* H) {
+  const double2 sum = cos_sums<kN, true>(h, n_eq, 1024, kCos4096);
+  const int slot = blockIdx.y * 16 + (threadIdx.x >> 4), k = blockIdx.x * 16 + (threadIdx.x & 15);
+  if (slot >= n_eq || k > kN / 4) return;
   float* Hn = H + (int64_t)slot * kN;
-  Hn[k] = Hk;
-  if (k > 0 && k < kN / 2) Hn[kN - k] = Hk;
+  auto put = [&](int bin, double v) {
+    const float Hk = (float)(2.0 * v / (double)kN);
+    Hn[bin] = Hk;
+    if (bin > 0 && bin < kN / 2) Hn[kN - bin] = Hk;
+  };
+  put(k, sum.x + sum.y);
+  if (k < kN / 4) put(kN / 2 - k, sum.x - sum.y);
 }
 
 // ---- forward ----------------------------------------------------------------------------------
@@ -249,27 +261,25 @@ __global__ __launch_bounds__(kBlock) void eq_grad_ifft_kernel(const float* F, do
 
 // dL/dp_k = (kappa_k / 2047) A_k (s[0] + sum_{n>=1} s[n] cos(2 pi k n / 2047)).
 __global__ __launch_bounds__(kBlock) void eq_grad_p_kernel(const float* P, const double* sbuf,
-                                                           float* dP) {
-  __shared__ double s[1024];
-  const int slot = blockIdx.x;
-  for (int i = threadIdx.x; i < 1024; i += kBlock) s[i] = sbuf[(int64_t)slot * 1024 + i];
-  __syncthreads();
-  const int k = blockIdx.y * kCosOut + (int)threadIdx.x / kCosLanes;  // 0..1023
-  const double acc = cos_sum<2047>(s, k, kCos2047);
-  if ((threadIdx.x & (kCosLanes - 1)) != 0) return;
+                                                           int n_eq, float* dP) {
+  const double2 sum = cos_sums<2047, false>(sbuf, n_eq, 1024, kCos2047);
+  const int slot = blockIdx.y * 16 + (threadIdx.x >> 4), k = blockIdx.x * 16 + (threadIdx.x & 15);
+  if (slot >= n_eq) return;
   const double A = exp((double)P[(int64_t)slot * 1024 + k]);
   const double kappa = k == 0 ? 1.0 : 2.0;
-  dP[(int64_t)slot * 1024 + k] = (float)(kappa / 2047.0 * A * (s[0] + acc));
+  dP[(int64_t)slot * 1024 + k] = (float)(kappa / 2047.0 * A * (sum.x + sum.y));
 }
 
 }  // namespace
 
 int eq_tiles(int64_t T) { return (int)((T + kEqHop - 1) / kEqHop); }
 
-hipError_t launch_eq_design(const float* P, int n_eq, double* h, float* H, hipStream_t s) {
+hipError_t launch_eq_design(int n_eq, double* h, float* H, hipStream_t s) {
   if (n_eq <= 0) return hipSuccess;
-  eq_design_h_kernel<<<dim3(n_eq, 1024 / kCosOut), kBlock, 0, s>>>(P, h);
-  eq_design_H_kernel<<<dim3(n_eq, (kN / 2 + kCosOut) / kCosOut), kBlock, 0, s>>>(h, H);
+  const int rows = (n_eq + 15) / 16;
+  eq_design_h_kernel<<<dim3(1024 / 16, rows), kBlock, 0, s>>>(reinterpret_cast<double*>(H), n_eq,
+                                                             h);
+  eq_design_H_kernel<<<dim3(kN / 4 / 16 + 1, rows), kBlock, 0, s>>>(h, n_eq, H);
   return hipGetLastError();
 }
 
@@ -293,7 +303,7 @@ hipError_t launch_eq_grad(const float* P, const float* Fpart, int tiles, float* 
   if (n_eq <= 0) return hipSuccess;
   eq_fold_reduce_kernel<<<dim3(n_eq, (kN / 2 + 64) / 64), kBlock, 0, s>>>(Fpart, tiles, F);
   eq_grad_ifft_kernel<<<n_eq, kBlock, 0, s>>>(F, sbuf);
-  eq_grad_p_kernel<<<dim3(n_eq, 1024 / kCosOut), kBlock, 0, s>>>(P, sbuf, dP);
+  eq_grad_p_kernel<<<dim3(1024 / 16, (n_eq + 15) / 16), kBlock, 0, s>>>(P, sbuf, n_eq, dP);
   return hipGetLastError();
 }
 

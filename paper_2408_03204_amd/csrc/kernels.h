@@ -44,7 +44,8 @@ constexpr int kEqHop = 2048;  // outputs per tile
 int eq_tiles(int64_t T);
 constexpr int kEqFoldStride = 2112;  // N/2 + 1 = 2049 folded bins, padded to 256 bytes
 // h: double [n_eq][1024] (windowed FIR, taps n = 0..1023; even), H: float [n_eq][4096]
-hipError_t launch_eq_design(const float* P, int n_eq, double* h, float* H, hipStream_t s);
+// A = exp(p) is taken from H's rows, where launch_prepare leaves it
+hipError_t launch_eq_design(int n_eq, double* h, float* H, hipStream_t s);
 hipError_t launch_eq_fwd(const GraphView& g, float* U, const float* H, int node_begin,
                          int n_nodes, hipStream_t s);
 // Adjoint of one step. Fpart: float [n_eq][tiles][kEqFoldStride]: the regions (by parameter
@@ -67,14 +68,26 @@ int comp_chunks(int64_t T);
 // serialise), with the node's coefficients in the second half of its line; err: error word (bit 0:
 // a wait ran out, bit 1: tickets were not reset)
 constexpr int kCompTicketStride = 64;
-// Before a pass: n totals reset, the rows' tickets and coefficients written (rows: n_comp nodes of
-// P, then n_gate noisegates of Pg; ar: attack/release rows), the error word cleared if given.
-hipError_t launch_dyn_prepare(bool ar, uint64_t* tot, int64_t n, unsigned* tickets, unsigned* err,
-                              const float* P, int n_comp, const float* Pg, int n_gate,
-                              hipStream_t s);
-// Compressors and noisegates share one workspace family ("dynamics"): rows [0, n_comp) belong to
-// the compressors, [n_comp, n_comp + n_gate) to the noisegates; ws_off is the family row of the
-// launch's type (0 or n_comp) and `gate` selects the noisegate curve.
+// Before a pass, in one launch: published totals reset, the rows' tickets and coefficients written
+// (dynamics rows: n compressors of P, then n_gate noisegates of Pg), the error word cleared if
+// given, and exp(p) of the EQ nodes formed in their rows of H (eq_P [n_eq][1024], forward).
+struct PrepareJobs {
+  struct Dyn {
+    uint64_t* tot;
+    int64_t n_tot;
+    unsigned* tickets;
+    const float* P;
+    int n;
+    const float* Pg;
+    int n_gate;
+  };
+  Dyn comp{}, ar{};
+  unsigned* err = nullptr;
+  const float* eq_P = nullptr;
+  int n_eq = 0;
+  float* eq_H = nullptr;
+};
+hipError_t launch_prepare(const PrepareJobs& jobs, hipStream_t s);
 hipError_t launch_comp_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int ws_off,
                            bool gate, uint64_t* agg, double* carry, unsigned* ticket,
                            unsigned* err, hipStream_t s);

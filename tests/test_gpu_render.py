@@ -121,6 +121,37 @@ def test_pointwise_odd_lengths(T):
         assert e <= GRAD_TOL, (k, e)
 
 
+@pytest.mark.parametrize("n", [1, 16, 17, 33])
+def test_eq_node_counts(n):
+    """EQ designs and parameter gradients around the 16 nodes that one block of the design products
+    takes, forward and adjoint against the oracle (the usual tolerances), and to the bit against
+    each node rendered alone."""
+    T = 2048 + 77
+    say(f"[eq nodes] n={n}")
+    b = synth.GraphBuilder()
+    for _ in range(n):
+        i, e, o = b.add(synth.IN), b.add(synth.EQ), b.add(synth.OUT)
+        b.connect(i, e)
+        b.connect(e, o)
+    g = b.build()
+    w = synth.Workload("eqs", g, synth.make_sources(synth.rng_for(n, 1), n, T),
+                       synth.draw_params(synth.rng_for(n, 2), g), None, T, n)
+    sched = Schedule(g.node_type, g.edges)
+    S, P = device_inputs(w)
+    Y, U = render(sched, S, P, return_U=True)
+    torch.cuda.synchronize()
+    check_render(w, sched, Y, U)
+    for k, e in run_backward(w, n).items():
+        assert e <= GRAD_TOL, (k, e)
+    one = synth.GraphBuilder()
+    one.chain([synth.IN, synth.EQ, synth.OUT])
+    g1 = one.build()
+    s1 = Schedule(g1.node_type, g1.edges)
+    for k in {0, n // 2, n - 1}:
+        y = render(s1, S[k:k + 1].clone(), {synth.EQ: P[synth.EQ][k:k + 1].clone()})
+        assert torch.equal(y[0], Y[k]), k
+
+
 # ---- adjoint -------------------------------------------------------------------------------
 
 
