@@ -75,7 +75,7 @@ constexpr int kW1 = 8 * 9;
 __device__ __forceinline__ void load_twiddles512(Twiddles512& tw, float2* w1, int j) {
   w1[(j >> 3) * 9 + (j & 7)] = kTw4096[64 * (j >> 3) * (j & 7)];
 #pragma unroll
-  for (int r = 1; r < 8; ++r) tw.w2[r] = kTw4096[8 * r * j];
+  for (int r = 1; r < 8; ++r) tw.w2[r] = kTwRows512[64 * r + j];
   tw.w1 = w1 + (j & 7) * 9;
 }
 

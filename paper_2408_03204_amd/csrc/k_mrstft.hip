@@ -59,6 +59,20 @@ __device__ __forceinline__ float2 twid(int q) {
   return INV ? make_float2(w.x, -w.y) : w;
 }
 
+// exp(-+2 pi i r j / N), j < N / R for the radix R of the table's rows (16 for N = 256, else 8): read by
+// neighbouring lanes from one line. The scattered reads of the plain table bounded the passes below
+// (2^18 samples: statistics 27 -> 22 us, gradient 36 -> 28 us; the window likewise has a table).
+template <int N, bool INV>
+__device__ __forceinline__ float2 twid_row(int r, int j) {
+  const float2 w = N == 64     ? kTwRows64[8 * r + j]
+                   : N == 128  ? kTwRows128[16 * r + j]
+                   : N == 256  ? kTwRows256[16 * r + j]
+                   : N == 512  ? kTwRows512[64 * r + j]
+                   : N == 1024 ? kTwRows1024[128 * r + j]
+                               : kTwRows2048[256 * r + j];
+  return INV ? make_float2(w.x, -w.y) : w;
+}
+
 __device__ __forceinline__ constexpr int lpad(int i) { return i + (i >> 4); }
 
 // LDS accesses of one wave are executed in order; this keeps the compiler from moving them across
@@ -110,6 +124,7 @@ template <int N, bool INV>
 __device__ __forceinline__ void group_fft(float2 (&v)[N / Grp<N>::G], float2* s, int j) {
   constexpr int G = Grp<N>::G, P = N / G, R1 = Grp<N>::R1, R2 = G / R1;
   static_assert(P % R1 == 0 && P % R2 == 0, "radices must divide the points per thread");
+  static_assert(R2 == 8 && R1 == (R1 * P == 256 ? 16 : 8), "radices of the twiddle rows");
   dft_p<P, INV>(v);
 #pragma unroll
   for (int r = 0; r < P; ++r) s[lpad(P * j + r)] = v[r];
@@ -123,7 +138,7 @@ __device__ __forceinline__ void group_fft(float2 (&v)[N / Grp<N>::G], float2* s,
     const int k = j % P;
     float2 w[R1];
 #pragma unroll
-    for (int r = 1; r < R1; ++r) w[r] = twid<N, INV>(r * k * (N / (R1 * P)));
+    for (int r = 1; r < R1; ++r) w[r] = twid_row<R1 * P, INV>(r, k);
 #pragma unroll
     for (int h = 0; h < P / R1; ++h) {
       float2* u = v + R1 * h;
@@ -149,7 +164,7 @@ __device__ __forceinline__ void group_fft(float2 (&v)[N / Grp<N>::G], float2* s,
       float2* u = v + R2 * h;
       const int b = j + G * h;
 #pragma unroll
-      for (int r = 1; r < R2; ++r) u[r] = cmul(u[r], twid<N, INV>(r * b));
+      for (int r = 1; r < R2; ++r) u[r] = cmul(u[r], twid_row<N, INV>(r, b));
       dft_r<R2, INV>(u);
 #pragma unroll
       for (int r = 0; r < R2; ++r) o[h + (P / R2) * r] = u[r];  // X[j + G (h + (P/R2) r)]
@@ -161,7 +176,7 @@ __device__ __forceinline__ void group_fft(float2 (&v)[N / Grp<N>::G], float2* s,
 
 template <int N>
 __device__ __forceinline__ float hann(int n) {
-  return 0.5f - 0.5f * kTw4096[n * (4096 / N)].x;
+  return N == 512 ? kHann512[n] : N == 1024 ? kHann1024[n] : kHann2048[n];
 }
 
 // Forward transform of one windowed stereo frame (left + i right) by thread j of its group; the
