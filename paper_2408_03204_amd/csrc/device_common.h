@@ -48,6 +48,15 @@ __device__ __forceinline__ const float* adj_row(const GraphView& g, int d) {
                           : g.dU + (int64_t)d * 2 * g.T;
 }
 
+// A pointer that is the same in every lane, in scalar registers whatever the compiler can prove.
+template <typename T>
+__device__ __forceinline__ T* scalar_ptr(T* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)a);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32));
+  return reinterpret_cast<T*>(hi << 32 | lo);
+}
+
 // Raw buffer resource over n floats starting at p: loads through it take a 32-bit element
 // offset and return 0 outside [0, n) (the hardware range check), which implements the zero
 // padding of signal windows without branches. Requires n < 2^29.

@@ -208,15 +208,17 @@ __device__ __forceinline__ double await_total(uint64_t* slot, unsigned* err, int
 template <bool ADJ, bool RAGGED>
 __device__ __forceinline__ void stage(const GraphView& g, int node, int t0, float* sl, float* sr) {
   const int64_t T = g.T;
-  const int e0 = ADJ ? g.out_ptr[node] : g.in_ptr[node];
-  const int e1 = ADJ ? g.out_ptr[node + 1] : g.in_ptr[node + 1];
+  // the edges, their rows and lengths are the same in every lane: kept scalar, or a load would loop
+  // over the lanes' descriptors
+  const int e0 = __builtin_amdgcn_readfirstlane(ADJ ? g.out_ptr[node] : g.in_ptr[node]);
+  const int e1 = __builtin_amdgcn_readfirstlane(ADJ ? g.out_ptr[node + 1] : g.in_ptr[node + 1]);
   float l[kPer], r[kPer];
 #pragma unroll
   for (int q = 0; q < kPer; ++q) l[q] = r[q] = 0.f;
   for (int e = e0; e < e1; ++e) {  // all loads of a row issued before any is consumed
-    const int other = ADJ ? g.out_dst[e] : g.in_src[e];
+    const int other = __builtin_amdgcn_readfirstlane(ADJ ? g.out_dst[e] : g.in_src[e]);
     const float* row = ADJ ? adj_row(g, other) : out_row(g, other);
-    const int64_t L = RAGGED ? (int64_t)g.len[other] : T;
+    const int64_t L = RAGGED ? (int64_t)__builtin_amdgcn_readfirstlane(g.len[other]) : T;
     const auto rl = row_rsrc(row, L), rr = row_rsrc(row + T, L);
     float xl[kPer], xr[kPer];
 #pragma unroll
@@ -249,7 +251,9 @@ __device__ __forceinline__ double energy(const float* sl, const float* sr, int i
 // length Tn are dropped.
 __device__ __forceinline__ void store_chunk(float* row, int64_t T, int64_t Tn, int t0,
                                             const float* sl, const float* sr) {
-  const auto rl = row_rsrc(row, Tn), rr = row_rsrc(row + T, Tn);
+  const int n = __builtin_amdgcn_readfirstlane((int)Tn);
+  row = scalar_ptr(row);
+  const auto rl = row_rsrc(row, n), rr = row_rsrc(row + T, n);
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     // an opaque copy of the thread index keeps the compiler from holding the staging
