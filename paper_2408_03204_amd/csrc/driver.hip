@@ -241,19 +241,41 @@ GraphView dyn_view(const GraphView& g, int n_nodes) {
   return d;
 }
 
+bool is_pointwise(int t) {
+  return t == GRAFX_IN || t == GRAFX_OUT || t == GRAFX_MIX || t == GRAFX_GAIN_PAN ||
+         t == GRAFX_IMAGER || t == GRAFX_TANH;
+}
+
+// The chain of steps [n, n + count); dst and partials for the adjoint.
+PointwiseChain chain_of(const grafx_schedule_t* h, const float* const* P, void* ws,
+                        const WsLayout& L, int n, int count, float* dU, float* dS) {
+  PointwiseChain c;
+  c.n = count;
+  for (int i = 0; i < count; ++i) {
+    const int t = h->step_type[n + i];
+    const size_t part = t == GRAFX_GAIN_PAN ? L.part_gp : t == GRAFX_IMAGER ? L.part_im
+                                                                            : L.part_tanh;
+    c.link[i] = {t, h->step_ptr[n + i], P ? P[t] : nullptr, t == GRAFX_IN ? dS : dU,
+                 kParamCount[t] > 0 && dU ? at<double>(ws, part) : nullptr};
+  }
+  return c;
+}
+
+// Enqueues step n, or, if it heads a chain of at most `most` steps, the chain; `done` receives how
+// many steps that was.
 hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const float* const* P,
-                            float* U, void* ws, const WsLayout& L, int n, hipStream_t stream) {
+                            float* U, void* ws, const WsLayout& L, int n, int most, int* done,
+                            hipStream_t stream) {
   const int t = h->step_type[n];
   const int b = h->step_ptr[n], cnt = h->step_ptr[n + 1] - b;
+  *done = 1;
   if (cnt == 0) return hipSuccess;
-  const float* p = P ? P[t] : nullptr;
+  if (is_pointwise(t)) {
+    while (*done < most && n + *done <= h->N && h->chained[n + *done - 1]) ++*done;
+    return launch_pointwise_fwd(chain_of(h, P, ws, L, n, *done, nullptr, nullptr), g, U, cnt,
+                                stream);
+  }
   switch (t) {
-    case GRAFX_MIX:
-    case GRAFX_OUT:
-    case GRAFX_GAIN_PAN:
-    case GRAFX_IMAGER:
-    case GRAFX_TANH:
-      return launch_pointwise_fwd(t, g, U, p, b, cnt, stream);
     case GRAFX_EQ:
       return launch_eq_fwd(g, U, at<float>(ws, L.eq_H), b, cnt, stream);
     case GRAFX_COMPRESSOR:
@@ -284,21 +306,20 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
   }
 }
 
+// The adjoint of step n, or of a chain that ends with it (down to the input step if dS is given).
 hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const float* const* P,
-                            float* dU, void* ws, const WsLayout& L, int n, hipStream_t stream) {
+                            float* dU, float* dS, void* ws, const WsLayout& L, int n, int most,
+                            int* done, hipStream_t stream) {
   const int t = h->step_type[n];
   const int b = h->step_ptr[n], cnt = h->step_ptr[n + 1] - b;
+  *done = 1;
   if (cnt == 0) return hipSuccess;
-  const float* p = P ? P[t] : nullptr;
+  if (is_pointwise(t)) {
+    while (*done < most && n - *done >= (dS ? 0 : 1) && h->chained[n - *done]) ++*done;
+    return launch_pointwise_bwd(chain_of(h, P, ws, L, n - *done + 1, *done, dU, dS), g, cnt,
+                                stream);
+  }
   switch (t) {
-    case GRAFX_MIX:
-      return launch_pointwise_bwd(t, g, dU, nullptr, b, cnt, nullptr, stream);
-    case GRAFX_GAIN_PAN:
-      return launch_pointwise_bwd(t, g, dU, p, b, cnt, at<double>(ws, L.part_gp), stream);
-    case GRAFX_IMAGER:
-      return launch_pointwise_bwd(t, g, dU, p, b, cnt, at<double>(ws, L.part_im), stream);
-    case GRAFX_TANH:
-      return launch_pointwise_bwd(t, g, dU, p, b, cnt, at<double>(ws, L.part_tanh), stream);
     case GRAFX_EQ:
       return launch_eq_bwd(g, dU, at<float>(ws, L.eq_H), b, cnt, at<float>(ws, L.eq_C), stream);
     case GRAFX_COMPRESSOR:
@@ -369,8 +390,8 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,
                          at<double2>(ws, L.rv_Un), at<float>(ws, L.rv_h), at<float4>(ws, L.rv_H),
                          stream);
-  for (int n = 1; n <= h->N && e == hipSuccess; ++n)
-    e = enqueue_fwd_step(h, g, P, U, ws, L, n, stream);
+  for (int n = 1, done = 0; n <= h->N && e == hipSuccess; n += done)
+    e = enqueue_fwd_step(h, g, P, U, ws, L, n, PointwiseChain::kMax, &done, stream);
   return hip_status(e, "render launch");
 }
 
@@ -478,10 +499,9 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
   auto dpar = [&](int t) -> float* { return dP ? dP[t] : nullptr; };
   hipError_t e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
-  for (int n = h->N - 1; n >= 1 && e == hipSuccess; --n)
-    e = enqueue_bwd_step(h, g, P, dU, ws, L, n, stream);
-  if (e == hipSuccess && dS && h->K > 0)  // adjoint of the input step: sum over output edges
-    e = launch_pointwise_bwd(GRAFX_IN, g, dS, nullptr, 0, h->K, nullptr, stream);
+  // the input step (its adjoint: the sum over output edges) only if dS is asked for
+  for (int n = h->N - 1, done = 0; n >= (dS ? 0 : 1) && e == hipSuccess; n -= done)
+    e = enqueue_bwd_step(h, g, P, dU, dS, ws, L, n, PointwiseChain::kMax, &done, stream);
   const int tiles = pointwise_tiles(T, h->pw_unroll), chunks = comp_chunks(T);
   ReduceJobs jobs;
   if (dpar(GRAFX_GAIN_PAN))
@@ -537,7 +557,8 @@ grafx_status grafx_render_step(const grafx_schedule_t* h, const void* dev_plan, 
   const GraphView g = make_view(h, dev_plan, T, S, U);
   hipError_t e = hipSuccess;
   if (is_dynamics(h->step_type[step])) e = launch_prepare(dyn_jobs(h, P, ws, L, false, T), stream);
-  if (e == hipSuccess) e = enqueue_fwd_step(h, g, P, U, ws, L, step, stream);
+  int done = 0;
+  if (e == hipSuccess) e = enqueue_fwd_step(h, g, P, U, ws, L, step, 1, &done, stream);
   return hip_status(e, "render_step launch");
 }
 
@@ -556,7 +577,9 @@ grafx_status grafx_render_backward_step(const grafx_schedule_t* h, const void* d
   g.dU = dU;
   hipError_t e = hipSuccess;
   if (is_dynamics(h->step_type[step])) e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
-  if (e == hipSuccess) e = enqueue_bwd_step(h, g, P, dU, ws, L, step, stream);
+  int done = 0;
+  if (e == hipSuccess)
+    e = enqueue_bwd_step(h, g, P, dU, nullptr, ws, L, step, 1, &done, stream);
   return hip_status(e, "render_backward_step launch");
 }
 

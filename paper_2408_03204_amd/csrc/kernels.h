@@ -13,11 +13,22 @@ struct GraphView;
 // ---- pointwise family: mix / out / gain_pan / imager / tanh (k_pointwise.hip) --------------
 // blocks per node along time (partials per node) when every thread covers `unroll` float4 groups
 int pointwise_tiles(int64_t T, int unroll = 1);
-hipError_t launch_pointwise_fwd(int type, const GraphView& g, float* U, const float* P,
-                                int node_begin, int n_nodes, hipStream_t s);
-// dst: dU (or dS for the input step); part: double [slots][tiles][NP] (NP = 2, 1, 1, 0)
-hipError_t launch_pointwise_bwd(int type, const GraphView& g, float* dst, const float* P,
-                                int node_begin, int n_nodes, double* part, hipStream_t s);
+// A chain of pointwise steps (grafx_schedule_t::chained), node i of each link feeding node i of the
+// next. dst (adjoint): dU, or dS for the input step; part: double [slots][tiles][NP] (NP = 2, 1, 1, 0).
+struct PointwiseChain {
+  static constexpr int kMax = 4;
+  struct Link {
+    int type, node_begin;
+    const float* P;
+    float* dst;
+    double* part;
+  } link[kMax];
+  int n = 0;
+};
+hipError_t launch_pointwise_fwd(const PointwiseChain& c, const GraphView& g, float* U, int n_nodes,
+                                hipStream_t s);
+hipError_t launch_pointwise_bwd(const PointwiseChain& c, const GraphView& g, int n_nodes,
+                                hipStream_t s);
 // Fixed-order sums of per-tile parameter-gradient partials, several parameter types in one
 // launch: job q reduces part[q] [slots][tiles][np] (double) into dP[q] [slots][np] (float).
 struct ReduceJobs {

@@ -470,6 +470,21 @@ grafx_status grafx_schedule(int32_t num_nodes, const int32_t* node_type, int32_t
     h->param_row.resize(V);
     for (int i = 0; i < V; ++i) h->param_row[i] = row_of[h->perm[i]];
   }
+  auto pointwise = [](int t) {
+    return t == GRAFX_MIX || t == GRAFX_OUT || t == GRAFX_GAIN_PAN || t == GRAFX_IMAGER ||
+           t == GRAFX_TANH;
+  };
+  h->chained.assign(h->N, 0);
+  for (int n = 0; n < h->N; ++n) {
+    const int a = h->step_ptr[n], b = h->step_ptr[n + 1], cnt = b - a;
+    bool ok = cnt > 0 && h->step_ptr[n + 2] - b == cnt && pointwise(h->step_type[n + 1]) &&
+              (n == 0 || pointwise(h->step_type[n]));
+    for (int i = 0; i < cnt && ok; ++i)
+      ok = h->out_ptr[a + i + 1] - h->out_ptr[a + i] == 1 &&
+           h->in_ptr[b + i + 1] - h->in_ptr[b + i] == 1 &&
+           h->out_dst[h->out_ptr[a + i]] == b + i;
+    h->chained[n] = ok;
+  }
   build_plan(h);
   *out = h;
   return GRAFX_OK;

@@ -8,7 +8,7 @@ import torch
 import synth
 from gpu_common import (GRAD_TOL, check_render, device_inputs, grad_err, oracle_grads,
                         rel_err, say)
-from paper_2408_03204_amd import Schedule, render
+from paper_2408_03204_amd import RenderBuffers, Schedule, render
 
 pytestmark = pytest.mark.gpu
 
@@ -221,3 +221,51 @@ def test_compressor_alpha_edge_values(a):
     say("   grad errs", errs)
     for k, e in errs.items():
         assert e <= GRAD_TOL, (k, e)
+
+
+@pytest.mark.parametrize("unroll", [1, 2, 4])
+@pytest.mark.parametrize("T", [3, 1025, 2 * 4096 + 4])
+def test_pointwise_chains(T, unroll):
+    """Runs of pointwise steps whose nodes form paths are one launch, up to four steps at a time:
+    paths of five nodes (a tanh first, so the adjoint needs the sources; another inside), then a
+    mix -> gain -> out path. Output rows and input adjoints equal the single steps' to the bit;
+    everything equals the oracle to the usual tolerances."""
+    say(f"[pointwise chains] T={T} unroll={unroll}")
+    b = synth.GraphBuilder()
+    ends = []
+    for _ in range(3):
+        ends.append(b.chain([synth.IN, synth.TANH, synth.GAIN_PAN, synth.IMAGER, synth.TANH,
+                             synth.GAIN_PAN])[1])
+    a, _ = b.chain([synth.MIX, synth.GAIN_PAN, synth.OUT])
+    for v in ends:
+        b.connect(v, a)
+    g = b.build()
+    S = synth.make_sources(synth.rng_for(3, 1), 3, T)
+    S[0, :, ::3] = -0.0
+    w = synth.Workload("chains", g, S, synth.draw_params(synth.rng_for(3, 2), g), None, T, 3)
+    sched = Schedule(g.node_type, g.edges)
+    sched.set_tuning(Schedule.TUNE_POINTWISE_UNROLL, unroll)
+    Sd, P = device_inputs(w)
+    buf = RenderBuffers(sched, T, "cuda")
+    dY = torch.as_tensor(np.random.default_rng(4).normal(size=tuple(buf.Y.shape))
+                         .astype(np.float32)).cuda()
+    dS, dP = torch.empty_like(Sd), {t: torch.empty_like(p) for t, p in P.items()}
+    buf.U.fill_(7.0)
+    buf.dU.fill_(7.0)
+    buf.forward(Sd, P)
+    buf.backward(Sd, P, dY, dP, dS)
+    U, dU = buf.U.clone(), buf.dU.clone()
+    buf.U.fill_(7.0)
+    buf.dU.fill_(7.0)
+    for n in range(1, sched.num_steps + 1):
+        buf.step(Sd, P, n)
+    for n in range(sched.num_steps - 1, 0, -1):
+        buf.backward_step(Sd, P, dY, n)
+    torch.cuda.synchronize()
+    assert torch.equal(U.view(torch.int32), buf.U.view(torch.int32))
+    assert torch.equal(dU.view(torch.int32), buf.dU.view(torch.int32))
+    check_render(w, sched, U[sched.out_begin:], U)
+    ref = oracle_grads(w, dY.cpu().numpy())
+    assert grad_err(dS.cpu().numpy(), ref["S"]) <= GRAD_TOL
+    for t, p in dP.items():
+        assert grad_err(p.cpu().numpy(), ref[t]) <= GRAD_TOL, t
