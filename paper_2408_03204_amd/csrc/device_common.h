@@ -21,6 +21,8 @@ struct GraphView {
   const float* U;            // [V][2][T] node outputs (rows >= K)
   const float* dY;           // [n_out][2][T] output adjoint
   const float* dU;           // [V][2][T] input adjoints (rows of processed nodes)
+  float* dS;                 // [K][2][T] adjoint of the sources where their consumers' kernels store
+                             // it (every source feeds one processor with no other input), else null
   const int32_t* len;        // [V] per-node signal length, or null when every node has length T
   int64_t T;                 // row stride (and the length of every node when len is null)
   int32_t K;                 // number of input nodes (= sigma positions [0, K))
@@ -55,6 +57,20 @@ __device__ __forceinline__ T* scalar_ptr(T* p) {
   const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)a);
   const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32));
   return reinterpret_cast<T*>(hi << 32 | lo);
+}
+
+// The adjoint row of the source that is node v's input, or null if its input is none or v's kernel
+// does not store it. Where every source feeds one processor that has no other input, its adjoint is
+// that processor's input adjoint, so the processor's kernel stores it twice instead of an input step
+// reading it back (48 EQ -> compressor strips of 2^18 samples: 403 -> 383 us). Where only some do (a
+// batch of consoles), the stores cost their kernels what they save the input step, which is launched
+// anyway (2.00 ms as a step, 2.01 ms stored by the consumers).
+__device__ __forceinline__ float* source_row(const GraphView& g, int v) {
+  if (!g.dS) return nullptr;
+  const int e = __builtin_amdgcn_readfirstlane(g.in_ptr[v]);
+  if (__builtin_amdgcn_readfirstlane(g.in_ptr[v + 1]) == e) return nullptr;
+  const int k = __builtin_amdgcn_readfirstlane(g.in_src[e]);
+  return k < g.K ? g.dS + (int64_t)k * 2 * g.T : nullptr;
 }
 
 // Raw buffer resource over n floats starting at p: loads through it take a 32-bit element

@@ -246,17 +246,18 @@ bool is_pointwise(int t) {
          t == GRAFX_IMAGER || t == GRAFX_TANH;
 }
 
-// The chain of steps [n, n + count); dst and partials for the adjoint.
+// The chain of steps [n, n + count); dst (and with it the partials) for the adjoint.
 PointwiseChain chain_of(const grafx_schedule_t* h, const float* const* P, void* ws,
-                        const WsLayout& L, int n, int count, float* dU, float* dS) {
+                        const WsLayout& L, int n, int count, float* dst) {
   PointwiseChain c;
   c.n = count;
+  c.dst = dst;
   for (int i = 0; i < count; ++i) {
     const int t = h->step_type[n + i];
     const size_t part = t == GRAFX_GAIN_PAN ? L.part_gp : t == GRAFX_IMAGER ? L.part_im
                                                                             : L.part_tanh;
-    c.link[i] = {t, h->step_ptr[n + i], P ? P[t] : nullptr, t == GRAFX_IN ? dS : dU,
-                 kParamCount[t] > 0 && dU ? at<double>(ws, part) : nullptr};
+    c.link[i] = {t, h->step_ptr[n + i], P ? P[t] : nullptr,
+                 kParamCount[t] > 0 && dst ? at<double>(ws, part) : nullptr};
   }
   return c;
 }
@@ -272,7 +273,7 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
   if (cnt == 0) return hipSuccess;
   if (is_pointwise(t)) {
     while (*done < most && n + *done <= h->N && h->chained[n + *done - 1]) ++*done;
-    return launch_pointwise_fwd(chain_of(h, P, ws, L, n, *done, nullptr, nullptr), g, U, cnt,
+    return launch_pointwise_fwd(chain_of(h, P, ws, L, n, *done, nullptr), g, U, cnt,
                                 stream);
   }
   switch (t) {
@@ -306,18 +307,17 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
   }
 }
 
-// The adjoint of step n, or of a chain that ends with it (down to the input step if dS is given).
+// The adjoint of step n, or of a chain that ends with it.
 hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const float* const* P,
-                            float* dU, float* dS, void* ws, const WsLayout& L, int n, int most,
-                            int* done, hipStream_t stream) {
+                            float* dU, void* ws, const WsLayout& L, int n, int most, int* done,
+                            hipStream_t stream) {
   const int t = h->step_type[n];
   const int b = h->step_ptr[n], cnt = h->step_ptr[n + 1] - b;
   *done = 1;
   if (cnt == 0) return hipSuccess;
   if (is_pointwise(t)) {
-    while (*done < most && n - *done >= (dS ? 0 : 1) && h->chained[n - *done]) ++*done;
-    return launch_pointwise_bwd(chain_of(h, P, ws, L, n - *done + 1, *done, dU, dS), g, cnt,
-                                stream);
+    while (*done < most && n - *done >= 1 && h->chained[n - *done]) ++*done;
+    return launch_pointwise_bwd(chain_of(h, P, ws, L, n - *done + 1, *done, dU), g, cnt, stream);
   }
   switch (t) {
     case GRAFX_EQ:
@@ -499,9 +499,12 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
   auto dpar = [&](int t) -> float* { return dP ? dP[t] : nullptr; };
   hipError_t e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
-  // the input step (its adjoint: the sum over output edges) only if dS is asked for
-  for (int n = h->N - 1, done = 0; n >= (dS ? 0 : 1) && e == hipSuccess; n -= done)
-    e = enqueue_bwd_step(h, g, P, dU, dS, ws, L, n, PointwiseChain::kMax, &done, stream);
+  if (h->lone_inputs) g.dS = dS;
+  for (int n = h->N - 1, done = 0; n >= 1 && e == hipSuccess; n -= done)
+    e = enqueue_bwd_step(h, g, P, dU, ws, L, n, PointwiseChain::kMax, &done, stream);
+  if (e == hipSuccess && dS && h->K > 0 && !h->lone_inputs)
+    // adjoint of the input step: the sum over output edges
+    e = launch_pointwise_bwd(chain_of(h, P, ws, L, 0, 1, dS), g, h->K, stream);
   const int tiles = pointwise_tiles(T, h->pw_unroll), chunks = comp_chunks(T);
   ReduceJobs jobs;
   if (dpar(GRAFX_GAIN_PAN))
@@ -579,7 +582,7 @@ grafx_status grafx_render_backward_step(const grafx_schedule_t* h, const void* d
   if (is_dynamics(h->step_type[step])) e = launch_prepare(dyn_jobs(h, P, ws, L, true, T), stream);
   int done = 0;
   if (e == hipSuccess)
-    e = enqueue_bwd_step(h, g, P, dU, nullptr, ws, L, step, 1, &done, stream);
+    e = enqueue_bwd_step(h, g, P, dU, ws, L, step, 1, &done, stream);
   return hip_status(e, "render_backward_step launch");
 }
 

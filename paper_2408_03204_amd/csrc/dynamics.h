@@ -248,7 +248,8 @@ __device__ __forceinline__ double energy(const float* sl, const float* sr, int i
 }
 
 // Chunk store (from the padded layout) into a row of stride T; samples at or beyond the node's
-// length Tn are dropped.
+// length Tn are dropped. SUM: as the sum over one consumer (a zero's sign).
+template <bool SUM = false>
 __device__ __forceinline__ void store_chunk(float* row, int64_t T, int64_t Tn, int t0,
                                             const float* sl, const float* sr) {
   const int n = __builtin_amdgcn_readfirstlane((int)Tn);
@@ -261,8 +262,9 @@ __device__ __forceinline__ void store_chunk(float* row, int64_t T, int64_t Tn, i
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int idx = tid + kBlock * q;
-    bstore_nt(rl, t0 + idx, sl[lpos(idx)]);
-    bstore_nt(rr, t0 + idx, sr[lpos(idx)]);
+    const float l = sl[lpos(idx)], r = sr[lpos(idx)];
+    bstore_nt(rl, t0 + idx, SUM ? 0.f + l : l);
+    bstore_nt(rr, t0 + idx, SUM ? 0.f + r : r);
   }
 }
 

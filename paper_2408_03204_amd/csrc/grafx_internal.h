@@ -44,9 +44,10 @@ struct grafx_schedule_t {
   std::vector<int32_t> out_ptr;    // [V+1]
   std::vector<int32_t> out_dst;    // [E]
   std::vector<int32_t> param_row;  // [V]
-  // [N] whether steps n and n + 1 chain: both pointwise (or step n the inputs) with as many nodes, the
-  // i-th of step n feeding only the i-th of step n + 1, which has no other input
+  // [N] whether steps n and n + 1 chain: both pointwise with as many nodes, the i-th of step n feeding
+  // only the i-th of step n + 1, which has no other input
   std::vector<uint8_t> chained;
+  bool lone_inputs = false;  // every source feeds one processor that has no other input
   std::vector<int32_t> node_len;   // [V] per-node signal length (sigma order); empty = all T
   int32_t max_len = 0;             // largest node length (0 when uniform)
   int32_t pw_unroll = 1;           // tuning: pointwise 1024-sample parts per block

@@ -311,6 +311,7 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
   sums[3] = wave_total(accA);
   __syncthreads();
   store_chunk(dU + (int64_t)node * 2 * g.T, g.T, Tn, t0, yl, yr);
+  if (float* ds = source_row(g, node)) store_chunk<true>(ds, g.T, Tn, t0, yl, yr);
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
     for (int i = 0; i < 4; ++i) red[4 * i + (threadIdx.x >> 6)] = sums[i];

@@ -380,6 +380,7 @@ __global__ __launch_bounds__(kBlock, 3) void comp_ar_bwd_kernel(
     p[4] = -(double)k.cv.kR * sums[4];
   }
   store_chunk(dU + (int64_t)node * 2 * g.T, g.T, Tn, t0, yl, yr);
+  if (float* ds = source_row(g, node)) store_chunk<true>(ds, g.T, Tn, t0, yl, yr);
 }
 
 }  // namespace

@@ -235,9 +235,8 @@ __device__ __forceinline__ void load_window(const GraphView& g, int e0, int e1, 
   }
 }
 
-__device__ __forceinline__ void store_tile(const GraphView& g, float* out, int node, int Tn, int t0,
-                                           int j, const float2 (&v)[8]) {
-  float* y = out + (int64_t)node * 2 * g.T;
+__device__ __forceinline__ void store_tile(const GraphView& g, float* y, int Tn, int t0, int j,
+                                           const float2 (&v)[8]) {
   // a tile's outputs are elements 19 .. 492 of the transform, those past Tn are dropped
   const int n = min(kHop, Tn - t0);
   const auto yl = row_rsrc(y + t0, n), yr = row_rsrc(y + g.T + t0, n);
@@ -328,7 +327,7 @@ __global__ __launch_bounds__(kBlock, 4) void delay_fwd_kernel(GraphView g, float
   }
   join(acc, z, s, j);
   fft512<true>(z, s, tw, j);
-  store_tile(g, U, node, Tn, t0, j, z);
+  store_tile(g, U + (int64_t)node * 2 * g.T, Tn, t0, j, z);
 }
 
 // ---- adjoint -----------------------------------------------------------------------------------
@@ -422,7 +421,12 @@ __global__ __launch_bounds__(kBlock, 2) void delay_bwd_kernel(GraphView g, float
       if (!mine) continue;
     }
     fft512<true>(z, s, tw, j);
-    store_tile(g, dU, node, Tn, t0, j, z);
+    store_tile(g, dU + (int64_t)node * 2 * g.T, Tn, t0, j, z);
+    if (float* ds = source_row(g, node)) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) z[r] = make_float2(0.f + z[r].x, 0.f + z[r].y);
+      store_tile(g, ds, Tn, t0, j, z);
+    }
   }
   // lags of the even parts of the correlations (zeros for a group past the node's end)
   float* out = part + ((int64_t)slot * groups + group) * delay_lags(M);

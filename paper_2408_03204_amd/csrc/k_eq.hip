@@ -191,6 +191,15 @@ __global__ __launch_bounds__(kBlock) void eq_bwd_kernel(GraphView g, float* dU, 
       bstore_nt(dl, t, v[r].x);
       bstore_nt(dr, t, v[r].y);
     }
+    if (float* ds = source_row(g, node)) {
+      const auto sl = row_rsrc(ds, Tn), sr = row_rsrc(ds + T, Tn);
+#pragma unroll
+      for (int r = 4; r < 12; ++r) {
+        const int t = t0 + j + 256 * (r - 4);
+        bstore_nt(sl, t, 0.f + v[r].x);
+        bstore_nt(sr, t, 0.f + v[r].y);
+      }
+    }
   }
   gather_window<false>(g, node, t0 - kN / 4, v, 4, 12);  // input tile, zero-padded
   fft4096<false, 0x0FF0u>(v, lds, tw);

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kBlock) void pointwise_fwd_kernel(GraphView g, floa
     fwd_tile<TYPE, true, false, UN, kMax>(g, U, c, i, Tn, base);
 }
 
-// Adjoint of a chain. A link's dst receives its input adjoint (dU, or dS for the input step, whose
+// Adjoint of a chain. dst receives the links' input adjoints (dU, or dS for the input step, whose
 // rows are indexed the same way). Parameter-gradient partials (one per block and parameter, double)
 // go to the link's part[(slot * tiles + tile) * NP + j].
 template <bool V4>
@@ -299,6 +299,7 @@ __device__ __forceinline__ void bwd_tile(const GraphView& g, const PointwiseChai
   const int last = c.link[c.n - 1].node_begin + i, first = c.link[0].node_begin + i;
   const int o0 = g.out_ptr[last], o1 = g.out_ptr[last + 1];
   const int i0 = g.in_ptr[first], i1 = g.in_ptr[first + 1];
+  float* const ds = first >= g.K ? source_row(g, first) : nullptr;
   // Thread j covers samples base + kTile u + 4j .. + 3 (u < UN) in both paths, in the same order,
   // so the gradient partials are accumulated identically whichever path a launch takes. Blocks
   // past the node's length still write their (zero) partials.
@@ -371,9 +372,18 @@ __device__ __forceinline__ void bwd_tile(const GraphView& g, const PointwiseChai
         } else {
           adj_op(type, yl[n], yr[n], gl, gr, k[n], acc[n]);
         }
-        float* d = c.link[n].dst + (int64_t)(c.link[n].node_begin + i) * 2 * T;
+        float* d = c.dst + (int64_t)(c.link[n].node_begin + i) * 2 * T;
         store_n<V4>(d + t, gl);
         store_n<V4>(d + T + t, gr);
+        if (n == 0 && ds) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            gl[v] = 0.f + stored(gl[v]);
+            gr[v] = 0.f + stored(gr[v]);
+          }
+          store_n<V4>(ds + t, gl);
+          store_n<V4>(ds + T + t, gr);
+        }
       }
     }
   }

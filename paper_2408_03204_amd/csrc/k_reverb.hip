@@ -526,6 +526,7 @@ __global__ __launch_bounds__(kBlock) void rv_inverse_kernel(GraphView g, float* 
   pack_spectrum(al, ar, lds, v);
   fft4096<true>(v, lds, tw);
   float* y = out + (int64_t)node * 2 * T;
+  float* ds = CORR ? source_row(g, node) : nullptr;
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const int64_t t = (int64_t)kB * b + j + 256 * r;
@@ -533,6 +534,10 @@ __global__ __launch_bounds__(kBlock) void rv_inverse_kernel(GraphView g, float* 
       const float2 o = v[CORR ? r : r + 8];
       store_nt(y + t, o.x);
       store_nt(y + T + t, o.y);
+      if (CORR && ds) {
+        store_nt(ds + t, 0.f + o.x);
+        store_nt(ds + T + t, 0.f + o.y);
+      }
     }
   }
 }

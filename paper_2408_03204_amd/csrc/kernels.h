@@ -14,16 +14,16 @@ struct GraphView;
 // blocks per node along time (partials per node) when every thread covers `unroll` float4 groups
 int pointwise_tiles(int64_t T, int unroll = 1);
 // A chain of pointwise steps (grafx_schedule_t::chained), node i of each link feeding node i of the
-// next. dst (adjoint): dU, or dS for the input step; part: double [slots][tiles][NP] (NP = 2, 1, 1, 0).
+// next. part: double [slots][tiles][NP] (NP = 2, 1, 1, 0); dst (adjoint): dU, or dS for the input step.
 struct PointwiseChain {
   static constexpr int kMax = 4;
   struct Link {
     int type, node_begin;
     const float* P;
-    float* dst;
     double* part;
   } link[kMax];
   int n = 0;
+  float* dst = nullptr;
 };
 hipError_t launch_pointwise_fwd(const PointwiseChain& c, const GraphView& g, float* U, int n_nodes,
                                 hipStream_t s);

@@ -475,15 +475,22 @@ grafx_status grafx_schedule(int32_t num_nodes, const int32_t* node_type, int32_t
            t == GRAFX_TANH;
   };
   h->chained.assign(h->N, 0);
-  for (int n = 0; n < h->N; ++n) {
+  for (int n = 1; n < h->N; ++n) {
     const int a = h->step_ptr[n], b = h->step_ptr[n + 1], cnt = b - a;
-    bool ok = cnt > 0 && h->step_ptr[n + 2] - b == cnt && pointwise(h->step_type[n + 1]) &&
-              (n == 0 || pointwise(h->step_type[n]));
+    bool ok = cnt > 0 && h->step_ptr[n + 2] - b == cnt && pointwise(h->step_type[n]) &&
+              pointwise(h->step_type[n + 1]);
     for (int i = 0; i < cnt && ok; ++i)
       ok = h->out_ptr[a + i + 1] - h->out_ptr[a + i] == 1 &&
            h->in_ptr[b + i + 1] - h->in_ptr[b + i] == 1 &&
            h->out_dst[h->out_ptr[a + i]] == b + i;
     h->chained[n] = ok;
+  }
+  h->lone_inputs = true;
+  for (int k = 0; k < h->K && h->lone_inputs; ++k) {
+    h->lone_inputs = h->out_ptr[k + 1] - h->out_ptr[k] == 1;
+    if (!h->lone_inputs) break;
+    const int v = h->out_dst[h->out_ptr[k]];
+    h->lone_inputs = v < h->step_ptr[h->N] && h->in_ptr[v + 1] - h->in_ptr[v] == 1;
   }
   build_plan(h);
   *out = h;

@@ -269,3 +269,45 @@ def test_pointwise_chains(T, unroll):
     assert grad_err(dS.cpu().numpy(), ref["S"]) <= GRAD_TOL
     for t, p in dP.items():
         assert grad_err(p.cpu().numpy(), ref[t]) <= GRAD_TOL, t
+
+
+@pytest.mark.parametrize("lone", [True, False])
+@pytest.mark.parametrize("T", [777, 4096 + 1030])
+@pytest.mark.parametrize("t", sorted(set(range(2, 13))))
+def test_source_adjoints(t, T, lone):
+    """Where every source is one processor's only input, the processors' kernels store the source
+    adjoints, otherwise (several consumers, parallel edges, straight to an output, a consumer with
+    two inputs) the input step does: every row is the sum of its consumers' adjoint rows in edge
+    order, to the bit, for every node type."""
+    say(f"[source adjoints] type={t} T={T} lone={lone}")
+    b = synth.GraphBuilder()
+    ins = [b.add(synth.IN) for _ in range(3 if lone else 6)]
+    nodes = [b.add(t) for _ in range(3 if lone else 4)]
+    o = b.add(synth.OUT)
+    edges = [(0, 1), (1, 0), (2, 2)]
+    if not lone:
+        edges += [(2, 2), (3, 1), (4, None), (4, 0), (5, 3)]
+    for x, y in edges:
+        b.connect(ins[x], o if y is None else nodes[y])
+    for v in nodes:
+        b.connect(v, o)
+    g = b.build()
+    K = len(ins)
+    w = synth.Workload("sources", g, synth.make_sources(synth.rng_for(t, 1), K, T),
+                       synth.draw_params(synth.rng_for(t, 2), g), None, T, t)
+    sched = Schedule(g.node_type, g.edges)
+    S, P = device_inputs(w)
+    if t == synth.REVERB:
+        sched.set_reverb_noise(torch.rand((2, 3000), device="cuda") - 0.5)
+    buf = RenderBuffers(sched, T, "cuda")
+    dY = torch.as_tensor(np.random.default_rng(t).normal(size=tuple(buf.Y.shape))
+                         .astype(np.float32)).cuda()
+    dS = torch.full_like(S, 7.0)
+    buf.forward(S, P)
+    buf.backward(S, P, dY, {k: torch.empty_like(p) for k, p in P.items()}, dS)
+    torch.cuda.synchronize()
+    for k in range(K):
+        ref = torch.zeros_like(dS[k])
+        for v in sched.out_dst[sched.out_ptr[k]:sched.out_ptr[k + 1]]:
+            ref = ref + (dY[v - sched.out_begin] if v >= sched.out_begin else buf.dU[int(v)])
+        assert torch.equal(dS[k].view(torch.int32), ref.view(torch.int32)), k
