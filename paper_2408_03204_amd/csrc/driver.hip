@@ -521,11 +521,12 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   if (dpar(GRAFX_COMPRESSOR_AR))
     jobs.add(at<double>(ws, L.ar_part), h->type_count[GRAFX_COMPRESSOR_AR], chunks, kArParams,
              dpar(GRAFX_COMPRESSOR_AR));
-  if (e == hipSuccess) e = launch_reduce_partials(jobs, stream);
-  if (e == hipSuccess && dpar(GRAFX_EQ))
+  if (e == hipSuccess && !(dpar(GRAFX_EQ) && h->type_count[GRAFX_EQ] > 0))
+    e = launch_reduce_partials(jobs, stream);
+  else if (e == hipSuccess)
     e = launch_eq_grad(par(GRAFX_EQ), at<float>(ws, L.eq_C), eq_tiles(T),
                        at<float>(ws, L.eq_spec), h->type_count[GRAFX_EQ],
-                       at<double>(ws, L.eq_s), dpar(GRAFX_EQ), stream);
+                       at<double>(ws, L.eq_s), dpar(GRAFX_EQ), jobs, stream);
   for (int f = 0; f < 2; ++f) {
     const int t = kDelayType[f], M = kDelaySlots[f], n_del = h->type_count[t];
     if (e != hipSuccess || !dpar(t)) continue;

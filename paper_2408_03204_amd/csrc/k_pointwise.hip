@@ -24,6 +24,7 @@
 #include "device_common.h"
 #include "grafx_internal.h"
 #include "kernels.h"
+#include "reduce_partials.h"
 
 namespace grafx {
 namespace {
@@ -424,20 +425,8 @@ __global__ __launch_bounds__(kBlock) void pointwise_bwd_kernel(GraphView g, Poin
   }
 }
 
-// dP[slot][j] = sum over tiles of part[slot][tile][j], fixed order; one launch for every job of
-// the list, block b serving slot b of the concatenated slot ranges.
 __global__ __launch_bounds__(kBlock) void reduce_partials_kernel(ReduceJobs J) {
-  __shared__ double red[4];
-  int slot = blockIdx.x, q = 0;
-  while (q + 1 < J.n && slot >= J.slots[q]) slot -= J.slots[q++];  // uniform over the block
-  const double* part = J.part[q];
-  const int tiles = J.tiles[q], np = J.np[q];
-  for (int j = 0; j < np; ++j) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < tiles; i += kBlock) s += part[((int64_t)slot * tiles + i) * np + j];
-    s = block_sum<double>(s, red);
-    if (threadIdx.x == 0) J.dP[q][(int64_t)slot * np + j] = (float)s;
-  }
+  reduce_partials(J, blockIdx.x);
 }
 
 }  // namespace
@@ -513,10 +502,8 @@ hipError_t launch_pointwise_bwd(const PointwiseChain& c, const GraphView& g, int
 }
 
 hipError_t launch_reduce_partials(const ReduceJobs& jobs, hipStream_t s) {
-  int blocks = 0;
-  for (int q = 0; q < jobs.n; ++q) blocks += jobs.slots[q];
-  if (blocks <= 0) return hipSuccess;
-  reduce_partials_kernel<<<blocks, kBlock, 0, s>>>(jobs);
+  if (jobs.blocks() <= 0) return hipSuccess;
+  reduce_partials_kernel<<<jobs.blocks(), kBlock, 0, s>>>(jobs);
   return hipGetLastError();
 }
 

@@ -46,6 +46,11 @@ struct ReduceJobs {
     np[n] = n_par;
     ++n;
   }
+  int blocks() const {
+    int b = 0;
+    for (int q = 0; q < n; ++q) b += slots[q];
+    return b;
+  }
 };
 hipError_t launch_reduce_partials(const ReduceJobs& jobs, hipStream_t s);
 
@@ -66,8 +71,9 @@ hipError_t launch_eq_bwd(const GraphView& g, float* dU, const float* H, int node
 // After the last adjoint step: the tiles of Fpart summed per slot into F (float
 // [n_eq][kEqFoldStride]), then the FIR and parameter gradients; sbuf: double [n_eq][1024]
 // scratch; dP: float [n_eq][1024]
+// (its first launch also runs the reduction jobs of the other types)
 hipError_t launch_eq_grad(const float* P, const float* Fpart, int tiles, float* F, int n_eq,
-                          double* sbuf, float* dP, hipStream_t s);
+                          double* sbuf, float* dP, const ReduceJobs& jobs, hipStream_t s);
 
 // ---- compressor (k_comp.hip) ---------------------------------------------------------------
 constexpr int kCompChunk = 3072;  // 256 threads x 12 samples

@@ -8,7 +8,7 @@ import torch
 import synth
 from gpu_common import (GRAD_TOL, check_render, device_inputs, grad_err, oracle_grads,
                         rel_err, say)
-from paper_2408_03204_amd import RenderBuffers, Schedule, render
+from paper_2408_03204_amd import RenderBuffers, Schedule, merge_graphs, render
 
 pytestmark = pytest.mark.gpu
 
@@ -269,6 +269,45 @@ def test_pointwise_chains(T, unroll):
     assert grad_err(dS.cpu().numpy(), ref["S"]) <= GRAD_TOL
     for t, p in dP.items():
         assert grad_err(p.cpu().numpy(), ref[t]) <= GRAD_TOL, t
+
+
+@pytest.mark.parametrize("L", [5, 2048 * 3 + 1, 2048 * 32, 2048 * 32 + 1])
+def test_eq_gradients_alone_and_merged(L):
+    """An EQ's parameter gradient is the same bits whether its cross-spectra are summed by the
+    transform's launch (rows of up to 32 tiles) or by a launch of their own, as in a graph merged
+    with a longer one; a gain's reduction rides along in either."""
+    say(f"[eq gradients] L={L}")
+
+    def graph():
+        b = synth.GraphBuilder()
+        b.chain([synth.IN, synth.EQ, synth.GAIN_PAN, synth.OUT])
+        return b.build()
+
+    g, lens = graph(), [L, 2048 * 33 + 7]
+    m = merge_graphs([(g.node_type, g.edges, n) for n in lens])
+    rng = np.random.default_rng(L)
+    P = {synth.EQ: torch.as_tensor(rng.normal(0, 0.5, (2, 1024)).astype(np.float32)).cuda(),
+         synth.GAIN_PAN: torch.as_tensor(rng.normal(0, 0.5, (2, 2)).astype(np.float32)).cuda()}
+    S = torch.zeros((2, 2, m["T"]), device="cuda")
+    dY = torch.zeros_like(S)
+    for i, n in enumerate(lens):
+        S[i, :, :n] = torch.as_tensor(rng.normal(size=(2, n)).astype(np.float32))
+        dY[i, :, :n] = torch.as_tensor(rng.normal(size=(2, n)).astype(np.float32))
+    grads = []
+    for nodes, edges, lengths, T, rows in ((m["node_type"], m["edges"], m["lengths"], m["T"], 2),
+                                           (g.node_type, g.edges, None, L, 1)):
+        sched = Schedule(nodes, edges, lengths=lengths)
+        buf = RenderBuffers(sched, T, "cuda")
+        Pr = {t: p[:rows].clone() for t, p in P.items()}
+        dP = {t: torch.empty_like(p) for t, p in Pr.items()}
+        s = S[:rows, :, :T].clone(memory_format=torch.contiguous_format)
+        d = dY[:rows, :, :T].clone(memory_format=torch.contiguous_format)
+        buf.forward(s, Pr)
+        buf.backward(s, Pr, d, dP)
+        torch.cuda.synchronize()
+        grads.append({t: p[0] for t, p in dP.items()})
+    for t in P:
+        assert torch.equal(grads[0][t], grads[1][t]), t
 
 
 @pytest.mark.parametrize("lone", [True, False])
