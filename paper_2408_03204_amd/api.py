@@ -29,7 +29,11 @@ def _iptr(a):
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    """The current stream's handle (the raw one: building a Stream object takes ten times as
+    long)."""
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None
+                                              else index)
 
 
 class Schedule:
@@ -197,42 +201,51 @@ def _ptrs(tensors) -> "_lib.ptr_array":
     return _lib.ptr_array(*[(t.data_ptr() if t is not None else None) for t in tensors])
 
 
+def _type_ptrs(types, tensors) -> "_lib.ptr_array":
+    a = _lib.ptr_array()
+    for t, x in zip(types, tensors):
+        if x is not None:
+            a[t] = x.data_ptr()
+    return a
+
+
 class _Render(torch.autograd.Function):
+    # `types`: the node types whose parameters follow S, in the order given. Types without
+    # parameters are not passed: each argument of an autograd function costs host time in both
+    # directions, and a mastering chain of one file is bound by the host.
     @staticmethod
-    def forward(ctx, sched: Schedule, holder: list, S: torch.Tensor, *P):
+    def forward(ctx, sched: Schedule, holder: list, types: tuple, S: torch.Tensor, *P):
         dev = S.device
         K, T = sched.num_inputs, int(S.shape[-1])
         if S.dtype != torch.float32 or not S.is_contiguous() or tuple(S.shape) != (K, 2, T):
             raise ValueError(f"sources must be contiguous float32 [{K}, 2, T]")
-        want_bwd = any(ctx.needs_input_grad[2:])
+        want_bwd = any(ctx.needs_input_grad[3:])
         U = torch.empty((sched.num_nodes, 2, T), dtype=torch.float32, device=dev)
         ws = torch.empty(max(sched.workspace_bytes(T, want_bwd), 256), dtype=torch.uint8,
                          device=dev)
         check(load().grafx_render(sched._h, sched.plan(dev).data_ptr(), T, S.data_ptr(),
-                                  _ptrs(P), U.data_ptr(), ws.data_ptr(), ws.numel(),
+                                  _type_ptrs(types, P), U.data_ptr(), ws.data_ptr(), ws.numel(),
                                   _stream(dev)))
-        ctx.sched, ctx.U, ctx.ws = sched, U, ws
-        ctx.save_for_backward(S, *[p if p is not None else torch.empty(0) for p in P])
-        ctx.present = [p is not None for p in P]
+        ctx.sched, ctx.U, ctx.ws, ctx.types = sched, U, ws, types
+        ctx.save_for_backward(S, *P)
         holder.append(U)
         return U[sched.out_begin:]
 
     @staticmethod
     def backward(ctx, gY):
-        sched, U, ws = ctx.sched, ctx.U, ctx.ws
+        sched, U, ws, types = ctx.sched, ctx.U, ctx.ws, ctx.types
         S, *P = ctx.saved_tensors
-        P = [p if ok else None for p, ok in zip(P, ctx.present)]
         dev, T = U.device, U.shape[-1]
         dY = gY.contiguous() if gY is not None else torch.zeros_like(U[sched.out_begin:])
         dU = torch.empty_like(U)
-        dS = torch.empty_like(S) if ctx.needs_input_grad[2] else None
-        dP = [torch.empty_like(p) if (p is not None and ctx.needs_input_grad[3 + t]) else None
-              for t, p in enumerate(P)]
+        need = ctx.needs_input_grad
+        dS = torch.empty_like(S) if need[3] else None
+        dP = [torch.empty_like(p) if need[4 + i] else None for i, p in enumerate(P)]
         check(load().grafx_render_backward(
-            sched._h, sched.plan(dev).data_ptr(), T, S.data_ptr(), _ptrs(P), U.data_ptr(),
-            dY.data_ptr(), dU.data_ptr(), dS.data_ptr() if dS is not None else None, _ptrs(dP),
-            ws.data_ptr(), ws.numel(), _stream(dev)))
-        return (None, None, dS, *dP)
+            sched._h, sched.plan(dev).data_ptr(), T, S.data_ptr(), _type_ptrs(types, P),
+            U.data_ptr(), dY.data_ptr(), dU.data_ptr(), dS.data_ptr() if dS is not None else None,
+            _type_ptrs(types, dP), ws.data_ptr(), ws.numel(), _stream(dev)))
+        return (None, None, None, dS, *dP)
 
 
 def delay_phasor_regularise(delay_type, P: torch.Tensor, dP: torch.Tensor,
@@ -255,7 +268,9 @@ def render(sched: Schedule, S: torch.Tensor, P: dict, return_U: bool = False):
     GPU; P: type (code or name) -> float32 [|V_t|, N_t]. Returns Y [|V_N|, 2, T] (and U
     [|V|, 2, T] in reordered order, whose input rows [0, K) are not written)."""
     holder: list = []
-    Y = _Render.apply(sched, holder, S, *_param_list(sched, P))
+    Pl = _param_list(sched, P)
+    types = tuple(t for t in range(NUM_TYPES) if Pl[t] is not None)
+    Y = _Render.apply(sched, holder, types, S, *[Pl[t] for t in types])
     return (Y, holder[0]) if return_U else Y
 
 
@@ -297,7 +312,8 @@ class _MRSTFT(torch.autograd.Function):
     def backward(ctx, gL):
         Y, target = ctx.saved_tensors
         rows, T = int(Y.shape[0]), int(Y.shape[-1])
-        g = gL.detach().to(dtype=torch.float32).contiguous()
+        g = gL if gL.dtype == torch.float32 and gL.is_contiguous() else \
+            gL.to(dtype=torch.float32).contiguous()
         dY = torch.empty_like(Y)
         check(load().grafx_mrstft_backward(rows, T, Y.data_ptr(), target.data_ptr(),
                                            g.data_ptr(), dY.data_ptr(), ctx.ws.data_ptr(),

@@ -12,12 +12,9 @@ import ctypes
 import torch
 
 from ._lib import check, load
+from .api import _stream as _st
 
 N_MELS, N_OUT = 128, 11
-
-
-def _st(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need(t: torch.Tensor, name: str, dtype=torch.float32) -> torch.Tensor:
