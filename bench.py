@@ -128,7 +128,7 @@ def _len(sched, i: int, T: int) -> int:
     return T if sched.len_sigma is None else int(sched.len_sigma[i])
 
 
-DELAY_FMA = 2 * 5 * 39  # per stereo sample: 2 channels x 5 taps x 39-tap FIR
+DELAY_FFT, DELAY_HOP = 512, 474  # the delays' transform and its new samples per tile
 RV_BLOCK, RV_HALF = 2048, 2049  # reverb output block, one-sided bins of its 4096-point transforms
 
 
@@ -136,16 +136,16 @@ def step_flops(sched, n: int, T: int, backward: bool) -> float:
     """Algorithmic FP32 flops of an FFT- or FIR-bound step. EQ: 5 N log2 N per complex N-point FFT
     (N = 4096), two transforms per 2048-sample tile forward (window FFT, inverse FFT) plus the
     real spectral product, three backward (adjoint window FFT, inverse FFT, input-tile FFT) plus
-    the spectral product and the complex cross-spectrum accumulation. Delay: 2 flops per FMA of
-    the 5 x 39-tap filters per channel, once forward, twice backward (input adjoint and tap
-    gradients)."""
+    the spectral product and the complex cross-spectrum accumulation. Delay: 5 N log2 N per
+    512-point FFT, one per slot and an inverse per 474-sample tile forward, one more backward (the
+    input tile of the tap gradients)."""
     if int(sched.step_type[n]) == 11:
         return reverb_flops(sched, n, T, backward)
     if int(sched.step_type[n]) in (7, 12):  # delay (5 slots), delay_long (20 slots)
-        samples = sum(_len(sched, i, T) for i in range(int(sched.step_ptr[n]),
-                                                         int(sched.step_ptr[n + 1])))
+        tiles = sum(-(-_len(sched, i, T) // DELAY_HOP)
+                    for i in range(int(sched.step_ptr[n]), int(sched.step_ptr[n + 1])))
         slots = 20 if int(sched.step_type[n]) == 12 else 5
-        return samples * 2.0 * DELAY_FMA * slots / 5 * (2 if backward else 1)
+        return tiles * (slots + (2 if backward else 1)) * 5.0 * DELAY_FFT * np.log2(DELAY_FFT)
     tiles = sum(-(-_len(sched, i, T) // (EQ_FFT // 2))
                 for i in range(int(sched.step_ptr[n]), int(sched.step_ptr[n + 1])))
     fft = 5.0 * EQ_FFT * np.log2(EQ_FFT)
@@ -623,8 +623,8 @@ def main():
                 "frac": round(tf / FP32_VALU_TFLOPS, 4),
                 "count": {"eq": "5 N log2 N flops per 4096-point complex FFT plus the spectral "
                                 "products",
-                          "delay": "2 flops per FIR multiply-add",
-                          "delay_long": "2 flops per FIR multiply-add",
+                          "delay": "5 N log2 N flops per 512-point complex FFT",
+                          "delay_long": "5 N log2 N flops per 512-point complex FFT",
                           "reverb": "5 N log2 N flops per 4096-point complex FFT plus 16 flops "
                                     "per one-sided bin, partition and block"}[tname],
                 "peak_basis": "published FP32 vector peak (unpacked instructions with register "
