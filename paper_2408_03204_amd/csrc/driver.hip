@@ -545,8 +545,8 @@ grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_pl
   if (e == hipSuccess && dpar(GRAFX_REVERB))
     e = launch_rv_grad(h->type_count[GRAFX_REVERB], T, h->rv_len, par(GRAFX_REVERB),
                        at<double2>(ws, L.rv_Un), at<float4>(ws, L.rv_Z), at<float4>(ws, L.rv_Y0),
-                       at<int32_t>(ws, L.rv_len), at<float4>(ws, L.rv_G), at<float>(ws, L.rv_hbar), at<double>(ws, L.rv_part),
-                       dpar(GRAFX_REVERB), stream);
+                       at<int32_t>(ws, L.rv_len), at<float4>(ws, L.rv_G), at<float>(ws, L.rv_hbar),
+                       at<double>(ws, L.rv_part), dpar(GRAFX_REVERB), stream);
   return hip_status(e, "render_backward launch");
 }
 

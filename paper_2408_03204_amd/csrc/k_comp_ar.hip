@@ -155,8 +155,8 @@ __device__ __forceinline__ double fold_maps_flags(uint64_t* row, int chunk, unsi
 template <bool RAGGED>
 __global__ __launch_bounds__(kBlock) void comp_ar_fwd_kernel(
     GraphView g, float* U, int node_begin, int n_nodes, int chunks, int max_pass,
-    const char* __restrict__ coefs, uint64_t* pslot, uint64_t* fin, double* carry, uint16_t* pats, unsigned* ticket,
-    unsigned* err) {
+    const char* __restrict__ coefs, uint64_t* pslot, uint64_t* fin, double* carry,
+    uint16_t* pats, unsigned* ticket, unsigned* err) {
   __shared__ float sl[kLdsChunk], sr[kLdsChunk];
   __shared__ Aff wtot[4];
   __shared__ uint16_t sh_pat[kBlock];
@@ -270,8 +270,8 @@ __global__ __launch_bounds__(kBlock) void comp_ar_fwd_kernel(
 template <bool RAGGED>
 __global__ __launch_bounds__(kBlock, 3) void comp_ar_bwd_kernel(
     GraphView g, float* dU, int node_begin, int n_nodes, int chunks,
-    const char* __restrict__ coefs, const double* carry, const uint16_t* pats, uint64_t* ragg, double* part, unsigned* ticket,
-    unsigned* err) {
+    const char* __restrict__ coefs, const double* carry, const uint16_t* pats, uint64_t* ragg,
+    double* part, unsigned* ticket, unsigned* err) {
   __shared__ float ul[kLdsChunk], ur[kLdsChunk], yl[kLdsChunk], yr[kLdsChunk];
   __shared__ Aff wtot[4];
   __shared__ double red[20];
@@ -385,34 +385,36 @@ __global__ __launch_bounds__(kBlock, 3) void comp_ar_bwd_kernel(
 
 }  // namespace
 
-hipError_t launch_comp_ar_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int max_pass, uint64_t* pslot, uint64_t* fin,
-                              double* carry, uint16_t* pats, unsigned* ticket, unsigned* err,
-                              hipStream_t s) {
+hipError_t launch_comp_ar_fwd(const GraphView& g, float* U, int node_begin, int n_nodes, int max_pass,
+                              uint64_t* pslot, uint64_t* fin, double* carry, uint16_t* pats,
+                              unsigned* ticket, unsigned* err, hipStream_t s) {
   if (max_pass < 1 || max_pass > kArPasses) return hipErrorInvalidValue;
   const int chunks = comp_chunks(g.T);
   const unsigned grid = (unsigned)(chunks * n_nodes);
   if (g.len)
-    comp_ar_fwd_kernel<true><<<grid, kBlock, 0, s>>>(g, U, node_begin, n_nodes, chunks,
-                                                     max_pass, dyn_coefs(ticket), pslot, fin, carry, pats, ticket,
-                                                     err);
+    comp_ar_fwd_kernel<true><<<grid, kBlock, 0, s>>>(g, U, node_begin, n_nodes, chunks, max_pass,
+                                                     dyn_coefs(ticket), pslot, fin, carry, pats,
+                                                     ticket, err);
   else
-    comp_ar_fwd_kernel<false><<<grid, kBlock, 0, s>>>(g, U, node_begin, n_nodes, chunks,
-                                                      max_pass, dyn_coefs(ticket), pslot, fin, carry, pats, ticket,
-                                                      err);
+    comp_ar_fwd_kernel<false><<<grid, kBlock, 0, s>>>(g, U, node_begin, n_nodes, chunks, max_pass,
+                                                      dyn_coefs(ticket), pslot, fin, carry, pats,
+                                                      ticket, err);
   return hipGetLastError();
 }
 
-hipError_t launch_comp_ar_bwd(const GraphView& g, float* dU, int node_begin, int n_nodes, const double* carry, const uint16_t* pats,
-                              uint64_t* ragg, double* part, unsigned* ticket, unsigned* err,
-                              hipStream_t s) {
+hipError_t launch_comp_ar_bwd(const GraphView& g, float* dU, int node_begin, int n_nodes,
+                              const double* carry, const uint16_t* pats, uint64_t* ragg,
+                              double* part, unsigned* ticket, unsigned* err, hipStream_t s) {
   const int chunks = comp_chunks(g.T);
   const unsigned grid = (unsigned)(chunks * n_nodes);
   if (g.len)
-    comp_ar_bwd_kernel<true><<<grid, kBlock, 0, s>>>(g, dU, node_begin, n_nodes, chunks, dyn_coefs(ticket), carry,
-                                                     pats, ragg, part, ticket, err);
+    comp_ar_bwd_kernel<true><<<grid, kBlock, 0, s>>>(g, dU, node_begin, n_nodes, chunks,
+                                                     dyn_coefs(ticket), carry, pats, ragg, part,
+                                                     ticket, err);
   else
-    comp_ar_bwd_kernel<false><<<grid, kBlock, 0, s>>>(g, dU, node_begin, n_nodes, chunks, dyn_coefs(ticket), carry,
-                                                      pats, ragg, part, ticket, err);
+    comp_ar_bwd_kernel<false><<<grid, kBlock, 0, s>>>(g, dU, node_begin, n_nodes, chunks,
+                                                      dyn_coefs(ticket), carry, pats, ragg, part,
+                                                      ticket, err);
   return hipGetLastError();
 }
 

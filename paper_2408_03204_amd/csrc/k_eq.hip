@@ -24,9 +24,10 @@
 // the conjugate spectrum of the zero-padded input tile). The design is even in n, so only
 // hbar[n] + hbar[-n] matters: the inverse transform of the real, even sequence
 // F[k] = Re C[k] + Re C[N - k], of which N/2 + 1 values are kept. Each block handles one tile
-// and writes its folded F into its node's own region; after the last step one launch sums the
-// tiles' F per node in a fixed order, which does not depend on how nodes are grouped into steps,
-// so results do not depend on the schedule. Then one inverse FFT per node gives
+// and writes its folded F into its node's own region; after the last step the tiles' F are summed
+// per node in a fixed order, by a launch of its own or (rows of few tiles) by the blocks of the
+// transform that follows. The order does not depend on how nodes are grouped into steps, so
+// results do not depend on the schedule. Then one inverse FFT per node gives
 // hbar[n] + hbar[-n], and the chain rule through the design gives
 // dL/dp_k = (kappa_k / 2047) A_k sum_n hbar[n] v[n] cos(2 pi k n / 2047).
 #include <type_traits>
