@@ -375,7 +375,10 @@ __global__ __launch_bounds__(kBlock) void rv_spectra_kernel(GraphView g, int nod
 // For one one-sided bin k the partitioned product is a short convolution along the block index:
 // forward C[b] = sum_p X[b - p] H[p], adjoint C[b] = sum_p Yf[b + p] conj(H[p]) with
 // Yf[c] = Y0[c + 1] + (-1)^k Y0[c] (per channel, complex). A lane owns one bin of one node and
-// kConvOut output blocks, summed in registers over every partition in ascending order: the
+// kConvOut output blocks, summed in registers over every partition, the last one first, so that a
+// decaying response adds its large terms at the end (relative errors over five draws of 2 s noise:
+// output 2.93e-7 -> 2.43e-7, source adjoint 3.00e-7 -> 2.41e-7; two sums of 22 partitions each, as
+// the kernel before this one made, 2.81e-7 and 2.84e-7; 391 -> 387 us a step of 16 reverbs). The
 // blocks' spectra slide through a register ring (one enters per partition; the loop is unrolled by
 // the ring's size, so the ring is indexed statically) and each partition spectrum is read once per
 // kConvOut blocks, so a step of two 16-byte loads, made kAhead steps ahead, feeds 8 kConvOut
@@ -429,52 +432,58 @@ __global__ __launch_bounds__(kBinWave, 3) void rv_conv_bins_kernel(GraphView g, 
   const float4* Hk = Hs + (int64_t)slot * parts * kRvStride + k;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   const float sg = (k & 1) ? -1.f : 1.f;
-  // Forward: partition p meets block b0 + i in ring[(i - p) mod kConvOut]; X[b0 - p - 1] enters
-  // after it. Adjoint: in ring[(i + p) mod kConvOut]; Yf[b0 + kConvOut + p] enters after it.
-  // Partitions from pe on meet zeros only.
+  // Step q takes partition pe - 1 - q. Forward: it meets block b0 + i in ring[(i + q) mod kConvOut];
+  // X[b0 + kConvOut - pe + 1 + q] enters after it. Adjoint: in ring[(i - q) mod kConvOut];
+  // Yf[b0 + pe - 2 - q] enters after it. Partitions from pe on meet zeros only.
   const int pe = min(parts, CORR ? nb - b0 : b0 + kConvOut);
   float4 acc[kConvOut], ring[kConvOut];
+  float4 y1 = CORR ? row_entry(Sk, b0 + pe - 1, nb) : zero;
+  float4 ya = y1;
 #pragma unroll
   for (int i = 0; i < kConvOut; ++i) {
     acc[i] = zero;
-    ring[i] = conv_entry<CORR>(Sk, b0 + i, 0, nb, sg);
+    const float4 yb = row_entry(Sk, CORR ? b0 + pe + i : b0 + i - pe + 1, nb);
+    ring[i] = CORR ? make_float4(fmaf(sg, ya.x, yb.x), fmaf(sg, ya.y, yb.y), fmaf(sg, ya.z, yb.z),
+                                 fmaf(sg, ya.w, yb.w))
+                   : yb;
+    ya = yb;
   }
-  // what enters after partition p: X[b0 - p - 1], or Y0[b0 + kConvOut + p + 1] (Y0[.. + p] before it)
-  auto entering = [&](int p) {
-    return row_entry(Sk, CORR ? b0 + kConvOut + p + 1 : b0 - p - 1, nb);
+  // what enters after step q: X[b0 + kConvOut - pe + 1 + q], or Y0[b0 + pe - 2 - q] (Y0 of the next
+  // block before it)
+  auto entering = [&](int q) {
+    return row_entry(Sk, CORR ? b0 + pe - 2 - q : b0 + kConvOut - pe + 1 + q, nb);
   };
-  auto filter = [&](int p) { return Hk[(int64_t)min(p, parts - 1) * kRvStride]; };
-  float4 y0 = CORR ? row_entry(Sk, b0 + kConvOut, nb) : zero;
+  auto filter = [&](int q) { return Hk[(int64_t)max(pe - 1 - q, 0) * kRvStride]; };
   float4 ea[kAhead], ha[kAhead];
 #pragma unroll
   for (int i = 0; i < kAhead; ++i) {
     ea[i] = entering(i);
     ha[i] = filter(i);
   }
-  for (int p0 = 0; p0 < pe; p0 += kConvOut) {
+  for (int q0 = 0; q0 < pe; q0 += kConvOut) {
 #pragma unroll
     for (int j = 0; j < kConvOut; ++j) {
-      const int p = p0 + j;
-      if (p < pe) {  // uniform
+      const int q = q0 + j;
+      if (q < pe) {  // uniform
         float4 h = ha[0], e = ea[0];
 #pragma unroll
         for (int i = 0; i + 1 < kAhead; ++i) {
           ha[i] = ha[i + 1];
           ea[i] = ea[i + 1];
         }
-        ha[kAhead - 1] = filter(p + kAhead);
-        ea[kAhead - 1] = entering(p + kAhead);
+        ha[kAhead - 1] = filter(q + kAhead);
+        ea[kAhead - 1] = entering(q + kAhead);
         if (CORR) h = make_float4(h.x, -h.y, h.z, -h.w);
 #pragma unroll
         for (int i = 0; i < kConvOut; ++i)
-          acc[i] = cmac2(acc[i], ring[(CORR ? i + j : i - j + kConvOut) % kConvOut], h);
+          acc[i] = cmac2(acc[i], ring[(CORR ? i - j + kConvOut : i + j) % kConvOut], h);
         if (CORR) {
-          const float4 y1 = e;
+          const float4 y0 = e;
           e = make_float4(fmaf(sg, y0.x, y1.x), fmaf(sg, y0.y, y1.y), fmaf(sg, y0.z, y1.z),
                           fmaf(sg, y0.w, y1.w));
-          y0 = y1;
+          y1 = y0;
         }
-        ring[CORR ? j : kConvOut - 1 - j] = e;
+        ring[CORR ? kConvOut - 1 - j : j] = e;
       }
     }
   }
