@@ -30,7 +30,10 @@ def _iptr(a):
 
 def _stream(device) -> int:
     """The current stream's handle (the raw one: building a Stream object takes ten times as
-    long)."""
+    long). Any device but a GPU is refused: the library reads raw addresses, and this is where
+    every call learns whose they are."""
+    if device.type != "cuda":
+        raise ValueError(f"Expected a cuda device, but got: {device}")
     index = device.index
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None
                                               else index)
