@@ -16,7 +16,7 @@
 // most 6.6 bytes for each of the limit's, since a slot's taps and delay (320 bytes) are inside it.
 static constexpr size_t kNoallocScratchBytes = GRAFX_NOALLOC_SCRATCH_BYTES;
 static constexpr size_t kNoallocSpecBytes = 7 * kNoallocScratchBytes;
-static_assert(grafx::delay_spec(1) * sizeof(float2) <=
+static_assert(grafx::delay_spec(1) * sizeof(float) <=
                   7 * (grafx::delay_coef(1) * sizeof(float) + 2 * sizeof(int32_t)),
               "the spectra of every delay that fits the limit fit the scratch");
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes + kNoallocSpecBytes];
@@ -98,7 +98,7 @@ WsLayout ws_layout(const grafx_schedule_t* h, int64_t T, bool with_bwd) {
   L.rv_C = take(n_rv * rv_nb * kRvStride * sizeof(float4));
   for (int f = 0; f < 2; ++f)  // last: the allocation-free render counts these apart
     L.delay_spec[f] = take((size_t)h->type_count[kDelayType[f]] * delay_spec(kDelaySlots[f]) *
-                           sizeof(float2));
+                           sizeof(float));
   L.fwd_end = off;
   if (with_bwd) {
     const size_t tiles = pointwise_tiles(T);
@@ -288,8 +288,9 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
     case GRAFX_DELAY:
     case GRAFX_DELAY_LONG: {
       const int f = delay_family(t);
-      return launch_delay_fwd(kDelaySlots[f], g, U, at<float2>(ws, L.delay_spec[f]),
-                              at<int32_t>(ws, L.delay_offs[f]), b, cnt, stream);
+      return launch_delay_fwd(kDelaySlots[f], g, U, at<float>(ws, L.delay_taps[f]),
+                              at<float>(ws, L.delay_spec[f]), at<int32_t>(ws, L.delay_offs[f]), b,
+                              cnt, stream);
     }
     case GRAFX_COMPRESSOR_AR: {
       const size_t n_ar = h->type_count[GRAFX_COMPRESSOR_AR], chunks = comp_chunks(g.T);
@@ -331,7 +332,8 @@ hipError_t enqueue_bwd_step(const grafx_schedule_t* h, const GraphView& g, const
     case GRAFX_DELAY:
     case GRAFX_DELAY_LONG: {
       const int f = delay_family(t);
-      hipError_t e = launch_delay_bwd(kDelaySlots[f], g, dU, at<float2>(ws, L.delay_spec[f]),
+      hipError_t e = launch_delay_bwd(kDelaySlots[f], g, dU, at<float>(ws, L.delay_taps[f]),
+                                      at<float>(ws, L.delay_spec[f]),
                                       at<int32_t>(ws, L.delay_offs[f]), b, cnt,
                                       at<float>(ws, L.delay_part[f]), stream);
       // R[n] = sum_t ybar[t - 19] u[t - n]: lag n - 19 of the plain correlation
@@ -384,7 +386,7 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
   for (int f = 0; f < 2 && e == hipSuccess; ++f)
     if (h->type_count[kDelayType[f]] > 0)
       e = launch_delay_design(kDelaySlots[f], par(kDelayType[f]), h->type_count[kDelayType[f]],
-                              at<float>(ws, L.delay_taps[f]), at<float2>(ws, L.delay_spec[f]),
+                              at<float>(ws, L.delay_taps[f]), at<float>(ws, L.delay_spec[f]),
                               at<int32_t>(ws, L.delay_offs[f]), stream);
   if (e == hipSuccess && h->type_count[GRAFX_REVERB] > 0)
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,

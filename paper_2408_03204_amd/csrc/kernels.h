@@ -135,20 +135,21 @@ constexpr int delay_coef(int M) { return 2 * M * kDelayFir; }  // filter taps pe
 constexpr int delay_row(int M) { return 2 * M * 22; }          // parameters per node
 constexpr int kDelayFFT = 512;                                 // transform of a 474-sample tile
 constexpr int kDelayBins = kDelayFFT / 2 + 8;                  // one-sided bins, padded
-constexpr int delay_spec(int M) { return M * kDelayBins; }     // (left, right) bins per node
+constexpr int delay_spec(int M) { return 2 * M * kDelayBins; }  // spectrum entries per node
 constexpr int delay_lags(int M) { return 2 * M * 20; }         // gradient lags per node
 constexpr int kTapTilesMin = 4;  // smallest tap-gradient group setting (sizes the partials)
 int delay_groups(int64_t T, int tap_tiles);  // tile groups per node in the adjoint
-// taps: float [n][delay_coef(M)]; spec: float2 [n][M][kDelayBins], the one-sided real spectra of
+// taps: float [n][delay_coef(M)]; spec: float [n][M][2][kDelayBins], the one-sided real spectra of
 // the slots' left and right filters, scaled by 1 / 1024; offs: int32 [n][2 M]
-hipError_t launch_delay_design(int M, const float* P, int n, float* taps, float2* spec,
+hipError_t launch_delay_design(int M, const float* P, int n, float* taps, float* spec,
                                int32_t* offs, hipStream_t s);
-hipError_t launch_delay_fwd(int M, const GraphView& g, float* U, const float2* spec,
-                            const int32_t* offs, int node_begin, int n_nodes, hipStream_t s);
-// Input adjoint and tap gradients; part: float [n][groups][delay_lags(M)]
-hipError_t launch_delay_bwd(int M, const GraphView& g, float* dU, const float2* spec,
-                            const int32_t* offs, int node_begin, int n_nodes, float* part,
+hipError_t launch_delay_fwd(int M, const GraphView& g, float* U, const float* taps,
+                            const float* spec, const int32_t* offs, int node_begin, int n_nodes,
                             hipStream_t s);
+// Input adjoint and tap gradients; part: float [n][groups][delay_lags(M)]
+hipError_t launch_delay_bwd(int M, const GraphView& g, float* dU, const float* taps,
+                            const float* spec, const int32_t* offs, int node_begin, int n_nodes,
+                            float* part, hipStream_t s);
 hipError_t launch_delay_grad(int M, const float* P, const float* part, int n, int groups,
                              float* dP, hipStream_t s);
 // Delay-time surrogate: lags -19 .. M x 4410 + 19 of the input/adjoint cross-correlation (the
