@@ -43,6 +43,13 @@ struct CurveCoef {
   float kR;              // -dc/dR in natural-log units: ln 2 / R^2 or ln 2
 };
 
+// An infinite coefficient (a noise gate of infinite ratio) as the largest float, so that its product
+// with a ramp of 0 is 0 where the curve has no effect, not NaN; elsewhere the gain is 0 all the same.
+__device__ __forceinline__ float finite_coef(float c) {
+  constexpr float most = 3.402823466e38f;
+  return c > most ? most : c < -most ? -most : c;
+}
+
 __device__ __forceinline__ CurveCoef make_curve(double thr, double knee, double ratio, bool gate) {
   constexpr double log2e = 1.4426950408889634074, ln2 = 0.69314718055994530942;
   CurveCoef k;
@@ -55,8 +62,8 @@ __device__ __forceinline__ CurveCoef make_curve(double thr, double knee, double 
   k.w_2 = (float)(2.0 * w);
   k.inv2w = w > 0.0 ? (float)(0.5 / w) : 0.f;
   k.inv4w = w > 0.0 ? (float)(0.25 / w) : 0.f;
-  k.c = (float)(gate ? 1.0 - ratio : 1.0 / ratio - 1.0);
-  k.kR = (float)(gate ? ln2 : ln2 / (ratio * ratio));
+  k.c = finite_coef((float)(gate ? 1.0 - ratio : 1.0 / ratio - 1.0));
+  k.kR = finite_coef((float)(gate ? ln2 : ln2 / (ratio * ratio)));
   return k;
 }
 
