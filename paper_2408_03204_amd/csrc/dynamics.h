@@ -105,12 +105,6 @@ __device__ __forceinline__ float gain(float f, const CurveCoef& k) {
   return __builtin_amdgcn_exp2f(k.c * f);
 }
 
-// a / gs for gs >= 1e-8 with one correction step (within one unit in the last place)
-__device__ __forceinline__ float over_envelope(float a, float gs) {
-  const float b = fminf(gs, 1e37f), r = __builtin_amdgcn_rcpf(b), q = a * r;
-  return fmaf(fmaf(-b, q, a), r, q);
-}
-
 // ---- wave exchanges without LDS ----------------------------------------------------------------
 
 // The value of another lane of the same row of 16 (a DPP control); lanes without a source get `old`.

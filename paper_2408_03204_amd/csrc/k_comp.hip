@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void comp_bwd_kernel(GraphView g, float* dU
       const float y_l = gam * yl[idx], y_r = gam * yr[idx];
       const float rho = fmaf(y_l, u_l, y_r * u_r);
       const float rfp = rho * r.fp;
-      gbar[i] = over_envelope(dg * rfp, gs);
+      gbar[i] = dg * rfp / gs;
       sum_fp += (double)rfp;
       sum_w += (double)(rfp * r.fq);
       sum_f += (double)(rho * r.f);

@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kBlock, 3) void comp_ar_bwd_kernel(
       const float y_l = gam * yl[idx], y_r = gam * yr[idx];
       const float rho = fmaf(y_l, u_l, y_r * u_r);
       const float rfp = rho * r.fp;
-      gbar[i] = over_envelope(k.cv.c * rfp, gs);
+      gbar[i] = k.cv.c * rfp / gs;
       sum_fp += (double)rfp;
       sum_w += (double)(rfp * r.fq);
       sum_f += (double)(rho * r.f);

@@ -58,3 +58,26 @@ def test_compressor_whose_ratio_has_no_finite_inverse(kind, alphas):
     dY = np.random.default_rng(7).standard_normal((2, T)).astype(np.float32)
     Y, dS, dP = run(kind, v, alphas + [-4.0, 0.5, 1e-39], dY)
     assert np.array_equal(Y, v) and np.array_equal(dS, dY) and np.all(dP == 0.0)
+
+
+@pytest.mark.parametrize("kind,alphas,p", [(synth.COMP, [0.0], -0.5), (synth.COMP_AR, [0.0, 0.0], -0.5),
+                                           (synth.GATE, [0.0], 1.0)])
+@pytest.mark.parametrize("size", [2e18, 4e18, 9e18])
+def test_adjoint_of_an_envelope_near_the_largest_float(kind, alphas, p, size):
+    """alpha = 0 and a hard knee, every sample on the curve's slope: gamma = (g / e^T)^p with the
+    envelope g = (u_l + u_r)^2 of 1e37 to 3e38, so ubar_c = gamma ybar_c + 2 (u_l + u_r) rho p / g,
+    rho = sum_c ybar_c y_c. Tolerance: the gradients' 1e-3 of the largest entry, less the part that
+    does not pass the envelope."""
+    T, thr = 3100, (89.0 if kind == synth.GATE else 80.0)
+    rng = np.random.default_rng(8)
+    u = (rng.choice([-1.0, 1.0], (1, T)) * rng.uniform(0.8, 1.0, (2, T)) * size).astype(np.float32)
+    dY = rng.standard_normal((2, T)).astype(np.float32)
+    _, dS, _ = run(kind, u, alphas + [thr, 0.0, 2.0], dY)
+    u64, m = u.astype(np.float64), u.astype(np.float64).sum(axis=0)
+    g = m * m
+    gain = np.exp(p * (np.log(g) - thr))
+    through = 2.0 * m * (dY * gain * u64).sum(axis=0) * p / g
+    ref = gain * dY + through
+    say(f"[envelope near the largest float] kind {kind} size {size:g}: "
+        f"{np.abs(dS - ref).max() / np.abs(through).max():.2e}")
+    assert np.abs(dS - ref).max() <= 1e-3 * np.abs(through).max()
