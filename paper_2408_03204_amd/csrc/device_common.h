@@ -73,6 +73,10 @@ __device__ __forceinline__ float* source_row(const GraphView& g, int v) {
   return k < g.K ? g.dS + (int64_t)k * 2 * g.T : nullptr;
 }
 
+// Between LDS accesses through which the lanes of one wave exchange data: the hardware executes a wave's
+// LDS accesses in order, this keeps the compiler from moving them. Costs no instruction.
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
 // Raw buffer resource over n floats starting at p: loads through it take a 32-bit element
 // offset and return 0 outside [0, n) (the hardware range check), which implements the zero
 // padding of signal windows without branches. Requires n < 2^29.

@@ -86,8 +86,6 @@ __device__ __forceinline__ void load_twiddles512(Twiddles512& tw, float2* w1, in
   tw.w1 = w1 + (j & 7) * 9;
 }
 
-__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
 // On entry v[r] = x[j + 64 r], on exit X[j + 64 r] (forward exp(-2 pi i nk/N), inverse exp(+...),
 // unnormalised). Element e of an exchange sits at e + e / 8: the writes at 8 j + r and
 // 64 (j / 8) + j mod 8 + 8 r and the reads at j + 64 r fall on distinct banks (but for a wrap of

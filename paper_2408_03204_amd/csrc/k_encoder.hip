@@ -661,10 +661,12 @@ __global__ __launch_bounds__(kGradBlock) void weight_grad_kernel(GradLayers P, i
         const int e = lane + 64 * m, r = e / kGradCols;
         if (e < 4 * kGradCols) xw[r * kGradRow + e - r * kGradCols] = c.x[m];
       }
+      lds_order();
       if (s + 1 < n) load(nx);
       float xv[kGradFrames / 4];
 #pragma unroll
       for (int j = 0; j < kGradFrames / 4; ++j) xv[j] = xq[8 * j];
+      lds_order();  // read before the next unit's stores
       auto multiply = [&](auto whole) {
 #pragma unroll
         for (int j = 0; j < kGradFrames / 4; ++j) {

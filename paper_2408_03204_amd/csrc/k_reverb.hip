@@ -63,8 +63,6 @@ __device__ __forceinline__ void fill_tw384(double2* tw) {
   }
 }
 
-__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
 __device__ __forceinline__ double2 dadd(double2 a, double2 b) {
   return make_double2(a.x + b.x, a.y + b.y);
 }
