@@ -268,13 +268,14 @@ grafx_status grafx_render(const grafx_schedule_t* sched, const void* dev_plan, i
  *
  *   dev_plan, T, S, P, U, stream   exactly as for grafx_render
  * Scratch: one array per GPU, in the library's code object: GRAFX_NOALLOC_SCRATCH_BYTES (32 MiB)
- * and seven times as much for the slot spectra of multitap delays (2,112 bytes per slot and node,
- * which count apart); each GPU the library runs on holds it until the process ends. The first call on a
- * device (the device current on the calling thread, which must own `stream`) looks up the
- * array's address there; no call allocates or frees memory. A render whose forward workspace
- * (grafx_workspace_bytes with with_backward = 0), less its delay spectra, exceeds
- * GRAFX_NOALLOC_SCRATCH_BYTES fails with
- * GRAFX_E_WORKSPACE before any device work: use grafx_render then. The call clears what must
+ * and 2 MiB for the slot spectra of multitap delays (2,112 bytes per slot and node, which count
+ * apart: a graph with more of them has each step's spectra formed there part by part, two
+ * launches for every 198 delays or 49 2 s delays). Each GPU the library runs on holds it until the
+ * process ends. The first call on a device (the device current on the calling thread, which must
+ * own `stream`) looks up the array's address there; no call allocates or frees memory. A render
+ * whose forward workspace (grafx_workspace_bytes with with_backward = 0), less its delay spectra,
+ * exceeds GRAFX_NOALLOC_SCRATCH_BYTES fails with GRAFX_E_WORKSPACE before any device work: use
+ * grafx_render then. The call clears what must
  * start at zero (the dynamics chunk states and the error word) itself; everything else it
  * writes before reading.
  * Every call on a GPU shares that GPU's scratch, which keeps the last call's contents: two calls

@@ -12,13 +12,11 @@
 // Workspace of grafx_render_noalloc: a file-scope device array, one copy per GPU, held until the
 // process ends. In host code its name is not a device address: the address comes from
 // hipGetSymbolAddress, looked up once per device (with that device current) by noalloc_scratch.
-// The public limit holds for the workspace without the delays' slot spectra, which come on top: at
-// most 6.6 bytes for each of the limit's, since a slot's taps and delay (320 bytes) are inside it.
+// The public limit holds for the workspace without the delays' slot spectra, which come on top: 2 MiB,
+// the spectra of 198 delays (49 of 2 s). A render with more of them forms its steps' spectra in that
+// space, as many nodes at a time.
 static constexpr size_t kNoallocScratchBytes = GRAFX_NOALLOC_SCRATCH_BYTES;
-static constexpr size_t kNoallocSpecBytes = 7 * kNoallocScratchBytes;
-static_assert(grafx::delay_spec(1) * sizeof(float) <=
-                  7 * (grafx::delay_coef(1) * sizeof(float) + 2 * sizeof(int32_t)),
-              "the spectra of every delay that fits the limit fit the scratch");
+static constexpr size_t kNoallocSpecBytes = (size_t)2 << 20;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes + kNoallocSpecBytes];
 
 namespace grafx {
@@ -38,6 +36,7 @@ struct WsLayout {
   size_t rv_Y0, rv_G, rv_hbar, rv_part, rv_len;
   size_t dl_X[2], dl_Y0[2], dl_G[2], dl_R[2], dl_len[2];
   size_t total;
+  int spec_nodes[2];  // delays whose spectra fit delay_spec at a time, 0: all, by parameter row
 };
 
 // Dynamics rows: compressors first, then noisegates.
@@ -287,10 +286,18 @@ hipError_t enqueue_fwd_step(const grafx_schedule_t* h, const GraphView& g, const
                              error_word(ws, L), stream);
     case GRAFX_DELAY:
     case GRAFX_DELAY_LONG: {
-      const int f = delay_family(t);
-      return launch_delay_fwd(kDelaySlots[f], g, U, at<float>(ws, L.delay_taps[f]),
-                              at<float>(ws, L.delay_spec[f]), at<int32_t>(ws, L.delay_offs[f]), b,
-                              cnt, stream);
+      const int f = delay_family(t), M = kDelaySlots[f], most = L.spec_nodes[f];
+      float *taps = at<float>(ws, L.delay_taps[f]), *spec = at<float>(ws, L.delay_spec[f]);
+      int32_t* offs = at<int32_t>(ws, L.delay_offs[f]);
+      if (!most) return launch_delay_fwd(M, g, U, taps, spec, false, offs, b, cnt, stream);
+      hipError_t e = hipSuccess;
+      for (int i = 0; i < cnt && e == hipSuccess; i += most) {
+        const int n = std::min(most, cnt - i);
+        e = launch_delay_design(M, P[t], g.param_row + b + i, n, taps, spec, offs, stream);
+        if (e == hipSuccess)
+          e = launch_delay_fwd(M, g, U, taps, spec, true, offs, b + i, n, stream);
+      }
+      return e;
     }
     case GRAFX_COMPRESSOR_AR: {
       const size_t n_ar = h->type_count[GRAFX_COMPRESSOR_AR], chunks = comp_chunks(g.T);
@@ -371,8 +378,7 @@ grafx_status hip_status(hipError_t e, const char* what) {
 // parameter preprocessing, reset of the dynamics chaining state, then steps 1..N.
 grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int64_t T,
                             const float* S, const float* const* P, float* U, void* ws,
-                            hipStream_t stream) {
-  const WsLayout L = ws_layout(h, T, false);
+                            const WsLayout& L, hipStream_t stream) {
   const GraphView g = make_view(h, dev_plan, T, S, U);
   auto par = [&](int t) -> const float* { return P ? P[t] : nullptr; };
   // per-render parameter preprocessing and the dynamics chaining state
@@ -384,10 +390,11 @@ grafx_status enqueue_render(const grafx_schedule_t* h, const void* dev_plan, int
   if (e == hipSuccess)
     e = launch_eq_design(jobs.n_eq, at<double>(ws, L.eq_h), jobs.eq_H, stream);
   for (int f = 0; f < 2 && e == hipSuccess; ++f)
-    if (h->type_count[kDelayType[f]] > 0)
-      e = launch_delay_design(kDelaySlots[f], par(kDelayType[f]), h->type_count[kDelayType[f]],
-                              at<float>(ws, L.delay_taps[f]), at<float>(ws, L.delay_spec[f]),
-                              at<int32_t>(ws, L.delay_offs[f]), stream);
+    if (h->type_count[kDelayType[f]] > 0 && !L.spec_nodes[f])
+      e = launch_delay_design(kDelaySlots[f], par(kDelayType[f]), nullptr,
+                              h->type_count[kDelayType[f]], at<float>(ws, L.delay_taps[f]),
+                              at<float>(ws, L.delay_spec[f]), at<int32_t>(ws, L.delay_offs[f]),
+                              stream);
   if (e == hipSuccess && h->type_count[GRAFX_REVERB] > 0)
     e = launch_rv_design(par(GRAFX_REVERB), h->type_count[GRAFX_REVERB], h->rv_noise, h->rv_len,
                          at<double2>(ws, L.rv_Un), at<float>(ws, L.rv_h), at<float4>(ws, L.rv_H),
@@ -454,7 +461,7 @@ grafx_status grafx_render(const grafx_schedule_t* h, const void* dev_plan, int64
   clear_error();
   grafx_status st = check_common(h, dev_plan, T, S, P, U, ws, ws_bytes, false);
   if (st != GRAFX_OK) return st;
-  return enqueue_render(h, dev_plan, T, S, P, U, ws, stream);
+  return enqueue_render(h, dev_plan, T, S, P, U, ws, ws_layout(h, T, false), stream);
 }
 
 grafx_status grafx_render_noalloc(const grafx_schedule_t* h, const void* dev_plan, int64_t T,
@@ -464,12 +471,9 @@ grafx_status grafx_render_noalloc(const grafx_schedule_t* h, const void* dev_pla
   // the same checks as grafx_render with a stand-in workspace of the scratch's size (aligned, not
   // dereferenced), so that a request beyond the scratch fails before any HIP call
   void* const stand_in = reinterpret_cast<void*>(uintptr_t{256});
-  size_t need = 0, spectra = 0;
-  if (h && T >= 1) {
-    const WsLayout L = ws_layout(h, T, false);
-    need = L.delay_spec[0];
-    spectra = L.fwd_end - need;
-  }
+  WsLayout L{};
+  if (h && T >= 1) L = ws_layout(h, T, false);
+  const size_t need = L.delay_spec[0], spectra = L.fwd_end - need;
   grafx_status st =
       check_common(h, dev_plan, T, S, P, U, stand_in, kNoallocScratchBytes + spectra, false);
   if (st == GRAFX_E_WORKSPACE)
@@ -481,7 +485,12 @@ grafx_status grafx_render_noalloc(const grafx_schedule_t* h, const void* dev_pla
   void* ws = nullptr;
   st = hip_status(noalloc_scratch(&ws), "scratch address");
   if (st != GRAFX_OK) return st;
-  return enqueue_render(h, dev_plan, T, S, P, U, ws, stream);
+  if (spectra > kNoallocSpecBytes)
+    for (int f = 0; f < 2; ++f) {  // the steps of both types in turn, on one stream
+      L.delay_spec[f] = need;
+      L.spec_nodes[f] = (int)(kNoallocSpecBytes / (delay_spec(kDelaySlots[f]) * sizeof(float)));
+    }
+  return enqueue_render(h, dev_plan, T, S, P, U, ws, L, stream);
 }
 
 grafx_status grafx_render_backward(const grafx_schedule_t* h, const void* dev_plan, int64_t T,

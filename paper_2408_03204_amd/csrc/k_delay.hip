@@ -475,10 +475,11 @@ struct Balance {
 
 // One block per (node, slot): the taps of both channels, the integer delays and the spectra.
 template <int M>
-__global__ __launch_bounds__(kBlock) void delay_design_kernel(const float* P, float* taps,
-                                                              float* spec, int32_t* offs) {
+__global__ __launch_bounds__(kBlock) void delay_design_kernel(const float* P, const int32_t* rows,
+                                                              float* taps, float* spec,
+                                                              int32_t* offs) {
   __shared__ double cn[kN], c39[kDelayFir], A[2][20], h[2][20];
-  const int node = blockIdx.x, m = blockIdx.y, tid = threadIdx.x;
+  const int node = rows ? rows[blockIdx.x] : (int)blockIdx.x, m = blockIdx.y, tid = threadIdx.x;
   const float* p = P + (int64_t)node * delay_row(M);
   for (int i = tid; i < kN; i += kBlock) cn[i] = cospi((double)i / (kN / 2));
   if (tid < kDelayFir) c39[tid] = cospi(2.0 * tid / 39.0);
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(kBlock) void delay_design_kernel(const float* P, fl
     offs[(int64_t)node * 2 * M + tid * M + m] = m * kDelaySlot + d;
   }
   __syncthreads();
-  float* sp = spec + (int64_t)node * delay_spec(M) + 2 * m * kDelayBins;
+  float* sp = spec + (int64_t)blockIdx.x * delay_spec(M) + 2 * m * kDelayBins;
   for (int k = tid; k <= kN / 2; k += kBlock) {
     double l = h[0][0], r = h[1][0];
     for (int j = 1; j <= kHalf; ++j) {
@@ -523,6 +524,7 @@ __global__ __launch_bounds__(kBlock) void delay_design_kernel(const float* P, fl
 template <int M>
 __global__ __launch_bounds__(kBlock, 4) void delay_fwd_kernel(GraphView g, float* U,
                                                               const float* taps, const float* spec,
+                                                              bool spec_by_node,
                                                               const int32_t* offs, int node_begin,
                                                               int per_node) {
   __shared__ float2 lds[kWaves][kSlice], w1[kWaves][kW1];
@@ -535,7 +537,8 @@ __global__ __launch_bounds__(kBlock, 4) void delay_fwd_kernel(GraphView g, float
   float2* s = lds[wave];
   const int slot = __builtin_amdgcn_readfirstlane(g.param_row[node]);
   const int32_t* d = offs + (int64_t)slot * 2 * M;
-  const float* sp = spec + (int64_t)slot * delay_spec(M) + c * kDelayBins;
+  const float* sp =
+      spec + (int64_t)(spec_by_node ? node - node_begin : slot) * delay_spec(M) + c * kDelayBins;
   const int e0 = __builtin_amdgcn_readfirstlane(g.in_ptr[node]);
   const int e1 = __builtin_amdgcn_readfirstlane(g.in_ptr[node + 1]);
   Twiddles512 tw;
@@ -856,22 +859,23 @@ hipError_t with_slots(int M, F&& body) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_delay_design(int M, const float* P, int n, float* taps, float* spec,
-                               int32_t* offs, hipStream_t s) {
+hipError_t launch_delay_design(int M, const float* P, const int32_t* rows, int n, float* taps,
+                               float* spec, int32_t* offs, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   return with_slots(M, [&](auto m) {
-    delay_design_kernel<decltype(m)::value><<<dim3(n, M), kBlock, 0, s>>>(P, taps, spec, offs);
+    delay_design_kernel<decltype(m)::value><<<dim3(n, M), kBlock, 0, s>>>(P, rows, taps, spec,
+                                                                            offs);
     return hipGetLastError();
   });
 }
 
 hipError_t launch_delay_fwd(int M, const GraphView& g, float* U, const float* taps,
-                            const float* spec, const int32_t* offs, int node_begin, int n_nodes,
-                            hipStream_t s) {
+                            const float* spec, bool spec_by_node, const int32_t* offs,
+                            int node_begin, int n_nodes, hipStream_t s) {
   const int tiles = (int)((g.T + kHop - 1) / kHop), per_node = (tiles + kWaves - 1) / kWaves;
   return with_slots(M, [&](auto m) {
     delay_fwd_kernel<decltype(m)::value><<<(unsigned)(per_node * n_nodes), kBlock, 0, s>>>(
-        g, U, taps, spec, offs, node_begin, per_node);
+        g, U, taps, spec, spec_by_node, offs, node_begin, per_node);
     return hipGetLastError();
   });
 }

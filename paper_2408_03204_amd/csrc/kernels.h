@@ -141,11 +141,14 @@ constexpr int kTapTilesMin = 4;  // smallest tap-gradient group setting (sizes t
 int delay_groups(int64_t T, int tap_tiles);  // tile groups per node in the adjoint
 // taps: float [n][delay_coef(M)]; spec: float [n][M][2][kDelayBins], the one-sided real spectra of
 // the slots' left and right filters, scaled by 1 / 1024; offs: int32 [n][2 M]
-hipError_t launch_delay_design(int M, const float* P, int n, float* taps, float* spec,
-                               int32_t* offs, hipStream_t s);
+// rows: the nodes' parameter rows (device), or null for rows 0 .. n - 1; taps and offs are stored by
+// parameter row, spec by position in the launch
+hipError_t launch_delay_design(int M, const float* P, const int32_t* rows, int n, float* taps,
+                               float* spec, int32_t* offs, hipStream_t s);
+// spec_by_node: spec holds the launch's nodes in order, not all nodes by parameter row
 hipError_t launch_delay_fwd(int M, const GraphView& g, float* U, const float* taps,
-                            const float* spec, const int32_t* offs, int node_begin, int n_nodes,
-                            hipStream_t s);
+                            const float* spec, bool spec_by_node, const int32_t* offs,
+                            int node_begin, int n_nodes, hipStream_t s);
 // Input adjoint and tap gradients; part: float [n][groups][delay_lags(M)]
 hipError_t launch_delay_bwd(int M, const GraphView& g, float* dU, const float* taps,
                             const float* spec, const int32_t* offs, int node_begin, int n_nodes,

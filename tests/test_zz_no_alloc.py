@@ -43,3 +43,34 @@ def test_noalloc_render_matches_render_on_successive_smaller_inputs():
         sched, Y, U = _pair(w)
     check_render(w, sched, Y, U)
 
+
+
+def test_noalloc_render_of_more_delays_than_its_spectra_space_holds():
+    """3,000 delays and 300 2 s delays, in two layers and in shuffled order: their taps fit the
+    scratch, their spectra (44 MB) do not, and are formed part by part."""
+    T, rng = 700, synth.rng_for(77, 1)
+    kinds = [synth.DELAY] * 3000 + [synth.DELAY_LONG] * 300
+    rng.shuffle(kinds)
+    b = synth.GraphBuilder()
+    ins = [b.add(synth.IN) for _ in range(3)]
+    nodes = [b.add(k) for k in kinds]
+    m, o = b.add(synth.MIX), b.add(synth.OUT)
+    for i, n in enumerate(nodes):  # every third delay follows the one before it
+        b.connect(nodes[i - 1] if i % 3 == 2 else ins[i % 2], n)
+        b.connect(n, m)
+    b.connect(ins[2], m)
+    b.connect(m, o)
+    g = b.build()
+    P = synth.draw_params(synth.rng_for(77, 2), g)
+    w = synth.Workload("delays", g, synth.make_sources(synth.rng_for(77, 3), 3, T), P, None, T, 77)
+    sched = Schedule(g.node_type, g.edges, "greedy")
+    assert sched.workspace_bytes(T, False) > (40 << 20)
+    S, P = device_inputs(w)
+    ref = RenderBuffers(sched, T, "cuda", with_backward=False)
+    ref.forward(S, P)
+    U = torch.full((sched.num_nodes, 2, T), float("nan"), dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        render_noalloc(sched, ref.plan, S, P, U)
+    torch.cuda.synchronize()
+    K = sched.num_inputs
+    assert torch.equal(U[K:].view(torch.int32), ref.U[K:].view(torch.int32))
