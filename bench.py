@@ -576,6 +576,8 @@ def main():
         dPd = {t: torch.empty_like(p) for t, p in Pd.items()}
         rb.forward(S, Pd)
         rb.backward(S, Pd, dY, dPd)
+        # step by step: runs of pointwise steps, which a whole pass launches as one chain, count here as
+        # the steps they are made of
         reps = 5
         evs = []
         for direction in ("fwd", "bwd"):
