@@ -379,15 +379,15 @@ __global__ __launch_bounds__(kBlock) void rv_spectra_kernel(GraphView g, int nod
 // the kernel before this one made, 2.81e-7 and 2.84e-7; 391 -> 387 us a step of 16 reverbs). The
 // blocks' spectra slide through a register ring (one enters per partition; the loop is unrolled by
 // the ring's size, so the ring is indexed statically) and each partition spectrum is read once per
-// kConvOut blocks, so a step of two 16-byte loads, made kAhead steps ahead, feeds 8 kConvOut
-// multiply-adds. One wave per 64 bins; bin 2048 is left to the inverse kernel, because a 33rd wave
-// for it would start a second round of waves on a full chip. Waves of one node and bin range are
-// neighbours on one XCD, whose L2 keeps the spectra that they share. 16 nodes, 128 blocks, 44
-// partitions: 60 us (0.1 ms with 22 partitions in registers, blocks streaming through and the
-// partial products of the tiles written apart). Loads further ahead, 14 or 12 blocks a wave, or two
-// waves per SIMD instead of three gained nothing.
+// kConvOut blocks, so a step of two 16-byte loads, made a step ahead, feeds 8 kConvOut
+// multiply-adds. One wave per 64 bins; bin 2048 is left to the inverse kernel, since a 33rd wave for
+// it alone would be a thirty-third of the launch. Waves of one node and bin range are neighbours on
+// one XCD, whose L2 keeps the spectra that they share. 16 nodes, 128 blocks, 44 partitions: 4096
+// waves, three a SIMD (151 and 163 VGPRs), so one round and a third: 60 us (0.1 ms with 22
+// partitions in registers, blocks streaming through and the partial products of the tiles written
+// apart). Loads further ahead, 14 or 12 blocks a wave, or two waves per SIMD instead of three gained
+// nothing.
 constexpr int kConvOut = 16;
-constexpr int kAhead = 1;
 constexpr int kBinWave = 64;
 constexpr int kBinWaves = kN / 2 / kBinWave;  // 32
 
@@ -452,25 +452,15 @@ __global__ __launch_bounds__(kBinWave, 3) void rv_conv_bins_kernel(GraphView g, 
     return row_entry(Sk, CORR ? b0 + pe - 2 - q : b0 + kConvOut - pe + 1 + q, nb);
   };
   auto filter = [&](int q) { return Hk[(int64_t)max(pe - 1 - q, 0) * kRvStride]; };
-  float4 ea[kAhead], ha[kAhead];
-#pragma unroll
-  for (int i = 0; i < kAhead; ++i) {
-    ea[i] = entering(i);
-    ha[i] = filter(i);
-  }
+  float4 next_h = filter(0), next_e = entering(0);
   for (int q0 = 0; q0 < pe; q0 += kConvOut) {
 #pragma unroll
     for (int j = 0; j < kConvOut; ++j) {
       const int q = q0 + j;
       if (q < pe) {  // uniform
-        float4 h = ha[0], e = ea[0];
-#pragma unroll
-        for (int i = 0; i + 1 < kAhead; ++i) {
-          ha[i] = ha[i + 1];
-          ea[i] = ea[i + 1];
-        }
-        ha[kAhead - 1] = filter(q + kAhead);
-        ea[kAhead - 1] = entering(q + kAhead);
+        float4 h = next_h, e = next_e;
+        next_h = filter(q + 1);
+        next_e = entering(q + 1);
         if (CORR) h = make_float4(h.x, -h.y, h.z, -h.w);
 #pragma unroll
         for (int i = 0; i < kConvOut; ++i)
@@ -555,8 +545,8 @@ __global__ __launch_bounds__(kBlock) void rv_inverse_kernel(GraphView g, float* 
 // partitions: the input spectra enter a register ring one block per step (as in the product),
 // the block's Y0 is read once for the whole tile. Each group of kCrossTile consecutive blocks is
 // summed in float (at most kCrossTile terms), the groups in double, in block order. Bin 2048 is
-// left to the next kernel (a 33rd wave would start a second round). 16 nodes, 128 blocks, 44
-// partitions: 67 us (139 us with 33 waves).
+// left to the next kernel: 16 nodes, 128 blocks, 44 partitions are 2048 waves, two a SIMD (203
+// VGPRs), one round, which a 33rd wave per node and tile would make two: 67 us (139 us with it).
 constexpr int kCrossTile = 11;
 
 __global__ __launch_bounds__(kBinWave) void rv_cross_kernel(int nb, int parts, const float4* Y0,
@@ -573,13 +563,8 @@ __global__ __launch_bounds__(kBinWave) void rv_cross_kernel(int nb, int parts, c
     ring[i] = zero;
     acc[i][0] = acc[i][1] = acc[i][2] = acc[i][3] = 0.0;
   }
-  // blocks before p0 meet no input; Y0[b] and X[b - p0] are loaded kAhead blocks ahead
-  float4 xa[kAhead], ya[kAhead];
-#pragma unroll
-  for (int i = 0; i < kAhead; ++i) {
-    xa[i] = row_entry(xs, i, nb);
-    ya[i] = row_entry(ys, p0 + i, nb);
-  }
+  // blocks before p0 meet no input; Y0[b] and X[b - p0] are loaded a block ahead
+  float4 next_x = row_entry(xs, 0, nb), next_y = row_entry(ys, p0, nb);
   for (int b0 = p0; b0 < nb; b0 += kCrossTile) {
     float4 part[kCrossTile];
 #pragma unroll
@@ -588,23 +573,18 @@ __global__ __launch_bounds__(kBinWave) void rv_cross_kernel(int nb, int parts, c
     for (int j = 0; j < kCrossTile; ++j) {
       const int b = b0 + j;
       if (b < nb) {  // uniform
-      ring[j] = xa[0];  // X[b - p0]
-      const float4 y = ya[0];
+        ring[j] = next_x;  // X[b - p0]
+        const float4 y = next_y;
+        next_x = row_entry(xs, b - p0 + 1, nb);
+        next_y = row_entry(ys, b + 1, nb);
 #pragma unroll
-      for (int i = 0; i + 1 < kAhead; ++i) {
-        xa[i] = xa[i + 1];
-        ya[i] = ya[i + 1];
-      }
-      xa[kAhead - 1] = row_entry(xs, b - p0 + kAhead, nb);
-      ya[kAhead - 1] = row_entry(ys, b + kAhead, nb);
-#pragma unroll
-      for (int i = 0; i < kCrossTile; ++i) {  // partition p0 + i: X[b - p0 - i]
-        const float4 x = ring[(j - i + kCrossTile) % kCrossTile];
-        part[i].x = fma(y.x, x.x, fma(y.y, x.y, part[i].x));
-        part[i].y = fma(y.y, x.x, fma(-y.x, x.y, part[i].y));
-        part[i].z = fma(y.z, x.z, fma(y.w, x.w, part[i].z));
-        part[i].w = fma(y.w, x.z, fma(-y.z, x.w, part[i].w));
-      }
+        for (int i = 0; i < kCrossTile; ++i) {  // partition p0 + i: X[b - p0 - i]
+          const float4 x = ring[(j - i + kCrossTile) % kCrossTile];
+          part[i].x = fma(y.x, x.x, fma(y.y, x.y, part[i].x));
+          part[i].y = fma(y.y, x.x, fma(-y.x, x.y, part[i].y));
+          part[i].z = fma(y.z, x.z, fma(y.w, x.w, part[i].z));
+          part[i].w = fma(y.w, x.z, fma(-y.z, x.w, part[i].w));
+        }
       }
     }
 #pragma unroll
