@@ -248,8 +248,12 @@ __global__ __launch_bounds__(kBlock) void eq_fold_reduce_kernel(const float* Fpa
 // s[0] = hbar[0] and s[n] = v[n] (hbar[n] + hbar[-n]). FOLD (short rows, up to kFoldTiles tiles): the
 // block first forms the folded spectrum itself, in the order above, and the blocks after the nodes'
 // are the reduction jobs: one launch instead of three (4 nodes of 2^15 samples: 7.4 us, 3.3 + 4.8
-// + 4.3 us apart).
-constexpr int kFoldTiles = 32;
+// + 4.3 us apart). One block a node then sums all tiles, against 33 blocks in a launch of its own, so
+// the line lies at 16 tiles. Adjoint of 1, 4, 17, 48 EQ strips folded here and apart, us: 8 tiles 23.4,
+// 24.0, 26.8, 31.0 and 23.8, 24.6, 27.4, 31.9; 16 tiles 24.7, 25.4, 30.3, 38.3 and 24.8, 25.4, 30.3,
+// 39.1; 24 tiles 25.8, 26.9, 32.5, 47.0 and 25.6, 26.3, 32.2, 46.7; 32 tiles 26.9, 28.4, 38.2, 52.4
+// and 24.0, 25.4, 35.5, 51.4.
+constexpr int kFoldTiles = 16;
 template <bool FOLD>
 __global__ __launch_bounds__(kBlock) void eq_grad_ifft_kernel(const float* F, int tiles, int n_eq,
                                                               double* sbuf, ReduceJobs jobs) {

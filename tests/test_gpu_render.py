@@ -350,3 +350,10 @@ def test_source_adjoints(t, T, lone):
         for v in sched.out_dst[sched.out_ptr[k]:sched.out_ptr[k + 1]]:
             ref = ref + (dY[v - sched.out_begin] if v >= sched.out_begin else buf.dU[int(v)])
         assert torch.equal(dS[k].view(torch.int32), ref.view(torch.int32)), k
+
+
+@pytest.mark.parametrize("L", [2048 * 16, 2048 * 16 + 1])
+def test_eq_gradients_on_either_side_of_the_fold(L):
+    """The longest rows whose cross-spectra the transform's launch sums (16 tiles) and the shortest that
+    have a launch of their own (17): the same bits as in a graph merged with a longer one."""
+    test_eq_gradients_alone_and_merged(L)
