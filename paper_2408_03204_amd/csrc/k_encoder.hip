@@ -143,7 +143,7 @@ __device__ __forceinline__ void mma_chunk(const T* a, const T* b, f32x4 (&acc)[N
 // One layer over columns n = b * Fout + t: y[b][co][t] = ReLU(bias[co] + sum_{ci,k} W[co][ci][k]
 // x[b][ci][2t + k - 2]). A block computes all 64 channels of 16 NT columns, wave w the channels
 // 16 w .. 16 w + 15. K = Cin x 5 advances in chunks of CI input channels, staged in LDS while the
-// next chunk's loads are in flight. Two shapes: NT = 4, CI = 16 fills the CUs from about 200
+// next chunk's loads are in flight. Two shapes: NT = 4, CI = 16 fills the CUs from 140 to 190
 // blocks on (256 samples x 125 frames, layer 1, 2.6 GFLOP: 44 us, 61 TFLOP/s of the 154 that a
 // large float32 matrix product reaches; the six layers took 1105 us with one thread per output);
 // below that a chunk's load latency counts, and NT = 1, CI = 64 has four times the blocks and a
@@ -813,12 +813,15 @@ TailLayers tail_layers(const EncLayout& L, const float* weights, float* acts, fl
   return t;
 }
 
-// 64-column tiles from 200 blocks on, 16-column tiles below (same bits).
+// 64-column tiles where they give enough blocks, 16-column tiles below (same bits). Forward of frames of
+// 125, by blocks of 64 columns, us with 64 and with 16 columns: float32 99: 67.7 and 59.0, 148: 70.0 and
+// 72.0, 178: 69.9 and 72.7, 200: 70.2 and 84.9; bfloat16 148: 71.4 and 68.3, 178: 71.8 and 67.9, 200:
+// 71.4 and 74.2.
 template <bool BF16>
 void launch_conv_fwd(int B, int Cin, int Fin, int Fout, const float* x, const float* W,
                      const float* bias, float* y, hipStream_t s) {
   const int64_t n = (int64_t)B * Fout;
-  if (n >= 200 * 64)
+  if (n >= (BF16 ? 190 : 140) * 64)
     conv_fwd_kernel<BF16, 4, 16><<<(unsigned)((n + 63) / 64), kBlock, 0, s>>>(B, Cin, Fin, Fout, x,
                                                                              W, bias, y);
   else

@@ -239,3 +239,15 @@ def test_backward_within_its_scratch_and_without_a_loss(B, F):
                                         torch.cuda.current_stream().cuda_stream))
     torch.cuda.synchronize()
     assert torch.equal(dw, net.dw)
+
+
+@pytest.mark.parametrize("bf16,B", [(False, 142), (False, 143), (True, 193), (True, 194)])
+def test_forward_bits_on_either_side_of_the_wide_tiles(bf16, B):
+    """63 frames a sample after layer 1: the batches just below and from 140 (float32) or 190 (bfloat16)
+    blocks of 64 columns on; the same samples give the same bits as a small batch."""
+    x = torch.randn((B, 256, 125), generator=torch.Generator().manual_seed(4)).cuda() * 0.4
+    w = torch.as_tensor(_weights(1)[0]).cuda()
+    many = enc.Encoder(w, B, 125).forward(x, bf16=bf16)
+    few = enc.Encoder(w, 2, 125).forward(x[:2].contiguous(), bf16=bf16)
+    torch.cuda.synchronize()
+    assert torch.equal(many[:2], few)
