@@ -56,6 +56,7 @@ namespace {
 constexpr int kHalf = 19;                   // taps j = -19..19
 constexpr int kN = kDelayFFT;               // 512-point transforms
 constexpr int kHop = kN - 2 * kHalf;        // 474 outputs per tile
+constexpr int kReach = kHalf - 1;           // farthest tap that is not 0 (the Hann window's ends are)
 constexpr int kWaves = kBlock / 64;
 constexpr int kSlice = kN + kN / 8 + 2;     // LDS entries per wave (one pad per 8, element 512 = 0)
 
@@ -283,25 +284,33 @@ __device__ __forceinline__ void clear_dead(const Live& l, Bins& b) {
   }
 }
 
-// What is known of the zeros in the windows of two tiles. full: some slot's windows hold none (as most
-// do), so no output depends on zeros only. odd: some window holds zeros inside the signal of Tn samples;
-// if not, its zeros are the samples before the start or past the end.
+// What is known of the zeros in the windows of two tiles. reached: in some slot's windows they are too
+// few for a run as long as the filter (37, of which 19 would lie in one of the 64-sample words), so
+// every output depends on something else, as nearly always. odd: some window holds zeros inside the
+// signal of Tn samples; if not, its zeros are the samples before the start or past the end. live: some
+// window holds anything else.
 struct Zeros {
-  bool full = false, odd = false;
-  // z: the window whose first tile starts at sample t
-  __device__ __forceinline__ void add(const float2 (&z)[8], int t, int Tn) {
-    if (full) return;
+  bool reached = false, odd = false, live = false;
+  // z: the window whose first tile starts at sample t. False if it is all zero.
+  __device__ __forceinline__ bool add(const float2 (&z)[8], int t, int Tn) {
+    if (reached) return true;
     float m = INFINITY;
 #pragma unroll
     for (int i = 0; i < 8; ++i) m = fminf(fminf(fabsf(z[i].x), fabsf(z[i].y)), m);
-    full = __all(m > 0.f);
-    if (full) return;
-    int n = 0;
+    if (__all(m > 0.f)) return reached = live = true;
+    int n = 0, most = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      n += __popcll(__ballot(z[i].x == 0.f)) + __popcll(__ballot(z[i].y == 0.f));
+    for (int i = 0; i < 8; ++i) {
+      const int a = __popcll(__ballot(z[i].x == 0.f)), b = __popcll(__ballot(z[i].y == 0.f));
+      n += a + b;
+      most = max(most, max(a, b));
+    }
+    reached = most <= kReach;
     auto outside = [&](int a) { return min(max(-a, 0), kN) + min(max(a + kN - Tn, 0), kN); };
     odd = odd || n != outside(t) + outside(t + kHop);
+    const bool any = n != 2 * kN;
+    live = live || any;
+    return any;
   }
 };
 
@@ -327,11 +336,11 @@ __device__ __forceinline__ void see(const GraphView& g, int e0, int e1, int c, i
   lds_order();
 }
 
-// Whether any of the elements e - 19 .. e + 19 that output e = j + 64 r depends on was seen.
+// Whether any of the elements e - 18 .. e + 18 that output e = j + 64 r depends on was seen.
 __device__ __forceinline__ bool reached(const uint64_t* w, int r, int j) {
-  const int i = r - (j < kHalf), sh = (j + 64 - kHalf) & 63;  // of element e - 19
+  const int i = r - (j < kReach), sh = (j + 64 - kReach) & 63;  // of element e - 18
   const uint64_t lo = i >= 0 ? w[i >= 0 ? i : 0] : 0, hi = i < 7 ? w[i < 7 ? i + 1 : 7] : 0;
-  return (((lo >> sh) | (hi << 1 << (63 - sh))) & ((1ull << kDelayFir) - 1)) != 0;
+  return (((lo >> sh) | (hi << 1 << (63 - sh))) & ((1ull << (2 * kReach + 1)) - 1)) != 0;
 }
 
 // The tiles' samples as direct sums over a channel c: taps and d (delays) of the node, both channels.
@@ -411,11 +420,17 @@ __device__ __forceinline__ void tile_samples(int node, int c, int t0, int Tn, in
 #pragma unroll
   for (int r = 0; r < 8; ++r) t = fmaf(z[r].x, 0.f, fmaf(z[r].y, 0.f, t));
   const bool direct = __any(t != t);
-  if (!direct && zeros.full) return;
+  if (!direct && zeros.reached) return;
+  if (!direct && !zeros.live) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) z[r] = make_float2(0.f, 0.f);
+    return;
+  }
   if (!direct && !zeros.odd) {  // reached from the signal's start or end on
     int nearest = d[c * M];
     for (int m = 1; m < M; ++m) nearest = min(nearest, d[c * M + m]);
-    const int e = ADJ ? Tn - t0 + 2 * kHalf - nearest : nearest - t0;  // the first not, or the first, reached
+    // the first element that is not reached (adjoint), or the first that is
+    const int e = ADJ ? Tn - t0 + kHalf + kReach - nearest : nearest - t0 + kHalf - kReach;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       const int i = j + 64 * r;
@@ -550,7 +565,7 @@ __global__ __launch_bounds__(kBlock, 4) void delay_fwd_kernel(GraphView g, float
   for (int m = 0; m < M; ++m) {
     const int t = t0 - d[c * M + m] - kHalf;
     load_window<false>(g, e0, e1, c, t, j, z);
-    zeros.add(z, t, Tn);
+    if (!zeros.add(z, t, Tn)) continue;
     fft512<false>(z, s, tw, j);
     Bins b;
     separate(z, b, s, j);
@@ -647,7 +662,8 @@ __global__ __launch_bounds__(kBlock, 2) void delay_bwd_kernel(GraphView g, float
       }
       if (j == 0) {
         s[kN] = make_float2(acc.na, acc.nb);
-        s[kN + 1] = make_float2(zeros.full ? 1.f : 0.f, zeros.odd ? 1.f : 0.f);
+        s[kN + 1] = make_float2(zeros.reached ? 1.f : 0.f, zeros.odd ? 1.f : 0.f);
+        s[kN + 2] = make_float2(zeros.live ? 1.f : 0.f, 0.f);
       }
       __syncthreads();
       const bool mine = half == (tile >> 1 & 1);
@@ -661,8 +677,9 @@ __global__ __launch_bounds__(kBlock, 2) void delay_bwd_kernel(GraphView g, float
         const float2 n = sum(kN), f = sum(kN + 1);
         acc.na = n.x;
         acc.nb = n.y;
-        zeros.full = __builtin_amdgcn_readfirstlane((int)f.x) != 0;
+        zeros.reached = __builtin_amdgcn_readfirstlane((int)f.x) != 0;
         zeros.odd = __builtin_amdgcn_readfirstlane((int)f.y) != 0;
+        zeros.live = __builtin_amdgcn_readfirstlane((int)sum(kN + 2).x) != 0;
       }
       __syncthreads();
       if (!mine) continue;
