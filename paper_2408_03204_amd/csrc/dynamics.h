@@ -76,7 +76,7 @@ struct Ramp {
 // is a difference of whole numbers plus a part below 2 and carries an absolute error near 1e-7; the
 // logarithm of gs itself, up to 27 in size, would carry ten times that into the knee's derivatives
 // and the sums over all samples (parameter gradients against float64: 1.3-7.9e-7 -> 0.7-1.6e-7 for
-// 1 us of 81 on 48 compressors of 2^18 samples). A render keeps the one logarithm: there the error
+// 1 us of 82 on 48 compressors of 2^18 samples). A render keeps the one logarithm: there the error
 // moves one sample's gain by a millionth. NaN stays NaN (v_med3 and v_max alone would drop it).
 template <bool GATE, bool GRAD>
 __device__ __forceinline__ Ramp ramp(float gs, const CurveCoef& k) {

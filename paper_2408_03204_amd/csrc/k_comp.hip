@@ -22,8 +22,8 @@
 // prepare_kernel and read as scalars; lanes exchange by DPP moves and readlane, not through
 // LDS; both gain curves are one branch-free ramp in base-2 units (dynamics.h); the curve's
 // derivatives are scaled once per chunk instead of per sample; and a thread's first read of an
-// earlier total is under way during the parameter sums. The same strips: adjoint 102 -> 81 us,
-// forward 52 -> 51 us (there memory, 3.9 of 4.8 TB/s, is the bound).
+// earlier total is under way during the parameter sums. The same strips: adjoint 94 -> 82 us,
+// forward 51 us before and after (there memory, 3.9 of 4.8 TB/s, is the bound).
 //
 // A block's node comes from its block id; its chunk within the node comes from an atomic ticket
 // on that node's counter (one cache line per counter), taken when the block starts, so every
